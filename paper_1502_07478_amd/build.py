@@ -2,9 +2,11 @@
 
 from __future__ import annotations
 
+import concurrent.futures
 import glob
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -28,13 +30,25 @@ def sources():
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + f".tmp{os.getpid()}"
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
-           "-o", tmp, *sources()]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
+    log = []
+    with tempfile.TemporaryDirectory() as objs, concurrent.futures.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
+        def compile_one(src):
+            obj = os.path.join(objs, os.path.basename(src) + ".o")
+            return obj, subprocess.run([hipcc, *compile_flags, "-I", os.path.join(ROOT, "include"),
+                                        "-I", os.path.join(HERE, "csrc"), "-c", "-o", obj, src],
+                                       capture_output=True, text=True)
+        made = list(ex.map(compile_one, sources()))
+        link = [hipcc, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *(o for o, _ in made)]
+        for res in [r for _, r in made]:
+            if res.returncode != 0:
+                raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+            log += (res.stdout + res.stderr).splitlines()
+        res = subprocess.run(link, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed (link):\n" + res.stdout + res.stderr)
     if verbose:
-        out = "\n".join(l for l in (res.stdout + res.stderr).splitlines() if "packed-fp32-ops" not in l)
+        out = "\n".join(l for l in log if "packed-fp32-ops" not in l)
         if out.strip():
             print(out)
     os.replace(tmp, LIB)

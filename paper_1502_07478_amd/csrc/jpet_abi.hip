@@ -153,13 +153,72 @@ static size_t tiled_lds_layout(int pitch, int W, int RY, int acc32, int epb, boo
   return align_up(off + 4u * (size_t)RY, 16);
 }
 
+// Dynamic LDS of the pass on ring blocks: two buffers of a block's constants per wavefront, the per-row
+// column shifts, the image and the 32-bit accumulators, with the slack columns before the image (the
+// buffers are part of it) and after the accumulators.
+static size_t ring_lds_layout(int pitch, int W, int RY, int waves, int events, int slack, int* off_at, int* img_at) {
+  const size_t free = (size_t)slack * (size_t)pitch * 4u;
+  const size_t off = (size_t)waves * 2u * (size_t)events * sizeof(EvRow);
+  const size_t img = align_up(std::max(off + 4u * (size_t)RY, free), 256);
+  if (off_at) *off_at = (int)off;
+  if (img_at) *img_at = (int)img;
+  return img + 8u * (size_t)pitch * (size_t)W + free;
+}
+
+// The register cache of the pass on ring blocks for ellipses reaching hy_px rows and half_px pixels of a
+// row from their centres: 0 when none is compiled for them.
+static int ring_shape(double hy_px, double half_px) {
+  for (int shape : kRingShapes) {
+    const int rings = shape_rings(shape), half = shape >= 1000 ? 32 : 16;
+    // (two events per wavefront up to 95 rows, and more where their rows are long)
+    if (!(hy_px < (double)(half * rings) - 0.5)) continue;
+    bool fits = true;
+    for (int k = 0; k < rings; ++k) {
+      // ring k's rows lie at least k half - 1/2 rows from the ellipse's centre
+      const double f = k ? ((double)(half * k) - 0.5) / hy_px : 0.0;
+      const int row = f < 1.0 ? (int)floor(2.0 * half_px * sqrt(1.0 - f * f)) + 1 : 1;
+      if ((row + 1) / 2 > ring_half_of(rings, shape_len(shape), k)) fits = false;
+    }
+    if (fits) return shape;
+  }
+  return 0;
+}
+
+// Columns beside the region that the pass on ring blocks may touch: where ring k's rows of a shape reach
+// past the halo.  A row's centre lies within slope times its distance from the event's row (and a
+// column of rounding) of the event's column, which is in the tile.  (Blocks that would still reach
+// further take the exact form, which does not.)
+static int ring_slack(int shape, int HZ, double slope, double hy_px) {
+  const int half = shape >= 1000 ? 32 : 16;
+  int slack = 0;
+  for (int k = 0; k < shape_rings(shape); ++k) {
+    const double dy = std::min(hy_px, (double)(half * (k + 1)));
+    const int reach = ring_half_of(shape_rings(shape), shape_len(shape), k) + 1 + (int)ceil(slope * dy);
+    slack = std::max(slack, std::min(reach - HZ, ring_half_of(shape_rings(shape), shape_len(shape), k)));
+  }
+  return slack;
+}
+
+// Pairs of all events per pixel of the region below which a pass takes half as many items (measured at
+// 64 x 64 pixels, 20,000 events: 16 us for the pass instead of 22; at 128 x 128 and 48,000 events both
+// take 17 us, above that the larger items leave the last round of workgroups emptier).
+constexpr double kItemPairs = 7000.0;
+
 // Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set.
-static void finish_plan(const jpet_geometry* g, int rows_max, int64_t n, Plan& p) {
+static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, Plan& p) {
   const double pix = g->pixel;
-  p.ev_per_batch = events_per_batch(p.waves, rows_max * p.segs);
-  p.cbytes = p.ev_per_batch * event_const_bytes(p.loglik != 0);
-  p.lds_bytes = tiled_lds_layout(p.pitch, p.W, p.RY, p.acc32, p.ev_per_batch, p.loglik != 0, &p.lds_ev, &p.lds_off);
-  p.batch_bytes = (int)(((unsigned)p.cbytes + 4u * (64u + kBlockTailWords) * (unsigned)p.waves + 255u) / 256u * 256u);
+  if (p.rings) {
+    p.ev_per_batch = p.solo ? 1 : 2;
+    p.lds_bytes =
+        ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, &p.lds_off, &p.lds_img);
+    p.batch_bytes = ring_block_bytes(p.ev_per_batch, p.rings);
+  } else {
+    p.ev_per_batch = events_per_batch(p.waves, rows_max * p.segs);
+    p.cbytes = p.ev_per_batch * event_const_bytes(p.loglik != 0);
+    p.lds_bytes = tiled_lds_layout(p.pitch, p.W, p.RY, p.acc32, p.ev_per_batch, p.loglik != 0, &p.lds_ev, &p.lds_off);
+    p.batch_bytes =
+        (int)(((unsigned)p.cbytes + 4u * (64u + kBlockTailWords) * (unsigned)p.waves + 255u) / 256u * 256u);
+  }
   p.nty = (g->n_y + p.TY - 1) / p.TY;
   // sheared column span: the widest over the t bins
   int span = g->n_z;
@@ -176,8 +235,12 @@ static void finish_plan(const jpet_geometry* g, int rows_max, int64_t n, Plan& p
   // events per workgroup item: enough items to fill the chip, at most 128 batches (the region's
   // staging and flush are amortised over the item)
   int64_t per = n / 1024;
+  // ring blocks: where a workgroup's share of the events is worth less than staging and flushing the
+  // region, fewer and larger items
+  if (p.rings && (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W) per = n / 512;
   if (per < p.ev_per_batch) per = p.ev_per_batch;
-  if (per > 128 * p.ev_per_batch) per = 128 * p.ev_per_batch;
+  const int64_t most = p.rings ? 510 : 128 * p.ev_per_batch;
+  if (per > most) per = most;
   // 32-bit accumulators hold 2^-s units: one event adds at most 2^s to a pixel, so an item of up
   // to 2^(32-s) - 1 events cannot overflow before the flush.  Items of at most 511 events keep
   // s = 23 (a rounding step of 2^-23 of a count per pair).
@@ -191,7 +254,8 @@ static void finish_plan(const jpet_geometry* g, int rows_max, int64_t n, Plan& p
   const int64_t nonempty = n < p.nbins ? n : p.nbins;
   p.max_items = (n + p.ev_per_wg - 1) / p.ev_per_wg + nonempty;
   if (p.max_items < 1) p.max_items = 1;
-  p.max_batches = (n + p.ev_per_batch - 1) / p.ev_per_batch + nonempty;
+  // each bin rounds its events up to whole batches once
+  p.max_batches = (n + (p.ev_per_batch - 1) * nonempty) / p.ev_per_batch;
   if (p.max_batches < 1) p.max_batches = 1;
   p.tiled = 1;
 }
@@ -270,6 +334,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
         const double occ_factor = pow(4.0 / (double)occ, 0.58) * (waves == 16 ? 1.1 : 1.0) * (segs > 1 ? 1.3 : 1.0);
         for (int acc32 = 0; acc32 <= 1; ++acc32) {
           if (acc32 && !allow_acc32) continue;
+          const int shape = acc32 && segs == 1 ? ring_shape(hy_px, 0.5 * chord_px) : 0;
           for (int dti = 0; dti < kPlanDtCount; ++dti) {
             const double dt = kPlanDt[dti];
             // largest |t - t_c| / c inside a bin (no shear: |t| / c <= sin(atan(tmax)))
@@ -303,16 +368,43 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
               p.wgs = wgs;
               p.loglik = loglik ? 1 : 0;
               p.code = plan_code(waves, acc32, wgs, dti, ti, cache);
+              // ring blocks where a cache holds a whole event's rows and the LDS still lets as many
+              // wavefronts run as the registers do (that many, shared by the workgroups of the code)
+              int simd = occ;
+              if (shape && (pitch == shape_pitch(shape, 0) || pitch == shape_pitch(shape, 1))) {
+                const int most = 4 * shape_waves_per_simd(shape);
+                const int fit = std::max(1, std::min(wgs, most / waves)), each = std::min(waves, most / fit);
+                const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
+                if (ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, nullptr, nullptr) <=
+                    kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
+                  p.rings = shape_rings(shape);
+                  p.solo = shape >= 1000;
+                  p.ring_len = shape_len(shape);
+                  for (int k = 0; k < p.rings; ++k) p.ring_half[k] = ring_half_of(p.rings, p.ring_len, k);
+                  p.slack = slack;
+                  p.waves = each;
+                  const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, nullptr, nullptr);
+                  simd = std::min(most / each, (int)(kLdsPerCU / align_up(lds + 256, kGranule))) * each / 4;
+                }
+              }
               if (dt != 0.0) {
                 p.ntb = (int)ceil(2.0 * tmax / dt);
                 if (p.ntb < 1) p.ntb = 1;
                 p.dt = dt;
                 p.tmin = -0.5 * dt * p.ntb;
               }
-              finish_plan(g, rows_max, n, p);
-              const double items = nn / p.ev_per_wg + (nn < p.nbins ? nn : (double)p.nbins);
-              const double cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
-                                  1.6 * items * (double)pitch * (double)W;
+              finish_plan(g, rows_max, pairs_per_event, n, p);
+              double cost;
+              if (loglik) {
+                const double items = nn / p.ev_per_wg + (nn < p.nbins ? nn : (double)p.nbins);
+                cost = nn * pairs_per_event * occ_factor + 1.6 * items * (double)pitch * (double)W;
+              } else {
+                const double some = 0.35 * (double)p.nbins;  // the bins an object fills
+                const double items = nn / p.ev_per_wg + some * (1.0 - exp(-nn / some));
+                const double unit = p.rings ? 0.5 * pow(4.0 / (double)simd, 0.58) * (p.waves == 16 ? 1.05 : 1.0)
+                                            : occ_factor * (acc32 ? 0.82 : 1.0);
+                cost = nn * pairs_per_event * unit + 4.5 * items * (double)RY * (double)W;
+              }
               out->push_back({p, cost});
             }
           }
@@ -374,6 +466,7 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
   w.bin_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.bin_fill = (uint32_t*)take(sizeof(uint32_t) * nb);
   w.item_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
+  w.rest_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.batch_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.items = (BinItem*)take(p.tiled ? sizeof(BinItem) * (size_t)p.max_items : 0);
   w.bytes = off;
@@ -391,7 +484,7 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
 // pass follow the classes, with their own launches.
 struct BatchClass {
   int first = 0, count = 0;  // table positions
-  int maxlen = 0, waves = 0, wgs = 0;
+  int kernel = 0, waves = 0, wgs = 0;  // kernel: see pass_kernel
   int pitch = 0;             // region row pitch the class is compiled for (0: a runtime value)
   size_t lds = 0;
   int64_t items = 0;         // workgroup items of the class's instances (set once they are prepared)
@@ -449,7 +542,7 @@ BatchLayout batch_layout(const jpet_instance* inst, int count) {
     }
     L.plan[k] = p;
     if (p.tiled) {
-      key[k] = ((batched_pitch_class(p.pitch) * 128 + p.maxlen) * 32 + p.waves) * 8 + p.wgs;
+      key[k] = ((batched_pitch_class(p.pitch) * 2048 + pass_kernel(p)) * 32 + p.waves) * 8 + p.wgs;
       // pixels of a typical ellipse (App. B half sizes at theta = 0) times events per workgroup
       work[k] = (1.5 * g.sigma_dl / g.pixel) * (3.0 * g.sigma_z / sqrt(2.0) / g.pixel) * p.ev_per_wg;
     }
@@ -476,7 +569,7 @@ BatchLayout batch_layout(const jpet_instance* inst, int count) {
     }
     BatchClass& c = L.cls.back();
     ++c.count;
-    c.maxlen = p.maxlen > c.maxlen ? p.maxlen : c.maxlen;
+    c.kernel = pass_kernel(p);  // the same for the whole class
     if (p.lds_bytes > c.lds) c.lds = p.lds_bytes;
   }
   size_t off = align_up(sizeof(BatchInst) * (size_t)count, 256);
@@ -1084,7 +1177,7 @@ static int batched_iterations(const jpet_instance* inst, int32_t count, int32_t 
         for (int q = 1; q < ns && r == hipSuccess; ++q) r = hipStreamWaitEvent(side.s[q - 1], side.fork, 0);
         for (size_t i = 0; i < L.launch.size() && r == hipSuccess; ++i) {
           const BatchClass& C = L.cls[(size_t)L.launch[i]];
-          r = launch_event_pass_batched(table + C.first, C.count, C.maxlen, C.waves, C.pitch, C.lds, C.items,
+          r = launch_event_pass_batched(table + C.first, C.count, C.kernel, C.waves, C.pitch, C.lds, C.items,
                                         C.stream > 0 ? side.s[C.stream - 1] : st);
         }
         for (int q = 1; q < ns && r == hipSuccess; ++q) {
@@ -1129,8 +1222,8 @@ static int batched_begin(const jpet_instance* inst, int32_t count, void* ws, siz
     const BatchClass& C = L->cls[c];
     size_t lds = C.lds;
     for (const BatchClass& D : L->cls)
-      if (D.maxlen == C.maxlen && D.waves == C.waves && D.pitch == C.pitch && D.lds > lds) lds = D.lds;
-    const hipError_t e = set_batched_lds(C.maxlen, C.waves, C.pitch, lds);
+      if (D.kernel == C.kernel && D.waves == C.waves && D.pitch == C.pitch && D.lds > lds) lds = D.lds;
+    const hipError_t e = set_batched_lds(C.kernel, C.waves, C.pitch, lds);
     if (e != hipSuccess) return hip_fail(e);
   }
   std::vector<int64_t> item_begin;

@@ -76,8 +76,8 @@ struct EvRow {
   float S0, S1, S2, GB0, GB1;
   float Q0, Q1, Q2;
   float qa, QB, s2u;
-  int32_t index;  // position of the event in the caller's array
-  int32_t pad;
+  int32_t index;  // position of the event in the caller's array (ring blocks: -1 for no event)
+  int32_t mid;    // ring blocks: the region row of the event's central row
 };
 
 static_assert(sizeof(EvRow) == 80, "EvRow is copied to LDS in 16-byte units");
@@ -90,14 +90,27 @@ constexpr uint32_t kWordCol = 0, kWordRow = 8, kWordLen = 17, kWordEv = 24;
 // A batch block: ev_per_batch per-event constants (EvRow for the MLEM pass, EvConst for the
 // log-likelihood pass), then one thread word per thread of the workgroup, then two words per
 // wavefront:
-//   its longest row (pixels; bit kGuardBit set when a row of the wavefront may reach kappa <= 0 and
-//   needs the per-pixel test);
+//   its longest row (pixels, bits 0-6) and, from bit kModeShift, how its rows' kernel is evaluated:
+//   kRowPoly5 or kRowPoly6 as the exponential of a polynomial of that degree, kRowExact pixel by
+//   pixel with the kappa <= 0 test (log-likelihood pass: kRowExact where a row may reach kappa <= 0,
+//   else 0);
 //   its shortest non-empty row (bits 0-7) and, with bit kHalfBit set, the one event of each
 //   half-wavefront's rows: lanes 0-31 in bits 8-12, lanes 32-63 in bits 16-20 (a half with no rows
 //   names the other half's event).
 constexpr int kBlockTailWords = 2;
-constexpr uint32_t kGuardBit = 31;
+constexpr uint32_t kModeShift = 30, kRowPoly5 = 0, kRowPoly6 = 1, kRowExact = 2;
 constexpr uint32_t kHalfBit = 31, kHalfLo = 8, kHalfHi = 16;
+
+// A ring block (plans with rings > 0) holds the two events, or the one, that a wavefront takes together:
+// their EvRow (polynomials in the rows from the event's central row on), at ring_tails one 16-bit tail
+// per ring (its longest row in bits 0-6, its shortest non-empty row in bits 7-13, from bit 14 how its
+// rows are evaluated: kRowExact for all rings or none), at ring_words one 32-bit word per lane for
+// every two rings.  With n = 32 (two events) or 64 lanes per event, lane l's row in ring k is row
+// l - n/2 + k (l < n/2 ? -n/2 : n/2) from its event's central row, l = lane mod n; its 16 bits hold the
+// row's first column (sheared, region-local) in bits 0-7 and its pixels (0: no row) in bits 8-14.
+constexpr int ring_tails(int events) { return events * (int)sizeof(EvRow); }
+constexpr int ring_words(int events) { return ring_tails(events) + 16; }
+constexpr int ring_block_bytes(int events, int rings) { return ring_words(events) + 256 * ((rings + 1) / 2); }
 
 // Spatial binning of events and launch shape of the tiled event pass.
 //
@@ -136,7 +149,56 @@ struct Plan {
   // two buffers of cbytes (the current and the next batch's constants), then at lds_off one
   // int per region row (its sheared column shift)
   int lds_ev, lds_off;
+  // ring blocks instead of batches of rows (rings = 0: batches): rings of 32 (solo: 64) rows per event,
+  // the register cache's pixels per row of the innermost ring and pairs of pixels of ring k's rows
+  // (ring_half_of), the image's place in LDS, the columns of slack beside the region
+  int rings, solo, ring_len, lds_img, slack;
+  int ring_half[4];
 };
+
+// Pairs of pixels (x = i + 1/2 and -(i + 1/2) from a row's centre) that ring k's rows of a cache of len
+// pixels may have: with n/2 = 16 or 32 rows per half ring, ring k's rows lie at least k n/2 - 1 rows from
+// the ellipse's centre, and the ellipse reaches at most rings n/2 rows to either side, so they are
+// shorter than the longest row by sqrt(1 - ((16 k - 1) / (16 rings))^2) or more (per mille below,
+// rounded up).  Plans check their rows against it.
+constexpr int ring_half_of(int rings, int len, int k) {
+  const int permille = k == 0        ? 1000
+                       : rings == 2 ? 884
+                       : rings == 3 ? (k == 1 ? 950 : 764)
+                                    : (k == 1 ? 973 : k == 2 ? 875 : 679);
+  return (len * permille + 1999) / 2000;
+}
+
+// The register caches the pass on ring blocks is compiled for: 1000 (one event per wavefront) + 100
+// rings + innermost length.  Ellipses of up to 95 rows go two to a wavefront, taller ones (and those
+// of long rows) alone, in rings of 64 rows.
+constexpr int kRingShapes[] = {108,  112,  116,  124,  210,  214,  218,  222,  228,  314,  318,
+                               322,  326,  1132, 1148, 1164, 1216, 1222, 1228, 1236, 1248, 1264,
+                               1318, 1324, 1332, 1344, 1354, 1364, 1420, 1428, 1440, 1454};
+constexpr int shape_rings(int shape) { return shape % 1000 / 100; }
+constexpr int shape_len(int shape) { return shape % 100; }
+// Wavefronts per SIMD a shape is compiled for: the cache and some 50 registers beside it fit the 64, 80,
+// 128, 168 or 256 registers that leaves.
+constexpr int shape_waves_per_simd(int shape) {
+  int cache = 0;
+  for (int k = 0; k < shape_rings(shape); ++k) cache += 2 * ring_half_of(shape_rings(shape), shape_len(shape), k);
+  return cache <= 16 ? 8 : cache <= 34 ? 6 : cache <= 72 ? 4 : cache <= 120 ? 3 : 2;
+}
+constexpr int shape_threads(int shape) {
+  return 256 * shape_waves_per_simd(shape) < 1024 ? 256 * shape_waves_per_simd(shape) : 1024;
+}
+// The two region row pitches a shape is compiled for (words; the rows and halo of its ellipses, and a
+// tile, give no other unless the tile is large).
+constexpr int shape_pitch(int shape, int which) {
+  const int rows = shape_rings(shape) * (shape >= 1000 ? 64 : 32);
+  const int first = rows <= 64 ? 64 : rows <= 128 ? 128 : rows <= 192 ? 192 : 256;
+  return first + 64 * which;
+}
+// The event pass's kernel as a number (a batch's classes): the register cache of the pass on batches of
+// rows, or 10000 + the shape.
+inline int pass_kernel(const Plan& p) {
+  return p.rings ? 10000 + 1000 * p.solo + 100 * p.rings + p.ring_len : p.maxlen;
+}
 
 // Bytes of the per-event constants of one event in a batch block.
 inline int event_const_bytes(bool loglik) { return loglik ? (int)sizeof(EvConst) : (int)sizeof(EvRow); }
@@ -191,7 +253,8 @@ struct Workspace {
   uint32_t* bin_count;        // [nbins]
   uint32_t* bin_start;        // [nbins + 1]
   uint32_t* bin_fill;         // [nbins]
-  uint32_t* item_start;       // [nbins + 1]
+  uint32_t* item_start;       // [nbins + 1] full workgroup items before each bin
+  uint32_t* rest_start;       // [nbins + 1] bins before each that also make a shorter item
   uint32_t* batch_start;      // [nbins + 1] first batch block of each bin
   BinItem* items;             // [max_items]
   unsigned long long* acc;    // [npix] back-projection accumulator, units of 2^-32
@@ -249,6 +312,29 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
 
 // Records e as this thread's last HIP error (jpet_last_hip_error) and returns JPET_EHIP.
 int record_hip_failure(hipError_t e);
+
+// The binned passes compiled for a register cache of MAXLEN pixels per row (one source file each, so
+// that they compile side by side).
+template <int MAXLEN>
+struct Binned {
+  static hipError_t event_pass(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
+                               hipStream_t st);
+  static hipError_t loglik(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
+                           bool value_only, hipStream_t st);
+  static hipError_t batched(const BatchInst* table, int count, int waves, int pitch, unsigned items, size_t lds_bytes,
+                            hipStream_t st);
+  static const void* batched_kernel(int waves, int pitch);
+};
+
+// The pass on ring blocks, compiled for one shape of the register cache.
+template <int SHAPE>
+struct Rings {
+  static hipError_t event_pass(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
+                               hipStream_t st);
+  static hipError_t batched(const BatchInst* table, int count, int waves, int pitch, unsigned items, size_t lds_bytes,
+                            hipStream_t st);
+  static const void* batched_kernel(int waves, int pitch);
+};
 
 // Kernel launchers (return the hipError_t of the launch).
 hipError_t launch_sensitivity(const Geo& g, float* s, hipStream_t st);

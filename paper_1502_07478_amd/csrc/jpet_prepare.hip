@@ -113,56 +113,47 @@ __global__ void __launch_bounds__(256) k_histogram(const uint32_t* __restrict__ 
   if (j < n && key[j] != kNoBin) atomicAdd(&bin_count[key[j]], 1u);
 }
 
-// Single workgroup: exclusive scans of the bin sizes, of the workgroup items per bin and of the
-// batch blocks per bin.
+// Single workgroup: exclusive scans over the bins of the events, of the full workgroup items, of the
+// items a bin's rest makes and of the batch blocks.
 __global__ void __launch_bounds__(1024) k_scan(int nbins, int ev_per_wg, int ev_per_batch,
                                                const uint32_t* __restrict__ bin_count, uint32_t* __restrict__ bin_start,
-                                               uint32_t* __restrict__ item_start, uint32_t* __restrict__ batch_start,
+                                               uint32_t* __restrict__ item_start, uint32_t* __restrict__ rest_start,
+                                               uint32_t* __restrict__ batch_start,
                                                unsigned long long* __restrict__ cnt) {
-  __shared__ uint32_t s_ev[1024], s_it[1024], s_ba[1024];
+  __shared__ uint4 s_sum[1024];
   const int T = blockDim.x;
   const int chunk = (nbins + T - 1) / T;
   const int lo = min(nbins, (int)threadIdx.x * chunk), hi = min(nbins, lo + chunk);
-  uint32_t se = 0, si = 0, sb = 0;
-  for (int b = lo; b < hi; ++b) {
-    const uint32_t c = bin_count[b];
-    se += c;
-    si += (c + ev_per_wg - 1) / ev_per_wg;
-    sb += (c + ev_per_batch - 1) / ev_per_batch;
-  }
-  s_ev[threadIdx.x] = se;
-  s_it[threadIdx.x] = si;
-  s_ba[threadIdx.x] = sb;
+  auto of_bin = [&](uint32_t c) {  // events, full items, rest, batches
+    return make_uint4(c, c / ev_per_wg, c % ev_per_wg ? 1u : 0u, (c + ev_per_batch - 1) / ev_per_batch);
+  };
+  auto plus = [](uint4 a, uint4 b) { return make_uint4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
+  uint4 sum = make_uint4(0, 0, 0, 0);
+  for (int b = lo; b < hi; ++b) sum = plus(sum, of_bin(bin_count[b]));
+  s_sum[threadIdx.x] = sum;
   __syncthreads();
   for (int off = 1; off < T; off <<= 1) {
-    uint32_t ae = 0, ai = 0, ab = 0;
-    if ((int)threadIdx.x >= off) {
-      ae = s_ev[threadIdx.x - off];
-      ai = s_it[threadIdx.x - off];
-      ab = s_ba[threadIdx.x - off];
-    }
+    uint4 a = make_uint4(0, 0, 0, 0);
+    if ((int)threadIdx.x >= off) a = s_sum[threadIdx.x - off];
     __syncthreads();
-    s_ev[threadIdx.x] += ae;
-    s_it[threadIdx.x] += ai;
-    s_ba[threadIdx.x] += ab;
+    s_sum[threadIdx.x] = plus(s_sum[threadIdx.x], a);
     __syncthreads();
   }
-  uint32_t re = threadIdx.x ? s_ev[threadIdx.x - 1] : 0u, ri = threadIdx.x ? s_it[threadIdx.x - 1] : 0u,
-           rb = threadIdx.x ? s_ba[threadIdx.x - 1] : 0u;
+  uint4 run = threadIdx.x ? s_sum[threadIdx.x - 1] : make_uint4(0, 0, 0, 0);
   for (int b = lo; b < hi; ++b) {
-    const uint32_t c = bin_count[b];
-    bin_start[b] = re;
-    item_start[b] = ri;
-    batch_start[b] = rb;
-    re += c;
-    ri += (c + ev_per_wg - 1) / ev_per_wg;
-    rb += (c + ev_per_batch - 1) / ev_per_batch;
+    bin_start[b] = run.x;
+    item_start[b] = run.y;
+    rest_start[b] = run.z;
+    batch_start[b] = run.w;
+    run = plus(run, of_bin(bin_count[b]));
   }
   if (threadIdx.x == T - 1) {
-    bin_start[nbins] = s_ev[T - 1];
-    item_start[nbins] = s_it[T - 1];
-    batch_start[nbins] = s_ba[T - 1];
-    cnt[C_ITEMS] = s_it[T - 1];
+    const uint4 all = s_sum[T - 1];
+    bin_start[nbins] = all.x;
+    item_start[nbins] = all.y;
+    rest_start[nbins] = all.z;
+    batch_start[nbins] = all.w;
+    cnt[C_ITEMS] = (unsigned long long)all.y + all.z;
   }
 }
 
@@ -177,22 +168,25 @@ __global__ void __launch_bounds__(256) k_scatter(const EventRec* __restrict__ ev
   evs[pos] = ev[j];
 }
 
+// The full items of all bins come first, then the bins' rests: the pass's workgroups are dispatched in
+// this order, so the short ones fill the chip's last round.
 __global__ void __launch_bounds__(256) k_items(int nbins, int ev_per_wg, int ev_per_batch,
                                                const uint32_t* __restrict__ bin_count,
                                                const uint32_t* __restrict__ bin_start,
                                                const uint32_t* __restrict__ item_start,
+                                               const uint32_t* __restrict__ rest_start,
                                                const uint32_t* __restrict__ batch_start, BinItem* __restrict__ items) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= nbins) return;
-  const uint32_t c = bin_count[b];
-  uint32_t q = item_start[b];
-  for (uint32_t s = 0; s < c; s += ev_per_wg, ++q) {
+  const uint32_t c = bin_count[b], full = c / (uint32_t)ev_per_wg;
+  for (uint32_t i = 0; i * ev_per_wg < c; ++i) {
+    const uint32_t s = i * ev_per_wg;
     BinItem it;
     it.bin = b;
     it.start = (int32_t)(bin_start[b] + s);
     it.count = (int32_t)min((uint32_t)ev_per_wg, c - s);
     it.batch = (int32_t)(batch_start[b] + s / ev_per_batch);
-    items[q] = it;
+    items[i < full ? item_start[b] + i : item_start[nbins] + rest_start[b]] = it;
   }
 }
 
@@ -237,8 +231,48 @@ __device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int rbase,
   k.QB = (float)(2.0 * s2u * pix);
   k.s2u = (float)s2u;
   k.index = e.index;
-  k.pad = 0;
+  k.mid = 0;
   return k;
+}
+
+// The pixel row nearest to an event's point (it may lie outside the grid).
+__device__ inline int centre_row(const Geo& g, const EventRec& e) {
+  return (int)floor((e.y - g.y0) * g.ipix + 0.5);
+}
+
+// How the event pass may evaluate the n pixels of a row segment from column klo on.  kappa is affine
+// along the row: unless it keeps a margin of 1e-3 of its first value at both ends, the pixels need
+// the kappa <= 0 test (kRowExact).  Otherwise the exponent of the kernel is expanded about the
+// segment's centre in y = delta x (the pass's RowP, with the same names): the remainder after x^5 is
+// at most (w x^2 y^4 + log2(e)/2 y^6 / 6) / (1 - y), beside log2(e)/2 (y^4 / 12 + 2 y^5 / 15) for the
+// logarithm's last two terms (taken as -delta times the one before), that after the economised x^7 and x^8 at
+// most w x^2 (y^5 / 64 + y^6 / 128 + y^7 / (1 - y)) + log2(e)/2 (y^7 / 448 + y^8 / 1024 + y^9 / (9 (1 - y))),
+// at the segment's end.
+// The polynomial is taken while that stays below 1e-7 in the exponent (base 2), under the rounding of
+// S q, and while no slot of the register cache, pixels past the segment's ends included, can
+// overflow.  Where the line lies: of prod400's rows all take x^5, of the paper's setting (R = 130 mm,
+// sigma_z = 10 mm) half need x^6 and few the exact form.
+__device__ inline int row_mode(const Geo& g, const Plan& p, const EventRec& e, int i, int klo, int n) {
+  double kf, ks;
+  const RowK r = row_constants(g, e, i, klo, &kf, &ks);
+  const double kend = kf + (double)(n - 1) * ks;
+  if (!(kf > 1e-3 * fabs(kf) && kend > 1e-3 * fabs(kf))) return kRowExact;
+  if (!p.rings) return 0;
+  const float L = (float)kHalfLog2e, mid = 0.5f * (float)(n - 1), M = 0.5f * (float)(n + 1), H = 0.5f * (float)p.ring_len;
+  const float kc = (float)(kf + 0.5 * (double)(n - 1) * ks), rq = __builtin_amdgcn_rsqf(kc);
+  const float dl = (float)ks * rq * rq, y = fabsf(dl) * M;
+  const float h0 = fmaf(mid, r.dgs, r.gs0) * rq, h1 = r.dgs * rq, d = h1 - dl * h0, w = d * d;
+  const float b1 = fmaf(mid, r.pix, r.b10), qa = r.a2 * r.pix * r.pix, qb = 2.0f * r.a2 * r.pix * b1;
+  // the exponent at any slot (|x| <= H + 1)
+  const float X = H + 1.0f, z = fabsf(dl) * X, c1 = h0 * (h1 + d) - L * dl - qb, c2 = w + 0.5f * L * dl * dl - qa;
+  const float most = fabsf(c1) * X + fmaxf(c2, 0.0f) * X * X + 2.0f * (w * X * X + L) * z * (1.0f + z * (1.0f + z * (1.0f + z)));
+  if (!(most < 100.0f) || !(y < 0.25f)) return kRowExact;
+  const float wm = w * M * M, y2 = y * y, y4 = y2 * y2, q = 1.0f / (1.0f - y);
+  if ((wm * y4 + L * y4 * y2 / 6.0f) * q + L * y4 * (1.0f / 12.0f + 2.0f / 15.0f * y) < 1e-7f) return kRowPoly5;
+  const float y5 = y4 * y, y6 = y4 * y2, y7 = y6 * y;
+  if (wm * (y5 / 64.0f + y6 / 128.0f + y7 * q) + L * (y7 / 448.0f + y4 * y4 / 1024.0f + y7 * y2 * q / 9.0f) < 1e-7f)
+    return kRowPoly6;
+  return kRowExact;
 }
 
 // Batch blocks of the binned pass: one workgroup per item builds, for each batch of ev_per_batch
@@ -386,7 +420,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       ri = qq < top ? qq : (grp_n[gi] >> 1) + 16 * K_s[gi] + (qq - top);
     }
     uint32_t word = 0u;
-    bool guard = false;  // this segment may reach kappa <= 0: the pass tests every pixel
+    int mode = 0;  // how the pass evaluates this segment (kRowPoly5, kRowPoly6, kRowExact)
     if (gi >= 0) {
       const int e = gi < nb ? gi : gi - nb;
       const EventRec ev = ev_s[e];
@@ -408,13 +442,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
           } else {
             word = ((uint32_t)kl << kWordCol) | ((uint32_t)rl << kWordRow) | ((uint32_t)n << kWordLen) |
                    ((uint32_t)e << kWordEv);
-            // kappa is affine along the row: its smallest value is at one of the segment's two
-            // ends; segments whose ends both keep a margin of 1e-3 of the first value can skip
-            // the test
-            double kf, ks;
-            (void)row_constants(g, ev, i, klo, &kf, &ks);
-            const double kend = kf + (double)(n - 1) * ks;
-            guard = !(kf > 1e-3 * fabs(kf) && kend > 1e-3 * fabs(kf));
+            mode = row_mode(g, p, ev, i, klo, n);
           }
         }
       }
@@ -424,7 +452,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       const int len = (int)((word >> kWordLen) & 127u);
       const int wl = wave_max_i(len);
       const int wmin = -wave_max_i(len > 0 ? -len : -wl);  // shortest non-empty row (0: none)
-      const bool wguard = __any(guard);
+      const int wmode = wave_max_i(mode);
       // does each half-wavefront hold rows of one event only (the pass then reduces the
       // denominators per half, without the per-event loop)?
       const int ev = (int)((word >> kWordEv) & 31u);
@@ -439,7 +467,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       if (!(act & 0xffffffffull)) ev_lo = ev_hi;
       if (!(act >> 32)) ev_hi = ev_lo;
       if (lane == 0) {
-        words[64 * p.waves + (tid >> 6)] = (uint32_t)wl | (wguard ? 1u << kGuardBit : 0u);
+        words[64 * p.waves + (tid >> 6)] = (uint32_t)wl | ((uint32_t)wmode << kModeShift);
         words[65 * p.waves + (tid >> 6)] =
             (uint32_t)wmin |
             (split ? 0u : (1u << kHalfBit) | ((uint32_t)ev_lo << kHalfLo) | ((uint32_t)ev_hi << kHalfHi));
@@ -448,6 +476,80 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
   }
   __syncthreads();
   if (tid == 0 && outside_s) atomicAdd(&cnt[C_OUTSIDE], (unsigned long long)outside_s);
+}
+
+// Ring blocks (plans with rings): one workgroup per item, first the row constants of its events, one
+// per thread, then one wavefront per block, one lane per row of its event and ring.
+__global__ void __launch_bounds__(512) k_build_rings(Geo g, Plan p, const EventRec* __restrict__ evs,
+                                                     const BinItem* __restrict__ items,
+                                                     unsigned char* __restrict__ blocks,
+                                                     unsigned long long* __restrict__ cnt) {
+  if ((unsigned long long)blockIdx.x >= cnt[C_ITEMS]) return;
+  const BinItem it = items[blockIdx.x];
+  const int tz = it.bin % p.ntz;
+  const int rest = it.bin / p.ntz;
+  const int ty = rest % p.nty;
+  const double tc = bin_slope(p, rest / p.nty);
+  const int kmin = -max(shear_offset(g, tc, 0), shear_offset(g, tc, g.n_y - 1));
+  const int rbase = ty * p.TY - p.HY;
+  const int kbase = kmin + tz * p.TZ - p.HZ;
+  const int epb = p.ev_per_batch, lpe = WAVE / epb;  // events per block, lanes per event
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), l = lane & (lpe - 1);
+  const int nblk = (it.count + epb - 1) / epb;
+  unsigned char* const blk0 = blocks + (size_t)it.batch * (size_t)p.batch_bytes;
+  for (int e = tid; e < nblk * epb; e += blockDim.x) {
+    const EventRec ev = evs[it.start + min(e, it.count - 1)];
+    // polynomials in the rows from the event's central row on: the rounding of their coefficients
+    // then stays below that of the rows' own values
+    const int mid = centre_row(g, ev);
+    EvRow k = event_row_constants(g, ev, mid, kbase);
+    k.mid = mid - rbase;
+    if (e >= it.count) k.index = -1;  // no event
+    reinterpret_cast<EvRow*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes)[e % epb] = k;
+  }
+  int outside = 0;
+  for (int q = tid >> 6; q < nblk; q += blockDim.x >> 6) {
+    unsigned char* const blk = blk0 + (size_t)q * (size_t)p.batch_bytes;
+    const int e = epb * q + lane / lpe;
+    EventRec ev = evs[it.start + min(e, it.count - 1)];
+    if (e >= it.count) ev.r1 = ev.r0 - 1;
+    const int mid = centre_row(g, ev);
+    uint32_t tails[4] = {0, 0, 0, 0}, word = 0;
+    int mode = 0;
+    for (int k = 0; k < p.rings; ++k) {
+      const int i = mid + l - lpe / 2 + k * (l < lpe / 2 ? -lpe / 2 : lpe / 2);
+      uint32_t w = 0;
+      int klo, khi, m = 0;
+      if (i >= ev.r0 && i <= ev.r1 && row_interval(g, ev, i, &klo, &khi)) {
+        const int n = khi - klo + 1, rl = i - rbase, kl = klo - shear_offset(g, tc, i) - kbase;
+        if (rl < 0 || rl >= p.RY || kl < 0 || kl + n > p.W || n > 2 * p.ring_half[k]) {
+          ++outside;
+        } else {
+          w = (uint32_t)kl | ((uint32_t)n << 8);
+          m = row_mode(g, p, ev, i, klo, n);
+        }
+      }
+      const int len = (int)(w >> 8), wl = wave_max_i(len), wmin = -wave_max_i(len > 0 ? -len : -wl);
+      // the chunks of two pairs the pass runs for this ring, from the row's centre, stay in the region and
+      // its slack
+      const int kc = (int)(w & 255u) + (len >> 1), reach = min(p.ring_half[k], (((wl + 1) >> 1) + 1) & ~1);
+      if (len > 0 && (kc - reach < -p.slack || kc + reach > p.W + p.slack)) m = (int)kRowExact;
+      m = wave_max_i(m);
+      mode = max(mode, m);
+      tails[k] = (uint32_t)wl | ((uint32_t)wmin << 7) | ((uint32_t)m << 14);
+      word |= w << (16 * (k & 1));
+      if ((k & 1) || k + 1 == p.rings) {
+        reinterpret_cast<uint32_t*>(blk + ring_words(epb))[(k >> 1) * WAVE + lane] = word;
+        word = 0;
+      }
+    }
+    if (mode == (int)kRowExact)  // one row of a block that needs the exact form: all take it
+      for (int k = 0; k < 4; ++k) tails[k] = (tails[k] & 0x3fffu) | (kRowExact << 14);
+    if (lane == 0)
+      for (int k = 0; k < 4; ++k) reinterpret_cast<uint16_t*>(blk + ring_tails(epb))[k] = (uint16_t)tails[k];
+  }
+  outside = (int)wave_sum_u64((unsigned long long)outside);
+  if (lane == 0 && outside) atomicAdd(&cnt[C_OUTSIDE], (unsigned long long)outside);
 }
 
 int blocks_for(int64_t n, int block) { return (int)((n + block - 1) / block); }
@@ -465,14 +567,17 @@ hipError_t launch_prepare(const Geo& g, const Plan& p, const float* events, int6
   hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(nb, 256)), dim3(256), 0, st, ws.bin_fill, nb);
   if (n > 0) hipLaunchKernelGGL(k_histogram, dim3(blocks_for(n, 256)), dim3(256), 0, st, ws.key, n, ws.bin_count);
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, p.nbins, p.ev_per_wg, p.ev_per_batch, ws.bin_count,
-                     ws.bin_start, ws.item_start, ws.batch_start, ws.cnt);
+                     ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.cnt);
   if (n > 0) {
     hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, st, ws.ev, ws.key, n, ws.bin_start,
                        ws.bin_fill, ws.evs);
   }
   hipLaunchKernelGGL(k_items, dim3(blocks_for(nb, 256)), dim3(256), 0, st, p.nbins, p.ev_per_wg, p.ev_per_batch,
-                     ws.bin_count, ws.bin_start, ws.item_start, ws.batch_start, ws.items);
-  if (n > 0) {
+                     ws.bin_count, ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.items);
+  if (n > 0 && p.rings) {
+    hipLaunchKernelGGL(k_build_rings, dim3((unsigned)p.max_items), dim3(512), 0, st, g, p, ws.evs, ws.items,
+                       ws.batches, ws.cnt);
+  } else if (n > 0) {
     hipLaunchKernelGGL(k_build_batches, dim3((unsigned)p.max_items), dim3(64 * p.waves), 0, st, g, p, ws.evs, ws.items,
                        ws.batches, ws.cnt);
   }

@@ -1,0 +1,7 @@
+// The pass on ring blocks, two events per wavefront (a part of its shapes; one source file each, so that they compile side by side).
+#include "jpet_rings.h"
+
+namespace jpet {
+template struct Rings<322>;
+template struct Rings<326>;
+}  // namespace jpet

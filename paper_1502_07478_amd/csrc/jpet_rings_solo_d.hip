@@ -1,0 +1,8 @@
+// The pass on ring blocks, one event per wavefront (a part of its shapes; one source file each, so that they compile side by side).
+#include "jpet_rings.h"
+
+namespace jpet {
+template struct Rings<1318>;
+template struct Rings<1324>;
+template struct Rings<1332>;
+}  // namespace jpet

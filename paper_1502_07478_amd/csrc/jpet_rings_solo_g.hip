@@ -1,0 +1,7 @@
+// The pass on ring blocks, one event per wavefront (a part of its shapes; one source file each, so that they compile side by side).
+#include "jpet_rings.h"
+
+namespace jpet {
+template struct Rings<1428>;
+template struct Rings<1440>;
+}  // namespace jpet
