@@ -121,9 +121,7 @@ int read_stats(const Workspace& ws, int64_t n, jpet_stats* stats, hipStream_t st
 }
 
 int do_prepare(const Geo& geo, const Plan& p, const float* events, int64_t n, const Workspace& w, hipStream_t st) {
-  hipError_t e = launch_fill_u64(w.cnt, C_COUNT, st);
-  if (e != hipSuccess) return hip_fail(e);
-  e = launch_prepare(geo, p, events, n, w, st);
+  const hipError_t e = launch_prepare(geo, p, events, n, w, st);
   if (e != hipSuccess) return hip_fail(e);
   return JPET_OK;
 }
@@ -460,11 +458,11 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
   w.ev = (EventRec*)take(sizeof(EventRec) * nn);
   w.key = (uint32_t*)take(sizeof(uint32_t) * nn);
   // binning (tiled pass only)
-  w.evs = (EventRec*)take(p.tiled ? sizeof(EventRec) * nn : 0);
+  w.order = (int32_t*)take(p.tiled ? sizeof(int32_t) * nn : 0);
+  w.rank = (uint32_t*)take(p.tiled ? sizeof(uint32_t) * nn : 0);
   w.batches = (unsigned char*)take(p.tiled ? (size_t)p.batch_bytes * (size_t)p.max_batches : 0);
   w.bin_count = (uint32_t*)take(sizeof(uint32_t) * nb);
   w.bin_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
-  w.bin_fill = (uint32_t*)take(sizeof(uint32_t) * nb);
   w.item_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.rest_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.batch_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));

@@ -247,7 +247,7 @@ __device__ __forceinline__ void copy_consts(const unsigned char* __restrict__ sr
 // accumulators are 64-bit in 2^-32 units, or with ACC32 32-bit in 2^-acc_shift units, acc_shift = 23
 // for items of up to 511 events).
 // With D_out (MLEM mode) each event's denominator times the kernel's constant factor is also
-// written at the event's input position (evs: the bin-sorted records).
+// written at the event's input position (order: the events by bin).
 // GRAD = true: the log-likelihood pass (acc: double image B = sum P / D; per-event log D' and the
 // sigma-derivative sums into red[0..2]; D' times the kernel's constant factor into D_out).
 // VALUE (with GRAD): the log-likelihood value only: per-event log D' sums, no B, no
@@ -258,7 +258,7 @@ __device__ __forceinline__ void event_pass_item(const Geo& g, const Plan& p, con
                                                 unsigned long long* __restrict__ acc,
                                                 unsigned long long* __restrict__ cnt, unsigned char* smem,
                                                 PassShared& ps, GradShared* gsh, float* __restrict__ D_out,
-                                                double* __restrict__ red, const EventRec* __restrict__ evs) {
+                                                double* __restrict__ red, const int32_t* __restrict__ order) {
   // rows of a column in LDS; a compile-time pitch turns the per-pixel LDS addresses into
   // immediate offsets
   const int pitch = PITCH ? PITCH : p.pitch;
@@ -379,7 +379,7 @@ __device__ __forceinline__ void event_pass_item(const Geo& g, const Plan& p, con
             atomicAdd(&ps.zero, 1u);
           }
           if (D_out)
-            D_out[evs[it.start + (bi - 1) * p.ev_per_batch + tid].index] =
+            D_out[order[it.start + (bi - 1) * p.ev_per_batch + tid]] =
                 (float)(De > 0.0 ? De * (double)Dnorm : 0.0);
         }
       } else {
@@ -395,7 +395,7 @@ __device__ __forceinline__ void event_pass_item(const Geo& g, const Plan& p, con
         if (wave == 0 && tid < nbp && !(Dp[tid] > 0.0)) atomicAdd(&ps.zero, 1u);
         // the denominators themselves (with P's constant factor), by input position
         if (D_out && wave == 0 && tid < nbp)
-          D_out[evs[it.start + (bi - 1) * p.ev_per_batch + tid].index] = (float)(Dp[tid] * g.cnorm);
+          D_out[order[it.start + (bi - 1) * p.ev_per_batch + tid]] = (float)(Dp[tid] * g.cnorm);
       }
     }
     if (bi < nbatch) {
@@ -629,13 +629,13 @@ __global__ void __launch_bounds__(WAVES * 64, pass_waves_per_simd<MAXLEN>()) k_e
                                                                     const float* __restrict__ rho,
                                                                     unsigned long long* __restrict__ acc,
                                                                     unsigned long long* __restrict__ cnt,
-                                                                    const EventRec* __restrict__ evs,
+                                                                    const int32_t* __restrict__ order,
                                                                     float* __restrict__ D_out) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ PassShared ps;
   if ((unsigned long long)blockIdx.x >= cnt[C_ITEMS]) return;  // uniform over the workgroup
   event_pass_item<MAXLEN, WAVES, false, ACC32, PITCH>(g, p, blocks, items[blockIdx.x], rho, acc, cnt, smem, ps,
-                                                     nullptr, D_out, nullptr, evs);
+                                                     nullptr, D_out, nullptr, order);
 }
 
 // The log-likelihood pass on the binned layout (B: double image of sum P / D, zeroed by the
@@ -649,14 +649,14 @@ template <int MAXLEN, int WAVES, bool VALUE, int PITCH>
 __global__ void __launch_bounds__(WAVES * 64, loglik_waves_per_simd<MAXLEN>())
     k_loglik_tiled(Geo g, Plan p, const unsigned char* __restrict__ blocks, const BinItem* __restrict__ items,
                    const float* __restrict__ rho, double* __restrict__ B, float* __restrict__ D_out,
-                   double* __restrict__ red, unsigned long long* __restrict__ cnt, const EventRec* __restrict__ evs) {
+                   double* __restrict__ red, unsigned long long* __restrict__ cnt, const int32_t* __restrict__ order) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ PassShared ps;
   __shared__ GradShared gsh;
   if ((unsigned long long)blockIdx.x >= cnt[C_ITEMS]) return;  // uniform over the workgroup
   event_pass_item<MAXLEN, WAVES, true, false, PITCH, VALUE>(g, p, blocks, items[blockIdx.x], rho,
                                                 reinterpret_cast<unsigned long long*>(B), cnt, smem, ps, &gsh, D_out,
-                                                red, evs);
+                                                red, order);
 }
 
 // The same pass over many independent reconstructions: one workgroup per workgroup item of a
@@ -694,7 +694,7 @@ hipError_t launch_tiled(const Geo& g, const Plan& p, const Workspace& ws, const 
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), p.lds_bytes, st, g, p, ws.batches,
-                     ws.items, rho, ws.acc, ws.cnt, ws.evs, D_out);
+                     ws.items, rho, ws.acc, ws.cnt, ws.order, D_out);
   return hipGetLastError();
 }
 
@@ -705,7 +705,7 @@ hipError_t launch_loglik_p(const Geo& g, const Plan& p, const Workspace& ws, con
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), p.lds_bytes, st, g, p, ws.batches,
-                     ws.items, rho, ws.B, D_out, ws.red, ws.cnt, ws.evs);
+                     ws.items, rho, ws.B, D_out, ws.red, ws.cnt, ws.order);
   return hipGetLastError();
 }
 

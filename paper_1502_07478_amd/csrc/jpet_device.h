@@ -97,7 +97,7 @@ __device__ inline bool row_interval(const Geo& g, const EventRec& e, int i, int*
   const double c = e.c;
   const double rem = 9.0 - 4.0 * g.wm * c * c * dy * dy;
   if (!(rem >= 0.0)) return false;
-  const double H = sqrt(rem * (0.5 / (g.um * e.su)));
+  const double H = sqrt(rem * e.hs);
   const double zc = e.z + e.t * dy;
   double a = ceil((zc - H - g.z0) * g.ipix);
   double b = floor((zc + H - g.z0) * g.ipix);

@@ -35,10 +35,11 @@ struct EventRec {
   double z;      // z~
   double su;     // this event's u over the geometry's: (sigma_z / sigma_z(e))^2, 1 for a constant
                  // sigma_z
+  double hs;     // 0.5 / (um su): a row's half chord is sqrt(hs (9 - 4 wm c^2 dy^2))
   int32_t r0;    // first pixel row of the 3-sigma ellipse (App. B), clipped to the grid
   int32_t r1;    // last row; r1 < r0 marks an invalid (dropped) event
-  int32_t npix;  // pixel centres inside the ellipse
   int32_t index; // position of the event in the caller's array
+  int32_t pad;
 };
 
 // Per-event constants of the binned event pass (64 bytes), written at prepare time.  With Y the
@@ -247,12 +248,12 @@ struct BinItem {
 // Workspace carve-up.
 struct Workspace {
   EventRec* ev;               // [n] records in input order
-  EventRec* evs;              // [n] records sorted by bin
+  int32_t* order;             // [n] events sorted by bin
   unsigned char* batches;     // [max_batches * batch_bytes] batch blocks of the binned pass
   uint32_t* key;              // [n] bin of each event (0xffffffff: dropped)
   uint32_t* bin_count;        // [nbins]
   uint32_t* bin_start;        // [nbins + 1]
-  uint32_t* bin_fill;         // [nbins]
+  uint32_t* rank;             // [n] position of each event in its bin
   uint32_t* item_start;       // [nbins + 1] full workgroup items before each bin
   uint32_t* rest_start;       // [nbins + 1] bins before each that also make a shorter item
   uint32_t* batch_start;      // [nbins + 1] first batch block of each bin

@@ -1,12 +1,15 @@
 // Per-event preparation and spatial binning (iteration-invariant, run once per event list).
 //
-//   k_prepare   direct reconstruction (Eq. 2), ellipse rows (App. B, Sec. 3), pixel count,
-//               validity and the bin of each event
-//   k_histogram events per bin
-//   k_scan      exclusive prefix sums of bin sizes and of workgroup items per bin
-//   k_scatter   records in bin order
-//   k_items     workgroup items: (bin, first event, count) with at most ev_per_wg events
-#include "jpet_device.h"
+//   k_clear        counters and events per bin
+//   k_prepare      direct reconstruction (Eq. 2), ellipse rows (App. B, Sec. 3), validity; for the binned
+//                  passes each event's bin and its rank in it, for the others the pixel count
+//   k_scan         exclusive prefix sums over the bins of events, workgroup items and batch blocks
+//   k_place        events in bin order, and the workgroup items: (bin, first event, count) with at most
+//                  ev_per_wg events
+//   k_build_rings, k_build_batches   the blocks the passes read, and the pixel count
+#include <algorithm>
+
+#include "jpet_rows.h"
 
 namespace jpet {
 
@@ -30,87 +33,149 @@ __device__ uint32_t bin_of(const Geo& g, const Plan& p, const EventRec& e) {
   return (uint32_t)(((int64_t)b * p.nty + ty) * p.ntz + tz);
 }
 
-__global__ void __launch_bounds__(256) k_prepare(Geo g, Plan p, const float* __restrict__ events, int64_t n,
-                                                 EventRec* __restrict__ ev, uint32_t* __restrict__ key,
-                                                 unsigned long long* __restrict__ cnt) {
+// Direct reconstruction and rows of event j: the record with r1 < r0 for an invalid one.  The rows are those
+// within the ellipse's half height, of which the outermost may hold no pixel centre; pixels (nullable):
+// the ellipse's pixel count.
+__device__ EventRec event_record(const Geo& g, const float* __restrict__ events, int64_t j, long long* pixels) {
+  const float zu = events[3 * j], zd = events[3 * j + 1], dl = events[3 * j + 2];
+  EventRec e;
+  e.r0 = 0;
+  e.r1 = -1;
+  e.index = (int32_t)j;
+  e.pad = 0;
+  e.t = e.c = e.y = e.z = e.hs = 0.0;
+  e.su = 1.0;
+  const double hl = 0.5 * g.L;
+  if (!(isfinite(zu) && isfinite(zd) && isfinite(dl) && fabs((double)zu) <= hl && fabs((double)zd) <= hl)) return e;
+  // Eq. 2, first forms
+  const double t = ((double)zu - (double)zd) / (2.0 * g.R);
+  const double c = sqrt(1.0 + t * t);
+  const double y = -0.5 * (double)dl / c;
+  const double z = 0.5 * ((double)zu + (double)zd + 2.0 * y * t);
+  e.t = t;
+  e.c = c;
+  e.y = y;
+  e.z = z;
+  // this event's sigma_z: sigma_z (1 + zedge zeta), zeta the mean of (z / (L/2))^2 over the
+  // two hits (Sec. 3 after Eq. 12); u scales by the inverse square
+  {
+    const double xu = (double)zu / hl, xd = (double)zd / hl;
+    const double f = 1.0 + g.zedge * (0.5 * (xu * xu + xd * xd));
+    e.su = 1.0 / (f * f);
+    e.hs = 0.5 / (g.um * e.su);
+  }
+  // rows within the ellipse's half height 1.5 sigma_dl / c (App. B)
+  const double hy = 1.5 / (sqrt(g.wm) * c);
+  double a = ceil((y - hy - g.y0) * g.ipix);
+  double b = floor((y + hy - g.y0) * g.ipix);
+  if (a < 0.0) a = 0.0;
+  if (b > (double)(g.n_y - 1)) b = (double)(g.n_y - 1);
+  if (!(a <= b)) return e;
+  const int first = (int)a, last = (int)b;
+  // valid when a pixel centre lies inside: the row nearest to the centre nearly always has one
+  int klo, khi;
+  bool some = row_interval(g, e, clamp_index(rint((y - g.y0) * g.ipix), first, last), &klo, &khi);
+  if (pixels || !some) {
+    long long count = 0;
+    for (int i = first; i <= last; ++i)
+      if (row_interval(g, e, i, &klo, &khi)) count += khi - klo + 1;
+    some = count > 0;
+    if (pixels) *pixels = count;
+  }
+  if (some) {
+    e.r0 = first;
+    e.r1 = last;
+  }
+  return e;
+}
+
+__global__ void k_clear(unsigned long long* __restrict__ cnt, uint32_t* __restrict__ bin_count, int64_t nbins) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < C_COUNT) cnt[i] = 0ull;
+  if (i < nbins) bin_count[i] = 0u;
+}
+
+// Sums over the workgroup, added to the counters by one thread.
+__device__ void add_counts(unsigned long long* __restrict__ cnt, unsigned long long valid, unsigned long long dropped,
+                           unsigned long long pairs) {
+  __shared__ unsigned long long s[3];
+  if (threadIdx.x < 3) s[threadIdx.x] = 0ull;
+  __syncthreads();
+  valid = wave_sum_u64(valid);
+  dropped = wave_sum_u64(dropped);
+  pairs = wave_sum_u64(pairs);
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
+    if (valid) atomicAdd(&s[0], valid);
+    if (dropped) atomicAdd(&s[1], dropped);
+    if (pairs) atomicAdd(&s[2], pairs);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s[0]) atomicAdd(&cnt[C_VALID], s[0]);
+    if (s[1]) atomicAdd(&cnt[C_DROPPED], s[1]);
+    if (s[2]) atomicAdd(&cnt[C_PAIRS], s[2]);
+  }
+}
+
+// Records for the passes without binning.
+__global__ void __launch_bounds__(256) k_prepare_plain(Geo g, const float* __restrict__ events, int64_t n,
+                                                       EventRec* __restrict__ ev,
+                                                       unsigned long long* __restrict__ cnt) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   unsigned long long valid = 0, pairs = 0;
   if (j < n) {
-    const float zu = events[3 * j], zd = events[3 * j + 1], dl = events[3 * j + 2];
-    EventRec e;
-    e.r0 = 0;
-    e.r1 = -1;
-    e.npix = 0;
-    e.index = (int32_t)j;
-    e.t = e.c = e.y = e.z = 0.0;
-    e.su = 1.0;
-    uint32_t k = kNoBin;
-    const double hl = 0.5 * g.L;
-    if (isfinite(zu) && isfinite(zd) && isfinite(dl) && fabs((double)zu) <= hl && fabs((double)zd) <= hl) {
-      // Eq. 2, first forms
-      const double t = ((double)zu - (double)zd) / (2.0 * g.R);
-      const double c = sqrt(1.0 + t * t);
-      const double y = -0.5 * (double)dl / c;
-      const double z = 0.5 * ((double)zu + (double)zd + 2.0 * y * t);
-      e.t = t;
-      e.c = c;
-      e.y = y;
-      e.z = z;
-      // this event's sigma_z: sigma_z (1 + zedge zeta), zeta the mean of (z / (L/2))^2 over the
-      // two hits (Sec. 3 after Eq. 12); u scales by the inverse square
-      {
-        const double xu = (double)zu / hl, xd = (double)zd / hl;
-        const double f = 1.0 + g.zedge * (0.5 * (xu * xu + xd * xd));
-        e.su = 1.0 / (f * f);
-      }
-      // rows within the ellipse's half height 1.5 sigma_dl / c (App. B)
-      const double hy = 1.5 / (sqrt(g.wm) * c);
-      double a = ceil((y - hy - g.y0) * g.ipix);
-      double b = floor((y + hy - g.y0) * g.ipix);
-      if (a < 0.0) a = 0.0;
-      if (b > (double)(g.n_y - 1)) b = (double)(g.n_y - 1);
-      int first = 1 << 30, last = -1;
-      long long cntp = 0;
-      if (a <= b) {
-        for (int i = (int)a; i <= (int)b; ++i) {
-          int klo, khi;
-          if (row_interval(g, e, i, &klo, &khi)) {
-            if (first > i) first = i;
-            last = i;
-            cntp += khi - klo + 1;
-          }
-        }
-      }
-      if (cntp > 0) {
-        e.r0 = first;
-        e.r1 = last;
-        e.npix = (int)cntp;
-        valid = 1;
-        pairs = (unsigned long long)cntp;
-        if (p.tiled) k = bin_of(g, p, e);
-      }
-    }
+    long long pixels = 0;
+    const EventRec e = event_record(g, events, j, &pixels);
     ev[j] = e;
+    valid = e.r1 >= e.r0;
+    if (valid) pairs = (unsigned long long)pixels;
+  }
+  add_counts(cnt, valid, j < n ? 1 - valid : 0, pairs);
+}
+
+// Records, and each event's bin and rank in it.  A workgroup takes 1024 per events.  With LDS_RANK it counts
+// them by bin in LDS first (nbins words) and adds each bin's count to the global one once: events
+// crowd into few bins, and one global atomic per event puts most of them on a few addresses (10M
+// events at 64 x 76 pixels: 2.7 ms for each of the former histogram and scatter).
+template <bool LDS_RANK>
+__global__ void __launch_bounds__(1024) k_prepare(Geo g, Plan p, const float* __restrict__ events, int64_t n, int per,
+                                                  EventRec* __restrict__ ev, uint32_t* __restrict__ key,
+                                                  uint32_t* __restrict__ rank, uint32_t* __restrict__ bin_count,
+                                                  unsigned long long* __restrict__ cnt) {
+  extern __shared__ uint32_t in_bin[];
+  const int64_t j0 = (int64_t)blockIdx.x * 1024 * per + threadIdx.x;
+  if constexpr (LDS_RANK) {
+    for (int b = threadIdx.x; b < p.nbins; b += 1024) in_bin[b] = 0u;
+    __syncthreads();
+  }
+  unsigned long long valid = 0, dropped = 0;
+  for (int q = 0; q < per; ++q) {
+    const int64_t j = j0 + 1024 * (int64_t)q;
+    if (j >= n) break;
+    const EventRec e = event_record(g, events, j, nullptr);
+    ev[j] = e;
+    uint32_t k = kNoBin;
+    if (e.r1 >= e.r0) {
+      ++valid;
+      k = bin_of(g, p, e);
+      rank[j] = atomicAdd(LDS_RANK ? &in_bin[k] : &bin_count[k], 1u);
+    } else {
+      ++dropped;
+    }
     key[j] = k;
   }
-  const unsigned long long v = wave_sum_u64(valid), pr = wave_sum_u64(pairs),
-                           in = wave_sum_u64(j < n ? 1ull : 0ull);
-  if ((threadIdx.x & (WAVE - 1)) == 0 && in) {
-    atomicAdd(&cnt[C_VALID], v);
-    atomicAdd(&cnt[C_DROPPED], in - v);
-    atomicAdd(&cnt[C_PAIRS], pr);
+  if constexpr (LDS_RANK) {
+    __syncthreads();
+    for (int b = threadIdx.x; b < p.nbins; b += 1024)
+      if (const uint32_t c = in_bin[b]) in_bin[b] = atomicAdd(&bin_count[b], c);
+    __syncthreads();
+    for (int q = 0; q < per; ++q) {  // this thread's own events
+      const int64_t j = j0 + 1024 * (int64_t)q;
+      if (j >= n) break;
+      if (key[j] != kNoBin) rank[j] += in_bin[key[j]];
+    }
   }
-}
-
-__global__ void k_fill_u32(uint32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
-}
-
-__global__ void __launch_bounds__(256) k_histogram(const uint32_t* __restrict__ key, int64_t n,
-                                                   uint32_t* __restrict__ bin_count) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n && key[j] != kNoBin) atomicAdd(&bin_count[key[j]], 1u);
+  add_counts(cnt, valid, dropped, 0ull);
 }
 
 // Single workgroup: exclusive scans over the bins of the events, of the full workgroup items, of the
@@ -157,27 +222,21 @@ __global__ void __launch_bounds__(1024) k_scan(int nbins, int ev_per_wg, int ev_
   }
 }
 
-__global__ void __launch_bounds__(256) k_scatter(const EventRec* __restrict__ ev, const uint32_t* __restrict__ key,
-                                                 int64_t n, const uint32_t* __restrict__ bin_start,
-                                                 uint32_t* __restrict__ bin_fill, EventRec* __restrict__ evs) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const uint32_t k = key[j];
-  if (k == kNoBin) return;
-  const uint32_t pos = bin_start[k] + atomicAdd(&bin_fill[k], 1u);
-  evs[pos] = ev[j];
-}
-
-// The full items of all bins come first, then the bins' rests: the pass's workgroups are dispatched in
-// this order, so the short ones fill the chip's last round.
-__global__ void __launch_bounds__(256) k_items(int nbins, int ev_per_wg, int ev_per_batch,
+// Thread j places event j; thread b writes bin b's items.  The full items of all bins come first, then the
+// bins' rests: the pass's workgroups are dispatched in this order, so the short ones fill the chip's
+// last round.
+__global__ void __launch_bounds__(256) k_place(const uint32_t* __restrict__ key, const uint32_t* __restrict__ rank,
+                                               int64_t n, int nbins, int ev_per_wg, int ev_per_batch,
                                                const uint32_t* __restrict__ bin_count,
                                                const uint32_t* __restrict__ bin_start,
                                                const uint32_t* __restrict__ item_start,
                                                const uint32_t* __restrict__ rest_start,
-                                               const uint32_t* __restrict__ batch_start, BinItem* __restrict__ items) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbins) return;
+                                               const uint32_t* __restrict__ batch_start, int32_t* __restrict__ order,
+                                               BinItem* __restrict__ items) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j < n && key[j] != kNoBin) order[bin_start[key[j]] + rank[j]] = (int32_t)j;
+  if (j >= nbins) return;
+  const int b = (int)j;
   const uint32_t c = bin_count[b], full = c / (uint32_t)ev_per_wg;
   for (uint32_t i = 0; i * ev_per_wg < c; ++i) {
     const uint32_t s = i * ev_per_wg;
@@ -240,34 +299,28 @@ __device__ inline int centre_row(const Geo& g, const EventRec& e) {
   return (int)floor((e.y - g.y0) * g.ipix + 0.5);
 }
 
-// How the event pass may evaluate the n pixels of a row segment from column klo on.  kappa is affine
-// along the row: unless it keeps a margin of 1e-3 of its first value at both ends, the pixels need
-// the kappa <= 0 test (kRowExact).  Otherwise the exponent of the kernel is expanded about the
-// segment's centre in y = delta x (the pass's RowP, with the same names): the remainder after x^5 is
-// at most (w x^2 y^4 + log2(e)/2 y^6 / 6) / (1 - y), beside log2(e)/2 (y^4 / 12 + 2 y^5 / 15) for the
+// How the pass on ring blocks may evaluate a row of nl + nr pixels about its centre, k its constants there.
+// kappa is affine along the row: unless it keeps a margin of 1e-3 of its central value at both ends, the
+// pixels need the kappa <= 0 test (kRowExact).  Otherwise the exponent of the kernel is expanded about
+// the centre in y = delta x (the pass's RowP, with the same names): the remainder after x^5 is at most
+// (w x^2 y^4 + log2(e)/2 y^6 / 6) / (1 - y), beside log2(e)/2 (y^4 / 12 + 2 y^5 / 15) for the
 // logarithm's last two terms (taken as -delta times the one before), that after the economised x^7 and x^8 at
 // most w x^2 (y^5 / 64 + y^6 / 128 + y^7 / (1 - y)) + log2(e)/2 (y^7 / 448 + y^8 / 1024 + y^9 / (9 (1 - y))),
-// at the segment's end.
-// The polynomial is taken while that stays below 1e-7 in the exponent (base 2), under the rounding of
-// S q, and while no slot of the register cache, pixels past the segment's ends included, can
-// overflow.  Where the line lies: of prod400's rows all take x^5, of the paper's setting (R = 130 mm,
-// sigma_z = 10 mm) half need x^6 and few the exact form.
-__device__ inline int row_mode(const Geo& g, const Plan& p, const EventRec& e, int i, int klo, int n) {
-  double kf, ks;
-  const RowK r = row_constants(g, e, i, klo, &kf, &ks);
-  const double kend = kf + (double)(n - 1) * ks;
-  if (!(kf > 1e-3 * fabs(kf) && kend > 1e-3 * fabs(kf))) return kRowExact;
-  if (!p.rings) return 0;
-  const float L = (float)kHalfLog2e, mid = 0.5f * (float)(n - 1), M = 0.5f * (float)(n + 1), H = 0.5f * (float)p.ring_len;
-  const float kc = (float)(kf + 0.5 * (double)(n - 1) * ks), rq = __builtin_amdgcn_rsqf(kc);
-  const float dl = (float)ks * rq * rq, y = fabsf(dl) * M;
-  const float h0 = fmaf(mid, r.dgs, r.gs0) * rq, h1 = r.dgs * rq, d = h1 - dl * h0, w = d * d;
-  const float b1 = fmaf(mid, r.pix, r.b10), qa = r.a2 * r.pix * r.pix, qb = 2.0f * r.a2 * r.pix * b1;
-  // the exponent at any slot (|x| <= H + 1)
-  const float X = H + 1.0f, z = fabsf(dl) * X, c1 = h0 * (h1 + d) - L * dl - qb, c2 = w + 0.5f * L * dl * dl - qa;
+// at the row's end.  The polynomial is taken while that stays below 1e-7 in the exponent (base 2), under
+// the rounding of S q, and while no slot of the register cache (the first H pixels from the centre),
+// pixels past the row's ends included, can overflow.  Where the line lies: with strips at 450 mm nearly all
+// rows take x^5, of the paper's setting (R = 130 mm, sigma_z = 10 mm) half need x^6, few the exact form.
+__device__ inline int row_mode(const RowF& k, int nl, int nr, int H) {
+  const float L = (float)kHalfLog2e, M = (float)nr, X = (float)(H + 1);
+  const float klo = fmaf(-(float)nl, k.dkap, k.kap0), khi = fmaf((float)nr, k.dkap, k.kap0);
+  if (!(k.kap0 > 0.0f && fminf(klo, khi) > 1e-3f * k.kap0)) return kRowExact;
+  const float rq = __builtin_amdgcn_rsqf(k.kap0), dl = k.dkap * rq * rq, y = fabsf(dl) * M;
+  const float h0 = k.gs0 * rq, h1 = k.dgs * rq, d = h1 - dl * h0, w = d * d;
+  // the exponent at any slot
+  const float z = fabsf(dl) * X, c1 = h0 * (h1 + d) - L * dl - k.qb, c2 = w + 0.5f * L * dl * dl - k.qa;
   const float most = fabsf(c1) * X + fmaxf(c2, 0.0f) * X * X + 2.0f * (w * X * X + L) * z * (1.0f + z * (1.0f + z * (1.0f + z)));
   if (!(most < 100.0f) || !(y < 0.25f)) return kRowExact;
-  const float wm = w * M * M, y2 = y * y, y4 = y2 * y2, q = 1.0f / (1.0f - y);
+  const float wm = w * M * M, y2 = y * y, y4 = y2 * y2, q = __builtin_amdgcn_rcpf(1.0f - y);
   if ((wm * y4 + L * y4 * y2 / 6.0f) * q + L * y4 * (1.0f / 12.0f + 2.0f / 15.0f * y) < 1e-7f) return kRowPoly5;
   const float y5 = y4 * y, y6 = y4 * y2, y7 = y6 * y;
   if (wm * (y5 / 64.0f + y6 / 128.0f + y7 * q) + L * (y7 / 448.0f + y4 * y4 / 1024.0f + y7 * y2 * q / 9.0f) < 1e-7f)
@@ -291,7 +344,8 @@ constexpr int kBuildBatch = 32;
 constexpr int kBuildGroups = 2 * kBuildBatch;
 constexpr int kBuildSlots = 64;
 
-__global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const EventRec* __restrict__ evs,
+__global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const EventRec* __restrict__ ev,
+                                                        const int32_t* __restrict__ order,
                                                         const BinItem* __restrict__ items,
                                                         unsigned char* __restrict__ blocks,
                                                         unsigned long long* __restrict__ cnt) {
@@ -317,6 +371,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
   const int tid = threadIdx.x;
   const int lane = tid & (WAVE - 1);
   if (tid == 0) outside_s = 0u;
+  unsigned long long pairs = 0;  // pixels of the rows this thread builds
   for (int e0 = 0, bi = 0; e0 < it.count; e0 += p.ev_per_batch, ++bi) {
     const int nb = min(p.ev_per_batch, it.count - e0);
     const int ng = p.segs > 1 ? 2 * nb : nb;
@@ -324,7 +379,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
     uint32_t* words = reinterpret_cast<uint32_t*>(blk + p.cbytes);
     __syncthreads();
     if (tid < nb) {
-      const EventRec e = evs[it.start + e0 + tid];
+      const EventRec e = ev[order[it.start + e0 + tid]];
       ev_s[tid] = e;
       grp_r0[tid] = 0;
       grp_n[tid] = e.r1 - e.r0 + 1;
@@ -420,15 +475,16 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       ri = qq < top ? qq : (grp_n[gi] >> 1) + 16 * K_s[gi] + (qq - top);
     }
     uint32_t word = 0u;
-    int mode = 0;  // how the pass evaluates this segment (kRowPoly5, kRowPoly6, kRowExact)
+    bool guard = false;  // this segment may reach kappa <= 0: the pass tests every pixel
     if (gi >= 0) {
       const int e = gi < nb ? gi : gi - nb;
-      const EventRec ev = ev_s[e];
-      const int i = ev.r0 + grp_r0[gi] + ri;
+      const EventRec er = ev_s[e];
+      const int i = er.r0 + grp_r0[gi] + ri;
       int klo, khi;
-      if (row_interval(g, ev, i, &klo, &khi)) {
+      if (row_interval(g, er, i, &klo, &khi)) {
         int n = khi - klo + 1;
         if (gi < nb) {  // first segment
+          pairs += n;
           if (n > p.maxlen && p.segs > 1) n = p.maxlen;
         } else {        // second segment: the pixels past the first
           klo += p.maxlen;
@@ -442,7 +498,13 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
           } else {
             word = ((uint32_t)kl << kWordCol) | ((uint32_t)rl << kWordRow) | ((uint32_t)n << kWordLen) |
                    ((uint32_t)e << kWordEv);
-            mode = row_mode(g, p, ev, i, klo, n);
+            // kappa is affine along the row: its smallest value is at one of the segment's two
+            // ends; segments whose ends both keep a margin of 1e-3 of the first value can skip
+            // the test
+            double kf, ks;
+            (void)row_constants(g, er, i, klo, &kf, &ks);
+            const double kend = kf + (double)(n - 1) * ks;
+            guard = !(kf > 1e-3 * fabs(kf) && kend > 1e-3 * fabs(kf));
           }
         }
       }
@@ -452,7 +514,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       const int len = (int)((word >> kWordLen) & 127u);
       const int wl = wave_max_i(len);
       const int wmin = -wave_max_i(len > 0 ? -len : -wl);  // shortest non-empty row (0: none)
-      const int wmode = wave_max_i(mode);
+      const bool wguard = __any(guard);
       // does each half-wavefront hold rows of one event only (the pass then reduces the
       // denominators per half, without the per-event loop)?
       const int ev = (int)((word >> kWordEv) & 31u);
@@ -467,7 +529,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
       if (!(act & 0xffffffffull)) ev_lo = ev_hi;
       if (!(act >> 32)) ev_hi = ev_lo;
       if (lane == 0) {
-        words[64 * p.waves + (tid >> 6)] = (uint32_t)wl | ((uint32_t)wmode << kModeShift);
+        words[64 * p.waves + (tid >> 6)] = (uint32_t)wl | (wguard ? kRowExact << kModeShift : 0u);
         words[65 * p.waves + (tid >> 6)] =
             (uint32_t)wmin |
             (split ? 0u : (1u << kHalfBit) | ((uint32_t)ev_lo << kHalfLo) | ((uint32_t)ev_hi << kHalfHi));
@@ -476,14 +538,101 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
   }
   __syncthreads();
   if (tid == 0 && outside_s) atomicAdd(&cnt[C_OUTSIDE], (unsigned long long)outside_s);
+  add_counts(cnt, 0ull, 0ull, pairs);
+}
+
+// The largest of each 16-bit half over the wavefront (all lanes active), to every lane.
+__device__ __forceinline__ uint32_t wave_max_u16x2(uint32_t v) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  auto step = [](uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+  };
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true));  // row_half_mirror
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true));  // row_mirror
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true));  // row_bcast:15 into rows 1 and 3
+  v = step(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true));  // row_bcast:31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// An event for the rows of its ring block, in pixels from its central row and the column nearest to its point.
+struct RowsOf {
+  float fy, zf;        // its point: rows past the central row, columns past kcen
+  float A, hs;         // 4 wm c^2 and hs in pixels
+  float t;
+  int32_t kcen;
+  int16_t r0, r1;      // its rows, from the central row on (r1 < r0: no event)
+  int16_t mid, mode;   // the central row in the region; how all its rows may be evaluated, kRowExact: row by row
+};
+static_assert(sizeof(RowsOf) == 32, "RowsOf is read in 16-byte units");
+
+__device__ RowsOf rows_of(const Geo& g, const EventRec& e, int mid, bool none) {
+  RowsOf o;
+  const double yp = (e.y - g.y0) * g.ipix, zp = (e.z - g.z0) * g.ipix, kc = rint(zp);
+  o.fy = (float)(yp - (double)mid);
+  o.zf = (float)(zp - kc);
+  o.A = (float)(4.0 * g.wm * e.c * e.c * g.pixel * g.pixel);
+  o.hs = (float)(e.hs * g.ipix * g.ipix);
+  o.t = (float)e.t;
+  o.kcen = (int)kc;
+  o.r0 = (int16_t)(none ? 0 : e.r0 - mid);
+  o.r1 = (int16_t)(none ? -1 : e.r1 - mid);
+  o.mid = 0;
+  o.mode = (int16_t)kRowExact;
+  return o;
+}
+
+// row_interval in single precision, for row x from the central row on.  False when the result is not
+// certain: an end within 5e-4 of a pixel centre, or a row within 0.01 of the ellipse's top in
+// 9 - 4 wm c^2 dy^2.  (Rounding: dy^2 and the product lose at most 4e-6 of 9, so a half chord of up to 32
+// pixels 2e-4 where 0.01 is left under the root; the centre's column, at most 150 away, 5e-5.)
+__device__ __forceinline__ bool row_interval_fast(const RowsOf& e, int x, int n_z, int* klo, int* khi) {
+  const float dy = (float)x - e.fy;
+  const float rem = fmaf(-e.A * dy, dy, 9.0f);
+  const float H = __builtin_amdgcn_sqrtf(fmaxf(rem, 0.0f) * e.hs);
+  const float c = fmaf(e.t, dy, e.zf), a = c - H, b = c + H;
+  const float lo = ceilf(a), hi = floorf(b);
+  *klo = max(e.kcen + (int)lo, 0);
+  *khi = rem > 0.0f ? min(e.kcen + (int)hi, n_z - 1) : -1;
+  const float near = fminf(fminf(lo - a, 1.0f - (lo - a)), fminf(b - hi, 1.0f - (b - hi)));
+  return rem < -0.01f || (rem > 0.01f && near > 5e-4f);
+}
+
+// row_mode for all rows of an event (half height X rows, at most 2 H pixels long) at once: over each of
+// eight bands of rows with the largest value that each of its terms has there.  kRowExact: not decided
+// by these bounds.
+__device__ inline int all_rows_mode(const EvRow& c, float X, int H, float pixf, float pix2) {
+  int mode = (int)kRowPoly5;
+  const float h = 0.125f * X;
+  for (int s = 0; s < 8; ++s) {
+    const float x = ((float)s - 3.5f) * 0.25f * X, out = (fabsf(x) - h) / X;  // band centre, its inner edge
+    const int M = min(H, (int)(sqrtf(1.0f - out * out) * (float)H) + 1);
+    const float kb = fabsf(fmaf(c.KB1, x, c.KB0)) + fabsf(c.KB1) * h, gb = fabsf(fmaf(c.GB1, x, c.GB0)) + fabsf(c.GB1) * h;
+    const float b1 = (float)(M + 1) * pixf;  // of a row's centre, rows cut by the grid's edge included
+    RowF k;
+    k.kap0 = fmaf(fmaf(c.K2, x, c.K1), x, c.K0) - fmaf(fabsf(c.K2), h, fabsf(fmaf(2.0f * c.K2, x, c.K1))) * h - kb * b1;
+    k.dkap = kb * pixf;
+    // (signs that add up in w and in the slope)
+    k.gs0 = -(fabsf(fmaf(fmaf(c.S2, x, c.S1), x, c.S0)) + fmaf(fabsf(c.S2), h, fabsf(fmaf(2.0f * c.S2, x, c.S1))) * h +
+              gb * b1);
+    k.dgs = gb * pixf;
+    k.qa = c.s2u * pix2;
+    k.qb = 2.0f * c.s2u * pixf * b1;
+    k.qc = 0.0f;
+    mode = max(mode, row_mode(k, M, M, H));
+  }
+  return mode;
 }
 
 // Ring blocks (plans with rings): one workgroup per item, first the row constants of its events, one
 // per thread, then one wavefront per block, one lane per row of its event and ring.
-__global__ void __launch_bounds__(512) k_build_rings(Geo g, Plan p, const EventRec* __restrict__ evs,
+__global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const EventRec* __restrict__ ev,
+                                                     const int32_t* __restrict__ order,
                                                      const BinItem* __restrict__ items,
                                                      unsigned char* __restrict__ blocks,
                                                      unsigned long long* __restrict__ cnt) {
+  extern __shared__ __align__(16) unsigned char smem[];  // the events' RowsOf, the column shift of every region row
   if ((unsigned long long)blockIdx.x >= cnt[C_ITEMS]) return;
   const BinItem it = items[blockIdx.x];
   const int tz = it.bin % p.ntz;
@@ -497,47 +646,68 @@ __global__ void __launch_bounds__(512) k_build_rings(Geo g, Plan p, const EventR
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), l = lane & (lpe - 1);
   const int nblk = (it.count + epb - 1) / epb;
   unsigned char* const blk0 = blocks + (size_t)it.batch * (size_t)p.batch_bytes;
+  RowsOf* const rows_s = reinterpret_cast<RowsOf*>(smem);
+  int* const off_s = reinterpret_cast<int*>(rows_s + p.ev_per_wg + 1);
+  for (int r = tid; r < p.RY; r += blockDim.x) off_s[r] = shear_offset(g, tc, rbase + r) + kbase;
   for (int e = tid; e < nblk * epb; e += blockDim.x) {
-    const EventRec ev = evs[it.start + min(e, it.count - 1)];
+    const EventRec er = ev[order[it.start + min(e, it.count - 1)]];
     // polynomials in the rows from the event's central row on: the rounding of their coefficients
     // then stays below that of the rows' own values
-    const int mid = centre_row(g, ev);
-    EvRow k = event_row_constants(g, ev, mid, kbase);
+    const int mid = centre_row(g, er);
+    EvRow k = event_row_constants(g, er, mid, kbase);
     k.mid = mid - rbase;
     if (e >= it.count) k.index = -1;  // no event
     reinterpret_cast<EvRow*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes)[e % epb] = k;
+    RowsOf o = rows_of(g, er, mid, e >= it.count);
+    o.mid = (int16_t)k.mid;
+    o.mode = (int16_t)all_rows_mode(k, (float)p.HY, p.ring_half[0], (float)g.pixel, (float)g.pixel * (float)g.pixel);
+    rows_s[e] = o;
   }
+  __syncthreads();
+  const float pixf = (float)g.pixel, pix2 = pixf * pixf;
   int outside = 0;
+  unsigned long long pairs = 0;
   for (int q = tid >> 6; q < nblk; q += blockDim.x >> 6) {
     unsigned char* const blk = blk0 + (size_t)q * (size_t)p.batch_bytes;
     const int e = epb * q + lane / lpe;
-    EventRec ev = evs[it.start + min(e, it.count - 1)];
-    if (e >= it.count) ev.r1 = ev.r0 - 1;
-    const int mid = centre_row(g, ev);
+    const RowsOf er = rows_s[e];
+    const int mid = er.mid + rbase;
     uint32_t tails[4] = {0, 0, 0, 0}, word = 0;
     int mode = 0;
     for (int k = 0; k < p.rings; ++k) {
-      const int i = mid + l - lpe / 2 + k * (l < lpe / 2 ? -lpe / 2 : lpe / 2);
-      uint32_t w = 0;
-      int klo, khi, m = 0;
-      if (i >= ev.r0 && i <= ev.r1 && row_interval(g, ev, i, &klo, &khi)) {
-        const int n = khi - klo + 1, rl = i - rbase, kl = klo - shear_offset(g, tc, i) - kbase;
-        if (rl < 0 || rl >= p.RY || kl < 0 || kl + n > p.W || n > 2 * p.ring_half[k]) {
+      const int x = l - lpe / 2 + k * (l < lpe / 2 ? -lpe / 2 : lpe / 2), i = mid + x;
+      int klo = 0, khi = -1, n = 0, kl = 0, m = (int)kRowPoly5;
+      if (x >= er.r0 && x <= er.r1 && !row_interval_fast(er, x, g.n_z, &klo, &khi) &&
+          !row_interval(g, ev[order[it.start + e]], i, &klo, &khi))
+        khi = klo - 1;
+      if (khi >= klo) {
+        n = khi - klo + 1;
+        pairs += n;
+        const int rl = i - rbase;
+        kl = rl >= 0 && rl < p.RY ? klo - off_s[rl] : -1;
+        if (kl < 0 || kl + n > p.W || n > 2 * p.ring_half[k]) {
           ++outside;
-        } else {
-          w = (uint32_t)kl | ((uint32_t)n << 8);
-          m = row_mode(g, p, ev, i, klo, n);
+          n = 0;
         }
       }
-      const int len = (int)(w >> 8), wl = wave_max_i(len), wmin = -wave_max_i(len > 0 ? -len : -wl);
-      // the chunks of two pairs the pass runs for this ring, from the row's centre, stay in the region and
-      // its slack
-      const int kc = (int)(w & 255u) + (len >> 1), reach = min(p.ring_half[k], (((wl + 1) >> 1) + 1) & ~1);
-      if (len > 0 && (kc - reach < -p.slack || kc + reach > p.W + p.slack)) m = (int)kRowExact;
-      m = wave_max_i(m);
+      const int nl = n >> 1, nr = n - nl, kc = kl + nl;
+      const uint32_t ends = wave_max_u16x2(n > 0 ? (uint32_t)n | (uint32_t)(128 - n) << 16 : 0u);
+      const int wl = (int)(ends & 0xffffu), wmin = wl ? 128 - (int)(ends >> 16) : 0;
+      if (n > 0) {
+        m = er.mode;
+        if (m == (int)kRowExact) {
+          const EvRow& c = reinterpret_cast<const EvRow*>(blk)[lane / lpe];
+          m = row_mode(ring_constants(c, (float)x, kc + off_s[i - rbase] - kbase, pixf, pix2), nl, nr, p.ring_half[k]);
+        }
+        // the chunks of two pairs the pass runs for this ring, from the row's centre, stay in the region and
+        // its slack
+        const int reach = min(p.ring_half[k], (((wl + 1) >> 1) + 1) & ~1);
+        if (kc - reach < -p.slack || kc + reach > p.W + p.slack) m = (int)kRowExact;
+      }
+      m = __any(m == (int)kRowExact) ? (int)kRowExact : __any(m == (int)kRowPoly6) ? (int)kRowPoly6 : (int)kRowPoly5;
       mode = max(mode, m);
       tails[k] = (uint32_t)wl | ((uint32_t)wmin << 7) | ((uint32_t)m << 14);
-      word |= w << (16 * (k & 1));
+      word |= (n > 0 ? (uint32_t)kl | ((uint32_t)n << 8) : 0u) << (16 * (k & 1));
       if ((k & 1) || k + 1 == p.rings) {
         reinterpret_cast<uint32_t*>(blk + ring_words(epb))[(k >> 1) * WAVE + lane] = word;
         word = 0;
@@ -546,10 +716,12 @@ __global__ void __launch_bounds__(512) k_build_rings(Geo g, Plan p, const EventR
     if (mode == (int)kRowExact)  // one row of a block that needs the exact form: all take it
       for (int k = 0; k < 4; ++k) tails[k] = (tails[k] & 0x3fffu) | (kRowExact << 14);
     if (lane == 0)
-      for (int k = 0; k < 4; ++k) reinterpret_cast<uint16_t*>(blk + ring_tails(epb))[k] = (uint16_t)tails[k];
+      *reinterpret_cast<uint2*>(blk + ring_tails(epb)) =
+          make_uint2(tails[0] | tails[1] << 16, tails[2] | tails[3] << 16);
   }
   outside = (int)wave_sum_u64((unsigned long long)outside);
   if (lane == 0 && outside) atomicAdd(&cnt[C_OUTSIDE], (unsigned long long)outside);
+  add_counts(cnt, 0ull, 0ull, pairs);
 }
 
 int blocks_for(int64_t n, int block) { return (int)((n + block - 1) / block); }
@@ -558,28 +730,44 @@ int blocks_for(int64_t n, int block) { return (int)((n + block - 1) / block); }
 
 hipError_t launch_prepare(const Geo& g, const Plan& p, const float* events, int64_t n, const Workspace& ws,
                           hipStream_t st) {
-  if (n > 0) {
-    hipLaunchKernelGGL(k_prepare, dim3(blocks_for(n, 256)), dim3(256), 0, st, g, p, events, n, ws.ev, ws.key, ws.cnt);
+  const int64_t nb = p.tiled ? p.nbins : 0;
+  hipLaunchKernelGGL(k_clear, dim3(blocks_for(nb > C_COUNT ? nb : C_COUNT, 256)), dim3(256), 0, st, ws.cnt,
+                     ws.bin_count, nb);
+  if (!p.tiled) {
+    if (n > 0)
+      hipLaunchKernelGGL(k_prepare_plain, dim3(blocks_for(n, 256)), dim3(256), 0, st, g, events, n, ws.ev, ws.cnt);
+    return hipGetLastError();
   }
-  if (!p.tiled) return hipGetLastError();
-  const int64_t nb = p.nbins;
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(nb, 256)), dim3(256), 0, st, ws.bin_count, nb);
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(nb, 256)), dim3(256), 0, st, ws.bin_fill, nb);
-  if (n > 0) hipLaunchKernelGGL(k_histogram, dim3(blocks_for(n, 256)), dim3(256), 0, st, ws.key, n, ws.bin_count);
+  if (n > 0) {
+    // events per thread: one while that leaves compute units idle, up to 32 (the more, the fewer bins a
+    // workgroup's events have to themselves); counting in LDS while its bins fit and are fewer than 8
+    // per event (else the counts are few, and clearing and adding them costs more)
+    const int per = (int)std::min<int64_t>(32, std::max<int64_t>(1, n / (1024 * 256)));
+    const size_t lds = sizeof(uint32_t) * (size_t)nb;
+    if (lds <= 144 * 1024 && nb <= 8 * 1024 * per) {
+      const hipError_t e = hipFuncSetAttribute((const void*)k_prepare<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_prepare<true>, dim3(blocks_for(n, 1024 * per)), dim3(1024), lds, st, g, p, events, n, per,
+                         ws.ev, ws.key, ws.rank, ws.bin_count, ws.cnt);
+    } else {
+      hipLaunchKernelGGL(k_prepare<false>, dim3(blocks_for(n, 1024 * per)), dim3(1024), 0, st, g, p, events, n, per,
+                         ws.ev, ws.key, ws.rank, ws.bin_count, ws.cnt);
+    }
+  }
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, p.nbins, p.ev_per_wg, p.ev_per_batch, ws.bin_count,
                      ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.cnt);
-  if (n > 0) {
-    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, 256)), dim3(256), 0, st, ws.ev, ws.key, n, ws.bin_start,
-                       ws.bin_fill, ws.evs);
-  }
-  hipLaunchKernelGGL(k_items, dim3(blocks_for(nb, 256)), dim3(256), 0, st, p.nbins, p.ev_per_wg, p.ev_per_batch,
-                     ws.bin_count, ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.items);
-  if (n > 0 && p.rings) {
-    hipLaunchKernelGGL(k_build_rings, dim3((unsigned)p.max_items), dim3(512), 0, st, g, p, ws.evs, ws.items,
-                       ws.batches, ws.cnt);
-  } else if (n > 0) {
-    hipLaunchKernelGGL(k_build_batches, dim3((unsigned)p.max_items), dim3(64 * p.waves), 0, st, g, p, ws.evs, ws.items,
-                       ws.batches, ws.cnt);
+  if (n <= 0) return hipGetLastError();
+  hipLaunchKernelGGL(k_place, dim3(blocks_for(n > nb ? n : nb, 256)), dim3(256), 0, st, ws.key, ws.rank, n, p.nbins,
+                     p.ev_per_wg, p.ev_per_batch, ws.bin_count, ws.bin_start, ws.item_start, ws.rest_start,
+                     ws.batch_start, ws.order, ws.items);
+  if (p.rings) {
+    hipLaunchKernelGGL(k_build_rings, dim3((unsigned)p.max_items), dim3(256),
+                       sizeof(RowsOf) * (size_t)(p.ev_per_wg + 1) + sizeof(int) * (size_t)p.RY, st, g, p,
+                       ws.ev, ws.order, ws.items, ws.batches, ws.cnt);
+  } else {
+    hipLaunchKernelGGL(k_build_batches, dim3((unsigned)p.max_items), dim3(64 * p.waves), 0, st, g, p, ws.ev, ws.order,
+                       ws.items, ws.batches, ws.cnt);
   }
   return hipGetLastError();
 }

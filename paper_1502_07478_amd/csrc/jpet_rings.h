@@ -117,7 +117,7 @@ __device__ __forceinline__ void ring_back(const float (&m)[2 * H], float sc, uns
   }
 }
 
-// A lane's row of one ring: the word's column and length, and the row constants at its centre.
+// A lane's row of one ring: the word's column and length.
 struct RingRow {
   int rl, kc, nl, nr;  // region row, first pixel right of the centre, pixels on either side
 };
@@ -130,23 +130,6 @@ __device__ __forceinline__ RingRow ring_row(uint32_t w16, int rl, int H) {
   r.nr = len - r.nl;
   r.kc = len > 0 ? (int)(w16 & 255u) + r.nl : H;
   return r;
-}
-
-// (x: the row from its event's central row on)
-__device__ __forceinline__ RowF ring_constants(const EvRow& c, const RingRow& r, float x, const int* __restrict__ off_s,
-                                               float pixf, float pix2) {
-  const float b1 = fmaf(pixf, (float)(r.kc + off_s[r.rl]) - 0.5f, fmaf(c.BT, x, c.B0));
-  const float kb = fmaf(c.KB1, x, c.KB0), gb = fmaf(c.GB1, x, c.GB0);
-  const float sb = c.s2u * b1;
-  RowF k;
-  k.kap0 = fmaf(kb, b1, fmaf(fmaf(c.K2, x, c.K1), x, c.K0));
-  k.dkap = kb * pixf;
-  k.gs0 = fmaf(gb, b1, fmaf(fmaf(c.S2, x, c.S1), x, c.S0));
-  k.dgs = gb * pixf;
-  k.qa = c.s2u * pix2;
-  k.qb = (sb + sb) * pixf;
-  k.qc = fmaf(sb, b1, fmaf(fmaf(c.Q2, x, c.Q1), x, c.Q0));
-  return k;
 }
 
 // P at offset x from the row's centre, 0 (counted) where kappa <= 0.
@@ -296,7 +279,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
         const uint32_t tw = tail(k);
         const int wlh = (int)((tw & 127u) + 1) >> 1, wminh = (int)((tw >> 7) & 127u) >> 1;
         const RingRow r = row(k, H);
-        const RowF rk = ring_constants(c, r, (float)(lrow + k * lstep), off_s, pixf, pix2);
+        const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
         at[k] = (r.kc - H) * pitch + r.rl;
         const float* const rr = rho_s + at[k];
         RowP rp;
@@ -336,7 +319,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const int first = opaque(0);
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
-      const RowF rk = ring_constants(c, r, (float)(lrow + k * lstep), off_s, pixf, pix2);
+      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
       for (int j = -r.nl; j < r.nr; ++j)
         D = fmaf(exact_at(rk, (float)j + 0.5f, &nbad), rho_s[(r.kc + j) * pitch + r.rl], D);
     }
@@ -348,7 +331,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const float sc = (float)((double)kUnit / ((double)De * 18446744073709551616.0));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
-      const RowF rk = ring_constants(c, r, (float)(lrow + k * lstep), off_s, pixf, pix2);
+      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
       for (int j = -r.nl; j < r.nr; ++j) {
         const int px = (r.kc + j) * pitch + r.rl;
         const float m = exact_at(rk, (float)j + 0.5f, &again) * rho_s[px] * 18446744073709551616.0f;

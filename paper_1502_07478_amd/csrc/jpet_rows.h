@@ -19,6 +19,23 @@ struct RowF {
   float kap0, dkap, gs0, dgs, qa, qb, qc;
 };
 
+// The constants at the centre of a row of a ring block: x the row from its event's central row on, col
+// the first pixel right of the centre (region-local column plus the row's shift).
+__device__ __forceinline__ RowF ring_constants(const EvRow& c, float x, int col, float pixf, float pix2) {
+  const float b1 = fmaf(pixf, (float)col - 0.5f, fmaf(c.BT, x, c.B0));
+  const float kb = fmaf(c.KB1, x, c.KB0), gb = fmaf(c.GB1, x, c.GB0);
+  const float sb = c.s2u * b1;
+  RowF k;
+  k.kap0 = fmaf(kb, b1, fmaf(fmaf(c.K2, x, c.K1), x, c.K0));
+  k.dkap = kb * pixf;
+  k.gs0 = fmaf(gb, b1, fmaf(fmaf(c.S2, x, c.S1), x, c.S0));
+  k.dgs = gb * pixf;
+  k.qa = c.s2u * pix2;
+  k.qb = (sb + sb) * pixf;
+  k.qc = fmaf(sb, b1, fmaf(fmaf(c.Q2, x, c.Q1), x, c.Q0));
+  return k;
+}
+
 // The same row as F exp2(E(x)), E a polynomial without constant term.  With kappa_0, gs_0 at the
 // centre, delta = dkap / kappa_0, h0 = gs_0 kappa_0^-1/2, h1 = dgs kappa_0^-1/2 and
 // w = (h1 - delta h0)^2 the exponent is exactly
