@@ -151,16 +151,25 @@ static size_t tiled_lds_layout(int pitch, int W, int RY, int acc32, int epb, boo
   return align_up(off + 4u * (size_t)RY, 16);
 }
 
-// Dynamic LDS of the pass on ring blocks: two buffers of a block's constants per wavefront, the per-row
-// column shifts, the image and the 32-bit accumulators, with the slack columns before the image (the
-// buffers are part of it) and after the accumulators.
-static size_t ring_lds_layout(int pitch, int W, int RY, int waves, int events, int slack, int* off_at, int* img_at) {
+// Events per workgroup item of the passes on ring blocks, at most (32-bit accumulators: see finish_plan).
+constexpr int kRingItem = 510;
+
+// Dynamic LDS of the passes on ring blocks: two buffers of a block's constants per wavefront, the per-row
+// column shifts (log-likelihood: three sums per event of an item), the image and the 32-bit accumulators
+// (doubles), with the slack columns before the image (the buffers are part of it) and after the
+// accumulators (the log-likelihood pass only reads there).
+struct RingLds {
+  int off, sum, img;
+  size_t bytes;
+};
+static RingLds ring_lds_layout(int pitch, int W, int RY, int waves, int events, int slack, bool loglik) {
   const size_t free = (size_t)slack * (size_t)pitch * 4u;
-  const size_t off = (size_t)waves * 2u * (size_t)events * sizeof(EvRow);
-  const size_t img = align_up(std::max(off + 4u * (size_t)RY, free), 256);
-  if (off_at) *off_at = (int)off;
-  if (img_at) *img_at = (int)img;
-  return img + 8u * (size_t)pitch * (size_t)W + free;
+  RingLds L;
+  L.off = waves * 2 * ring_tails(events, loglik);
+  L.sum = L.off + 4 * RY;
+  L.img = (int)align_up(std::max((size_t)L.sum + (loglik ? 12u * kRingItem : 0u), free), 256);
+  L.bytes = (size_t)L.img + (loglik ? 12u : 8u) * (size_t)pitch * (size_t)W + (loglik ? 0u : free);
+  return L;
 }
 
 // The register cache of the pass on ring blocks for ellipses reaching hy_px rows and half_px pixels of a
@@ -207,9 +216,12 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   const double pix = g->pixel;
   if (p.rings) {
     p.ev_per_batch = p.solo ? 1 : 2;
-    p.lds_bytes =
-        ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, &p.lds_off, &p.lds_img);
-    p.batch_bytes = ring_block_bytes(p.ev_per_batch, p.rings);
+    const RingLds lds = ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, p.loglik != 0);
+    p.lds_off = lds.off;
+    p.lds_sum = lds.sum;
+    p.lds_img = lds.img;
+    p.lds_bytes = lds.bytes;
+    p.batch_bytes = ring_block_bytes(p.ev_per_batch, p.rings, p.loglik != 0);
   } else {
     p.ev_per_batch = events_per_batch(p.waves, rows_max * p.segs);
     p.cbytes = p.ev_per_batch * event_const_bytes(p.loglik != 0);
@@ -237,7 +249,7 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   // region, fewer and larger items
   if (p.rings && (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W) per = n / 512;
   if (per < p.ev_per_batch) per = p.ev_per_batch;
-  const int64_t most = p.rings ? 510 : 128 * p.ev_per_batch;
+  const int64_t most = p.rings ? kRingItem : 128 * p.ev_per_batch;
   if (per > most) per = most;
   // 32-bit accumulators hold 2^-s units: one event adds at most 2^s to a pixel, so an item of up
   // to 2^(32-s) - 1 events cannot overflow before the flush.  Items of at most 511 events keep
@@ -332,7 +344,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
         const double occ_factor = pow(4.0 / (double)occ, 0.58) * (waves == 16 ? 1.1 : 1.0) * (segs > 1 ? 1.3 : 1.0);
         for (int acc32 = 0; acc32 <= 1; ++acc32) {
           if (acc32 && !allow_acc32) continue;
-          const int shape = acc32 && segs == 1 ? ring_shape(hy_px, 0.5 * chord_px) : 0;
+          const int shape = (acc32 != 0) != loglik && segs == 1 ? ring_shape(hy_px, 0.5 * chord_px) : 0;
           for (int dti = 0; dti < kPlanDtCount; ++dti) {
             const double dt = kPlanDt[dti];
             // largest |t - t_c| / c inside a bin (no shear: |t| / c <= sin(atan(tmax)))
@@ -370,18 +382,17 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
               // wavefronts run as the registers do (that many, shared by the workgroups of the code)
               int simd = occ;
               if (shape && (pitch == shape_pitch(shape, 0) || pitch == shape_pitch(shape, 1))) {
-                const int most = 4 * shape_waves_per_simd(shape);
-                const int fit = std::max(1, std::min(wgs, most / waves)), each = std::min(waves, most / fit);
+                const int most = 4 * shape_waves_per_simd(shape, loglik);
+                const int fit = std::max(1, std::min(wgs, (most + waves / 2) / waves)), each = std::min(waves, most / fit);
                 const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
-                if (ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, nullptr, nullptr) <=
-                    kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
+                const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, loglik).bytes;
+                if (lds <= kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
                   p.rings = shape_rings(shape);
                   p.solo = shape >= 1000;
                   p.ring_len = shape_len(shape);
                   for (int k = 0; k < p.rings; ++k) p.ring_half[k] = ring_half_of(p.rings, p.ring_len, k);
                   p.slack = slack;
                   p.waves = each;
-                  const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, nullptr, nullptr);
                   simd = std::min(most / each, (int)(kLdsPerCU / align_up(lds + 256, kGranule))) * each / 4;
                 }
               }
@@ -396,7 +407,8 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
               if (loglik) {
                 const double items = nn / p.ev_per_wg + (nn < p.nbins ? nn : (double)p.nbins);
                 cost = nn * pairs_per_event * occ_factor + 1.6 * items * (double)pitch * (double)W;
-              } else {
+              }
+              if (!loglik || p.rings) {
                 const double some = 0.35 * (double)p.nbins;  // the bins an object fills
                 const double items = nn / p.ev_per_wg + some * (1.0 - exp(-nn / some));
                 const double unit = p.rings ? 0.5 * pow(4.0 / (double)simd, 0.58) * (p.waves == 16 ? 1.05 : 1.0)

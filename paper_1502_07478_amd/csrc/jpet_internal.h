@@ -109,9 +109,19 @@ constexpr uint32_t kHalfBit = 31, kHalfLo = 8, kHalfHi = 16;
 // every two rings.  With n = 32 (two events) or 64 lanes per event, lane l's row in ring k is row
 // l - n/2 + k (l < n/2 ? -n/2 : n/2) from its event's central row, l = lane mod n; its 16 bits hold the
 // row's first column (sheared, region-local) in bits 0-7 and its pixels (0: no row) in bits 8-14.
-constexpr int ring_tails(int events) { return events * (int)sizeof(EvRow); }
-constexpr int ring_words(int events) { return ring_tails(events) + 16; }
-constexpr int ring_block_bytes(int events, int rings) { return ring_words(events) + 256 * ((rings + 1) / 2); }
+// Blocks of the log-likelihood pass hold the events' EvLog behind their EvRow.
+struct EvLog {
+  float A2, A3, GK, GG;  // w fa^2 c^2 t^2, 4 w c^2 (1 + 2 t^2), -4 gamma R c^3 t, -4 gamma R c^3
+  float Y0, yr;          // y of the central row, and y~ from there
+  float pad[2];
+};
+constexpr int ring_tails(int events, bool loglik) {
+  return events * (int)(sizeof(EvRow) + (loglik ? sizeof(EvLog) : 0));
+}
+constexpr int ring_words(int events, bool loglik) { return ring_tails(events, loglik) + 16; }
+constexpr int ring_block_bytes(int events, int rings, bool loglik) {
+  return ring_words(events, loglik) + 256 * ((rings + 1) / 2);
+}
 
 // Spatial binning of events and launch shape of the tiled event pass.
 //
@@ -154,6 +164,7 @@ struct Plan {
   // the register cache's pixels per row of the innermost ring and pairs of pixels of ring k's rows
   // (ring_half_of), the image's place in LDS, the columns of slack beside the region
   int rings, solo, ring_len, lds_img, slack;
+  int lds_sum;          // log-likelihood: the events' sums in LDS
   int ring_half[4];
 };
 
@@ -180,13 +191,14 @@ constexpr int shape_rings(int shape) { return shape % 1000 / 100; }
 constexpr int shape_len(int shape) { return shape % 100; }
 // Wavefronts per SIMD a shape is compiled for: the cache and some 50 registers beside it fit the 64, 80,
 // 128, 168 or 256 registers that leaves.
-constexpr int shape_waves_per_simd(int shape) {
+constexpr int shape_waves_per_simd(int shape, bool loglik = false) {
   int cache = 0;
   for (int k = 0; k < shape_rings(shape); ++k) cache += 2 * ring_half_of(shape_rings(shape), shape_len(shape), k);
+  if (loglik) return cache <= 16 ? 6 : cache <= 52 ? 4 : cache <= 100 ? 3 : 2;  // (some 70 registers beside it)
   return cache <= 16 ? 8 : cache <= 34 ? 6 : cache <= 72 ? 4 : cache <= 120 ? 3 : 2;
 }
-constexpr int shape_threads(int shape) {
-  return 256 * shape_waves_per_simd(shape) < 1024 ? 256 * shape_waves_per_simd(shape) : 1024;
+constexpr int shape_threads(int shape, bool loglik = false) {
+  return 256 * shape_waves_per_simd(shape, loglik) < 1024 ? 256 * shape_waves_per_simd(shape, loglik) : 1024;
 }
 // The two region row pitches a shape is compiled for (words; the rows and halo of its ellipses, and a
 // tile, give no other unless the tile is large).
@@ -335,7 +347,11 @@ struct Rings {
   static hipError_t batched(const BatchInst* table, int count, int waves, int pitch, unsigned items, size_t lds_bytes,
                             hipStream_t st);
   static const void* batched_kernel(int waves, int pitch);
+  static hipError_t loglik(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
+                           hipStream_t st);
 };
+hipError_t launch_loglik_rings_value(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
+                                     hipStream_t st);
 
 // Kernel launchers (return the hipError_t of the launch).
 hipError_t launch_sensitivity(const Geo& g, float* s, hipStream_t st);

@@ -180,6 +180,10 @@ hipError_t by_kernel(int kernel, F f) {
 hipError_t launch_loglik_tiled(const Geo& g, const Plan& p, int64_t n, const Workspace& ws, const float* rho,
                                float* D_out, bool value_only, hipStream_t st) {
   if (n <= 0) return hipSuccess;
+  if (p.rings) {
+    if (value_only) return launch_loglik_rings_value(g, p, ws, rho, D_out, st);
+    return by_shape<0>(pass_kernel(p) - 10000, [&](auto b) { return b.loglik(g, p, ws, rho, D_out, st); });
+  }
   return by_cache(p.maxlen, [&](auto b) { return b.loglik(g, p, ws, rho, D_out, value_only, st); });
 }
 

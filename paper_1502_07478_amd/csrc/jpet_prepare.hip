@@ -658,6 +658,19 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
     k.mid = mid - rbase;
     if (e >= it.count) k.index = -1;  // no event
     reinterpret_cast<EvRow*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes)[e % epb] = k;
+    if (p.loglik) {
+      const double w = g.w, c2 = er.c * er.c, t2 = er.t * er.t;
+      EvLog q;
+      q.A2 = (float)(w * g.fa * g.fa * c2 * t2);
+      q.A3 = (float)(4.0 * w * c2 * (1.0 + 2.0 * t2));
+      q.GG = (float)(-4.0 * g.gamma * g.R * c2 * er.c);
+      q.GK = (float)(-4.0 * g.gamma * g.R * c2 * er.c * er.t);
+      const double Y0 = g.y0 + (double)mid * g.pixel;
+      q.Y0 = (float)Y0;
+      q.yr = (float)(er.y - Y0);
+      q.pad[0] = q.pad[1] = 0.0f;
+      reinterpret_cast<EvLog*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes + epb * sizeof(EvRow))[e % epb] = q;
+    }
     RowsOf o = rows_of(g, er, mid, e >= it.count);
     o.mid = (int16_t)k.mid;
     o.mode = (int16_t)all_rows_mode(k, (float)p.HY, p.ring_half[0], (float)g.pixel, (float)g.pixel * (float)g.pixel);
@@ -709,14 +722,14 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
       tails[k] = (uint32_t)wl | ((uint32_t)wmin << 7) | ((uint32_t)m << 14);
       word |= (n > 0 ? (uint32_t)kl | ((uint32_t)n << 8) : 0u) << (16 * (k & 1));
       if ((k & 1) || k + 1 == p.rings) {
-        reinterpret_cast<uint32_t*>(blk + ring_words(epb))[(k >> 1) * WAVE + lane] = word;
+        reinterpret_cast<uint32_t*>(blk + ring_words(epb, p.loglik))[(k >> 1) * WAVE + lane] = word;
         word = 0;
       }
     }
     if (mode == (int)kRowExact)  // one row of a block that needs the exact form: all take it
       for (int k = 0; k < 4; ++k) tails[k] = (tails[k] & 0x3fffu) | (kRowExact << 14);
     if (lane == 0)
-      *reinterpret_cast<uint2*>(blk + ring_tails(epb)) =
+      *reinterpret_cast<uint2*>(blk + ring_tails(epb, p.loglik)) =
           make_uint2(tails[0] | tails[1] << 16, tails[2] | tails[3] << 16);
   }
   outside = (int)wave_sum_u64((unsigned long long)outside);

@@ -212,8 +212,8 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
                                        con_s + buf * kConst, 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < kWords; ++j)
-      word[j] = reinterpret_cast<const uint32_t*>(blk + ring_words(kEvents))[j * WAVE + ln];
-    tails = *reinterpret_cast<const uint2*>(blk + ring_tails(kEvents));
+      word[j] = reinterpret_cast<const uint32_t*>(blk + ring_words(kEvents, false))[j * WAVE + ln];
+    tails = *reinterpret_cast<const uint2*>(blk + ring_tails(kEvents, false));
   };
   if (wave < nblk) fetch(wave, 0);
   if (tid == 0) ps.zero = ps.bad = 0u;

@@ -7,7 +7,9 @@ Tolerance of the image (relative L2): 2e-6 for the single-precision kernel (the 
 magnitude, carries a few roundings of 2^-24) plus three standard deviations of the fixed-point
 rounding, 0.29 units of 2^-23 per (event, pixel) pair.  A single event's denominator: 1e-5 (all its
 pixels may share the roundings of the event's constants, each up to 2^-24 of an exponent near 13).
-Counts: exact.
+Counts: exact.  Log-likelihood: the value relative 1e-6 and dl/drho relative L2 1e-5 (an event's denominator
+divides every term of its back-projection); a sigma derivative, whose events may cancel, relative 1e-3 plus
+1e-5 of n / sigma, the size of its terms.
 """
 
 import math
@@ -113,3 +115,47 @@ def test_polynomial_and_exact_rows(R, L, sz, sdl, pixel, gamma, variant, edge):
     ev = simulate_events(c1_phantom(), R, L, sz, sdl, 700, 23, workers=1, sigma_z_edge=edge)
     rho = np.linspace(0.2, 2.0, kw["n_y"] * 90).reshape(kw["n_y"], 90)
     check(kw, ev, rho)
+
+
+@pytest.mark.parametrize("events,rings,length", SHAPES)
+@pytest.mark.parametrize("gamma,variant", [(0.0, 0), (3e-4, 1)])
+def test_log_likelihood_at_every_cache(events, rings, length, gamma, variant):
+    """Value, all gradients and the value alone, the ellipses held at sigmas 1.1 times the kernel's."""
+    mask = resolution(events, rings, length)
+    gamma = min(gamma, 0.3 / (mask[0] * mask[1]))  # a correlation well inside the domain, |gamma| sigma sigma < 1
+    kw = dict(R=450.0, L=500.0, sigma_z=mask[0] / 1.1, sigma_dl=mask[1] / 1.1, pixel=PIXEL, n_y=101, n_z=83,
+              gamma=gamma, kernel_variant=variant)
+    n = 257
+    ev_np = simulate_events(c1_phantom(), 450.0, 500.0, kw["sigma_z"], kw["sigma_dl"], n, 31 + length, workers=1)
+    check_log_likelihood(kw, ev_np, mask)
+
+
+@pytest.mark.parametrize("R,L,sz,sdl,pixel", [(130.0, 300.0, 10.0, 40.0, 4.0), (90.0, 400.0, 10.0, 30.0, 3.0)])
+def test_log_likelihood_of_polynomial_and_exact_rows(R, L, sz, sdl, pixel):
+    n_y = min(2 * int(0.45 * R / pixel), 120)
+    kw = dict(R=R, L=L, sigma_z=sz, sigma_dl=sdl, pixel=pixel, n_y=n_y, n_z=90, gamma=3e-4, kernel_variant=1)
+    check_log_likelihood(kw, simulate_events(c1_phantom(), R, L, sz, sdl, 700, 23, workers=1), None)
+
+
+def check_log_likelihood(kw, ev_np, mask):
+    g, go, n = jpet.geometry(**kw), oracle.geometry(**kw), len(ev_np)
+    ev = torch.from_numpy(ev_np).to(DEV)
+    rho_np = np.linspace(0.5, 1.5, kw["n_y"] * kw["n_z"]).reshape(kw["n_y"], kw["n_z"]).astype(np.float32)
+    rho = torch.from_numpy(rho_np).to(DEV)
+    so = oracle.sensitivity(go)
+    s = torch.from_numpy(so.astype(np.float32)).to(DEV)
+    l, dz, dd, gr, sto, D_want = oracle.loglik_grad(go, ev_np, rho_np, s=so, sigma_mask=mask, return_D=True)
+    res = jpet.loglik_grad(g, ev, rho, s=s, sigma_mask=mask, want_D=True, want_stats=True)
+    for key in ("n_valid", "n_dropped", "n_pairs", "n_zero_denominator", "n_kappa_nonpositive"):
+        assert res.stats[key] == sto[key], (key, res.stats[key], sto[key])
+    D, live = res.D.double().cpu().numpy(), D_want > 0
+    assert live.any() and np.array_equal(D > 0, live)
+    value = res.value.cpu().numpy()
+    errs = (abs(value[0] / l - 1), abs(value[1] - dz), abs(value[2] - dd),
+            rel_l2(res.grad_rho.double().cpu().numpy(), gr), float(np.max(np.abs(D[live] / D_want[live] - 1))))
+    print("errors " + " ".join(f"{e:.1e}" for e in errs), flush=True)
+    assert errs[0] <= 1e-6 and errs[3] <= 1e-5 and errs[4] <= 1e-5, errs
+    assert errs[1] <= 1e-3 * abs(dz) + 1e-5 * n / kw["sigma_z"], (value[1], dz)
+    assert errs[2] <= 1e-3 * abs(dd) + 1e-5 * n / kw["sigma_dl"], (value[2], dd)
+    alone = jpet.loglik_grad(g, ev, rho, s=s, sigma_mask=mask, value_only=True)
+    assert alone.value[0].item() == pytest.approx(l, rel=1e-6)
