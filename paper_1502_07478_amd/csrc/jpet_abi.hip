@@ -461,7 +461,7 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
   };
   const size_t nn = (size_t)(n > 0 ? n : 0);
   const size_t nb = (size_t)(p.tiled ? p.nbins : 0);
-  Workspace w;
+  Workspace w{};
   // buffers every entry point uses come first, so their offsets do not depend on the binning
   w.cnt = (unsigned long long*)take(sizeof(unsigned long long) * C_COUNT);
   w.red = (double*)take(sizeof(double) * RED_SLOTS);
@@ -820,15 +820,19 @@ int jpet_mlem_iterate(const jpet_geometry* g, const float* events, int64_t n, co
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   const Geo geo = make_geo(g, g->sigma_z, g->sigma_dl);
+  hipError_t e;
   if (!(flags & JPET_WS_PREPARED)) {
+    w.clear_acc = npix_of(g);  // the preparation clears the accumulators too
     rc = do_prepare(geo, p, events, n, w, st);
     if (rc) return rc;
+  } else {
+    if ((e = launch_fill_u64(w.acc, npix_of(g), st)) != hipSuccess) return hip_fail(e);
+    if (n_iter > 0 && (e = launch_fill_u64(w.cnt + C_ZERO_DEN, 2, st)) != hipSuccess) return hip_fail(e);
   }
-  hipError_t e = launch_fill_u64(w.acc, npix_of(g), st);
-  if (e != hipSuccess) return hip_fail(e);
   for (int it = 0; it < n_iter; ++it) {
-    rc = timed_event_pass(geo, p, n, w, rho, st, gran);
+    rc = timed([&] { return launch_event_pass(geo, p, n, w, rho, st, gran); }, st);
     if (rc) return rc;
+    w.more = it + 1 < n_iter;
     e = launch_update(geo, s, rho, w, st);
     if (e != hipSuccess) return hip_fail(e);
   }
@@ -999,9 +1003,7 @@ int jpet_loglik_grad(const jpet_geometry* g, const double* sigma_mask, const flo
     rc = do_prepare(geo, p, events, n, w, st);
     if (rc) return rc;
   }
-  hipError_t e = launch_fill_u64(w.cnt + C_ZERO_DEN, 2, st);
-  if (e != hipSuccess) return hip_fail(e);
-  e = launch_loglik(geo, p, n, w, rho, s, D_out, grad_rho, out3, value_only, st);
+  const hipError_t e = launch_loglik(geo, p, n, w, rho, s, D_out, grad_rho, out3, value_only, st);
   if (e != hipSuccess) return hip_fail(e);
   if (stats) {
     rc = read_stats(w, n, stats, st);

@@ -275,6 +275,8 @@ struct Workspace {
   double* red;                // [RED_SLOTS] double partial sums
   unsigned long long* cnt;    // [C_COUNT]
   size_t bytes;
+  int64_t clear_acc;          // accumulators that launch_prepare clears as well
+  int more;                   // launch_update: another pass follows, whose counters it clears
 };
 
 // One reconstruction of a batch, as the batched kernels read it from the workspace's instance

@@ -31,11 +31,6 @@ __global__ void k_fill_f32(float* p, int64_t n) {
     p[i] = 0.0f;
 }
 
-__global__ void k_fill_f64(double* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
-}
-
 // Direct-reconstruction image: each valid event counted at the pixel containing (y~, z~) of
 // Eq. 2 (first forms, double precision); the image is zeroed by the caller.
 __global__ void __launch_bounds__(256) k_direct_image(Geo g, double L, const float* __restrict__ events, int64_t n,
@@ -195,20 +190,57 @@ __global__ void __launch_bounds__(256) k_loglik_pass(Geo g, int64_t n, const Eve
   }
 }
 
-// Single block: fixed-order sum of the block partials, sum_l s_l rho_l, and the final scalars.
-__global__ void __launch_bounds__(256) k_loglik_finish(Geo g, int nblocks, const double* __restrict__ red,
-                                                       const float* __restrict__ rho, const float* __restrict__ s,
-                                                       const unsigned long long* __restrict__ cnt,
-                                                       double* __restrict__ out3, int value_only) {
+// The log-likelihood around its pass.  Launch latency bounds both ends (a 200^2 image is 160 KB): one launch
+// before and one after, where there were six, and no single block that reads the whole image.  200^2, 400k
+// events, value alone: 340 -> 238 us a call (the block's 82-111 us and three launches gone).
+// Before the pass: B and D_out (where given) and the counters of a pass cleared, the pass's three sums
+// too, and sum_l s_l rho_l in partial sums, one per block at red + kDotAt.
+constexpr int kDotBlocks = 256, kDotAt = RED_SLOTS - kDotBlocks;
+__global__ void __launch_bounds__(256) k_loglik_begin(int64_t npix, int64_t n, const float* __restrict__ rho,
+                                                      const float* __restrict__ s, double* __restrict__ B,
+                                                      float* __restrict__ D_out, double* __restrict__ red,
+                                                      unsigned long long* __restrict__ cnt) {
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (first < 3) red[first] = 0.0;
+  if (first == 0) cnt[C_ZERO_DEN] = cnt[C_KAPPA_BAD] = 0ull;
+  double d = 0.0;
+  for (int64_t p = first; p < npix; p += step) {
+    if (B) B[p] = 0.0;
+    d += (double)(s ? s[p] : 1.0f) * (double)rho[p];
+  }
+  if (D_out)
+    for (int64_t j = first; j < n; j += step) D_out[j] = 0.0f;
+  __shared__ double part[256 / WAVE];
+  d = wave_sum_d(d);
+  if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = d;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x / WAVE); ++w) d += part[w];
+    red[kDotAt + blockIdx.x] = d;
+  }
+}
+
+// After it: grad_rho = B - s (where asked for; s = 1 when absent) and, in the first block, the final
+// scalars from the pass's nparts triples of partial sums and the dots partial sums of s rho.
+__global__ void __launch_bounds__(256) k_loglik_end(Geo g, int nparts, int dots, const double* __restrict__ red,
+                                                    const double* __restrict__ B, const float* __restrict__ s,
+                                                    const unsigned long long* __restrict__ cnt,
+                                                    float* __restrict__ grad_rho, double* __restrict__ out3,
+                                                    int value_only) {
+  if (grad_rho) {
+    const int64_t npix = (int64_t)g.n_y * g.n_z;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npix; p += (int64_t)gridDim.x * blockDim.x)
+      grad_rho[p] = (float)(B[p] - (s ? (double)s[p] : 1.0));
+  }
+  if (blockIdx.x) return;
   __shared__ double sh[4][256];
   double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
-  for (int q = threadIdx.x; q < nblocks; q += blockDim.x) {
+  for (int q = threadIdx.x; q < nparts; q += blockDim.x) {
     a += red[3 * q];
     b += red[3 * q + 1];
     c += red[3 * q + 2];
   }
-  const int64_t npix = (int64_t)g.n_y * g.n_z;
-  for (int64_t p = threadIdx.x; p < npix; p += blockDim.x) d += (double)(s ? s[p] : 1.0f) * (double)rho[p];
+  for (int q = threadIdx.x; q < dots; q += blockDim.x) d += red[kDotAt + q];
   sh[0][threadIdx.x] = a;
   sh[1][threadIdx.x] = b;
   sh[2][threadIdx.x] = c;
@@ -229,13 +261,6 @@ __global__ void __launch_bounds__(256) k_loglik_finish(Geo g, int nblocks, const
     out3[1] = value_only ? NAN : sh[1][0] * (-2.0 * g.u / g.sigma_z);
     out3[2] = value_only ? NAN : sh[2][0] * (-2.0 * g.w / g.sigma_dl);
   }
-}
-
-// grad_rho = B - s (s = 1 when absent)
-__global__ void k_grad_rho(int64_t npix, const double* __restrict__ B, const float* __restrict__ s,
-                           float* __restrict__ out) {
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npix; p += (int64_t)gridDim.x * blockDim.x)
-    out[p] = (float)(B[p] - (s ? (double)s[p] : 1.0));
 }
 
 int grid_for(int64_t n, int block, int cap = 65536) {
@@ -275,24 +300,20 @@ hipError_t launch_loglik(const Geo& g, const Plan& p, int64_t n, const Workspace
                          const float* s, float* D_out, float* grad_rho, double* out3, bool value_only,
                          hipStream_t st) {
   const int64_t npix = (int64_t)g.n_y * g.n_z;
-  int nparts;
+  int nparts = 1;
+  // the binned pass accumulates B unless the value alone is asked for, the other one where grad_rho is
+  double* const B = (p.tiled ? !value_only : grad_rho != nullptr) ? ws.B : nullptr;
+  const int dots = grid_for(npix, 256, kDotBlocks);
+  hipLaunchKernelGGL(k_loglik_begin, dim3(dots), dim3(256), 0, st, npix, n, rho, s, B, D_out, ws.red, ws.cnt);
   if (p.tiled) {
-    // binned pass: B accumulated (unless the value alone is asked for), three partial sums
-    if (!value_only) hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(npix, 256)), dim3(256), 0, st, ws.B, npix);
-    hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, st, ws.red, (int64_t)3);
-    if (D_out) hipLaunchKernelGGL(k_fill_f32, dim3(grid_for(n, 256)), dim3(256), 0, st, D_out, n);
     const hipError_t e = launch_loglik_tiled(g, p, n, ws, rho, D_out, value_only, st);
     if (e != hipSuccess) return e;
-    nparts = 1;
   } else {
-    nparts = grid_for(n, 256 / WAVE, RED_SLOTS / 3);
-    if (grad_rho) hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(npix, 256)), dim3(256), 0, st, ws.B, npix);
-    hipLaunchKernelGGL(k_loglik_pass, dim3(nparts), dim3(256), 0, st, g, n, ws.ev, rho, grad_rho ? ws.B : nullptr,
-                       D_out, ws.red, ws.cnt);
+    nparts = grid_for(n, 256 / WAVE, kDotAt / 3);
+    hipLaunchKernelGGL(k_loglik_pass, dim3(nparts), dim3(256), 0, st, g, n, ws.ev, rho, B, D_out, ws.red, ws.cnt);
   }
-  hipLaunchKernelGGL(k_loglik_finish, dim3(1), dim3(256), 0, st, g, nparts, ws.red, rho, s, ws.cnt, out3,
-                     value_only ? 1 : 0);
-  if (grad_rho) hipLaunchKernelGGL(k_grad_rho, dim3(grid_for(npix, 256)), dim3(256), 0, st, npix, ws.B, s, grad_rho);
+  hipLaunchKernelGGL(k_loglik_end, dim3(grad_rho ? grid_for(npix, 256, 1024) : 1), dim3(256), 0, st, g, nparts, dots,
+                     ws.red, ws.B, s, ws.cnt, grad_rho, out3, value_only ? 1 : 0);
   return hipGetLastError();
 }
 

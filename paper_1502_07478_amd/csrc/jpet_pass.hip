@@ -102,8 +102,10 @@ __global__ void __launch_bounds__(256) k_event_pass_thread(Geo g, int64_t n, con
 }
 
 // rho_l = acc_l 2^-32 / s_l (0 where s_l = 0), or acc_l 2^-32 without sensitivity; acc cleared.
+// cnt (nullable): the pass's counters, cleared for the next one.
 __global__ void k_update(int64_t npix, const float* __restrict__ s, float* __restrict__ rho,
-                         unsigned long long* __restrict__ acc) {
+                         unsigned long long* __restrict__ acc, unsigned long long* __restrict__ cnt) {
+  if (cnt && blockIdx.x == 0 && threadIdx.x == 0) cnt[C_ZERO_DEN] = cnt[C_KAPPA_BAD] = 0ull;
   for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < npix; q += (int64_t)gridDim.x * blockDim.x) {
     const double a = (double)acc[q] * 2.3283064365386962890625e-10;
     double v;
@@ -241,7 +243,8 @@ hipError_t launch_update(const Geo& g, const float* s, float* rho, const Workspa
   const int64_t npix = (int64_t)g.n_y * g.n_z;
   int64_t blocks = (npix + 255) / 256;
   if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_update, dim3((unsigned)blocks), dim3(256), 0, st, npix, s, rho, ws.acc);
+  hipLaunchKernelGGL(k_update, dim3((unsigned)blocks), dim3(256), 0, st, npix, s, rho, ws.acc,
+                     ws.more ? ws.cnt : nullptr);
   return hipGetLastError();
 }
 

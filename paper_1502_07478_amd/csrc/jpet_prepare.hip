@@ -1,6 +1,6 @@
 // Per-event preparation and spatial binning (iteration-invariant, run once per event list).
 //
-//   k_clear        counters and events per bin
+//   k_clear        counters and events per bin (and the accumulators, where asked for)
 //   k_prepare      direct reconstruction (Eq. 2), ellipse rows (App. B, Sec. 3), validity; for the binned
 //                  passes each event's bin and its rank in it, for the others the pixel count
 //   k_scan         exclusive prefix sums over the bins of events, workgroup items and batch blocks
@@ -89,10 +89,12 @@ __device__ EventRec event_record(const Geo& g, const float* __restrict__ events,
   return e;
 }
 
-__global__ void k_clear(unsigned long long* __restrict__ cnt, uint32_t* __restrict__ bin_count, int64_t nbins) {
+__global__ void k_clear(unsigned long long* __restrict__ cnt, uint32_t* __restrict__ bin_count, int64_t nbins,
+                        unsigned long long* __restrict__ acc, int64_t npix) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < C_COUNT) cnt[i] = 0ull;
   if (i < nbins) bin_count[i] = 0u;
+  if (i < npix) acc[i] = 0ull;
 }
 
 // Sums over the workgroup, added to the counters by one thread.
@@ -744,8 +746,9 @@ int blocks_for(int64_t n, int block) { return (int)((n + block - 1) / block); }
 hipError_t launch_prepare(const Geo& g, const Plan& p, const float* events, int64_t n, const Workspace& ws,
                           hipStream_t st) {
   const int64_t nb = p.tiled ? p.nbins : 0;
-  hipLaunchKernelGGL(k_clear, dim3(blocks_for(nb > C_COUNT ? nb : C_COUNT, 256)), dim3(256), 0, st, ws.cnt,
-                     ws.bin_count, nb);
+  const int64_t clear = std::max<int64_t>(C_COUNT, std::max(nb, ws.clear_acc));
+  hipLaunchKernelGGL(k_clear, dim3(blocks_for(clear, 256)), dim3(256), 0, st, ws.cnt, ws.bin_count, nb, ws.acc,
+                     ws.clear_acc);
   if (!p.tiled) {
     if (n > 0)
       hipLaunchKernelGGL(k_prepare_plain, dim3(blocks_for(n, 256)), dim3(256), 0, st, g, events, n, ws.ev, ws.cnt);
