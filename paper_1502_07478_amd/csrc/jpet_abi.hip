@@ -383,7 +383,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
               int simd = occ;
               if (shape && (pitch == shape_pitch(shape, 0) || pitch == shape_pitch(shape, 1))) {
                 const int most = 4 * shape_waves_per_simd(shape, loglik);
-                const int fit = std::max(1, std::min(wgs, (most + waves / 2) / waves)), each = std::min(waves, most / fit);
+                const int fit = std::max(1, std::min(wgs, (most + waves / 2) / waves)), each = std::max(4, std::min(waves, most / fit) / 4 * 4);
                 const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
                 const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, loglik).bytes;
                 if (lds <= kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
@@ -403,18 +403,11 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
                 p.tmin = -0.5 * dt * p.ntb;
               }
               finish_plan(g, rows_max, pairs_per_event, n, p);
-              double cost;
-              if (loglik) {
-                const double items = nn / p.ev_per_wg + (nn < p.nbins ? nn : (double)p.nbins);
-                cost = nn * pairs_per_event * occ_factor + 1.6 * items * (double)pitch * (double)W;
-              }
-              if (!loglik || p.rings) {
-                const double some = 0.35 * (double)p.nbins;  // the bins an object fills
-                const double items = nn / p.ev_per_wg + some * (1.0 - exp(-nn / some));
-                const double unit = p.rings ? 0.5 * pow(4.0 / (double)simd, 0.58) * (p.waves == 16 ? 1.05 : 1.0)
-                                            : occ_factor * (acc32 ? 0.82 : 1.0);
-                cost = nn * pairs_per_event * unit + 4.5 * items * (double)RY * (double)W;
-              }
+              const double some = 0.35 * (double)p.nbins;  // the bins an object fills
+              const double items = nn / p.ev_per_wg + some * (1.0 - exp(-nn / some));
+              const double unit = p.rings ? 0.5 * pow(4.0 / (double)simd, 0.58) * (p.waves == 16 ? 1.05 : 1.0)
+                                          : occ_factor * (acc32 ? 0.82 : 1.0);
+              const double cost = nn * pairs_per_event * unit + 4.5 * items * (double)RY * (double)W;
               out->push_back({p, cost});
             }
           }
@@ -1234,7 +1227,7 @@ static int batched_begin(const jpet_instance* inst, int32_t count, void* ws, siz
     const BatchClass& C = L->cls[c];
     size_t lds = C.lds;
     for (const BatchClass& D : L->cls)
-      if (D.kernel == C.kernel && D.waves == C.waves && D.pitch == C.pitch && D.lds > lds) lds = D.lds;
+      if (D.kernel == C.kernel && D.pitch == C.pitch && D.lds > lds) lds = D.lds;  // whatever their waves
     const hipError_t e = set_batched_lds(C.kernel, C.waves, C.pitch, lds);
     if (e != hipSuccess) return hip_fail(e);
   }

@@ -267,7 +267,7 @@ struct Workspace {
   uint32_t* bin_start;        // [nbins + 1]
   uint32_t* rank;             // [n] position of each event in its bin
   uint32_t* item_start;       // [nbins + 1] full workgroup items before each bin
-  uint32_t* rest_start;       // [nbins + 1] bins before each that also make a shorter item
+  uint32_t* rest_start;       // [nbins + 1] each bin's shorter item, if it makes one
   uint32_t* batch_start;      // [nbins + 1] first batch block of each bin
   BinItem* items;             // [max_items]
   unsigned long long* acc;    // [npix] back-projection accumulator, units of 2^-32
