@@ -305,21 +305,25 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
   // compiled for a register cache of 16/32/48/64 pixels keeps at most 8/6/5/4 wavefronts per SIMD
   // (its launch bounds guarantee that many).
   //
-  // Each candidate's cost-model figure, in units of (event, pixel) pairs:
+  // Each candidate's cost-model figure, in units of (event, pixel) pairs.  On batches of rows:
   //   pairs of all events (an ellipse's area at theta = 0)
   //     x (4 / wavefronts per SIMD)^0.58  (measured: 6 resident wavefronts per SIMD run the pass
   //                                        in 0.79 of the time of 4)
   //     x 1.1 for 16-wave workgroups (more wavefronts meet at every barrier)
   //     x 0.82 for 32-bit accumulators (the back-projection's LDS atomics, about 30% of the pass
   //            with 64-bit ones, run 2.7 times faster on 32-bit words)
-  //   + 1.6 x region pixels x workgroup items,
-  // the second term being the staging of the image region and the flush of its accumulators
-  // (about 1.6 pair evaluations per region pixel); items are the events over the events per item
-  // plus, at most, one partial item per bin.
+  //   + 4.5 x region pixels x workgroup items,
+  // the second term being the staging of the image region and the flush of its accumulators; items
+  // are the events over the events per item plus one partial item for each bin an object fills.
   // (the log-likelihood pass, with its derivative terms, keeps 6 / 4 / 4 / 4).  Rows longer than
   // a cache of 16 or 32 may also be split into two segments, one thread each (x 1.3: the second
   // row setups, the shorter segments and the lanes they leave idle; a prior, not a measurement,
   // that keeps whole rows the model's choice wherever they fit and leaves split plans to timing).
+  // On ring blocks half of the pairs' time, 1.35 x region pixels x items (the flush runs along image rows; 3.1
+  // for the log-likelihood's doubles), and a quarter of the time of the last items, as many of the smallest
+  // as are resident.  The constants are a fit to 2900 timed plans of 32 calls (5,000 to 10M events,
+  // 61 x 77 to 1024^2, both passes): the first candidate is 1.8% slower than the best one in the mean, 7%
+  // (once 10%) at most; with one item term as on batches 4.5% and 17%.
   for (int cache = 0; cache <= 2; ++cache) {
     int maxlen = natural, segs = 1;
     if (cache > 0) {
@@ -403,11 +407,20 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
                 p.tmin = -0.5 * dt * p.ntb;
               }
               finish_plan(g, rows_max, pairs_per_event, n, p);
-              const double some = 0.35 * (double)p.nbins;  // the bins an object fills
-              const double items = nn / p.ev_per_wg + some * (1.0 - exp(-nn / some));
-              const double unit = p.rings ? 0.5 * pow(4.0 / (double)simd, 0.58) * (p.waves == 16 ? 1.05 : 1.0)
-                                          : occ_factor * (acc32 ? 0.82 : 1.0);
-              const double cost = nn * pairs_per_event * unit + 4.5 * items * (double)RY * (double)W;
+              // (some: the bins an object fills; rests: those that make an item of fewer events)
+              const double some = (p.rings ? 0.6 : 0.35) * (double)p.nbins, rests = some * (1.0 - exp(-nn / some));
+              double cost;
+              if (p.rings) {
+                const double unit = 0.5 * pow(4.0 / (double)simd, 0.62) * pow(p.waves / 8.0, 0.25);
+                const double items = std::max(nn / p.ev_per_wg + 0.56 * rests, rests);
+                const double resident = std::min(256.0 * 4.0 * simd / p.waves, items);
+                const double last = std::min(nn, (double)p.ev_per_wg) * std::min(1.0, resident / rests);
+                cost = (nn + 0.26 * resident * last) * pairs_per_event * unit +
+                       (loglik ? 3.1 : 1.35) * items * (double)RY * (double)W;
+              } else {
+                cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
+                       4.5 * (nn / p.ev_per_wg + rests) * (double)RY * (double)W;
+              }
               out->push_back({p, cost});
             }
           }
