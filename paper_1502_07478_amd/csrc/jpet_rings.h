@@ -41,8 +41,16 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 struct RingShared {
-  unsigned zero, bad;
+  unsigned zero, bad, odd;
 };
+
+// Accumulator units without a conversion.  A single-precision number below 2^-124 is, bit for bit, the
+// count of its 2^-149: with the image scaled by 2^-kBitsScale and the unit by 2^-149 on top, the product of
+// pass 2 is the addend itself, rounded to nearest.  Scaled so, no intermediate of an item whose image lies in
+// [2^-66, 2^24) (or is 0) leaves the normal range: P rho >= 2^-13 2^-66 2^-44, unit F / D >= 2^-126.  Other
+// images, and items of units finer than 2^-24 (fewer than 128 events), convert.  Ten iterations of 10M events on
+// 400^2: 58.8 -> 57.7 ms, on 64 x 76: 21.9 -> 21.0.
+constexpr int kBitsScale = 44, kBitsShift = 24;
 
 // Pass 1 along a lane's row of one ring (see pass1_poly in jpet_binned.h): chunks below the
 // wavefront's shortest row without masks, the others with the reads past the row's ends discarded
@@ -101,17 +109,18 @@ __device__ __forceinline__ float ring_forward(const RowP& p, const float* __rest
 
 // Pass 2 of one ring: m sc rounded into the fixed-point accumulators, up to the wavefront's longest
 // row; past a row's own ends m is 0 and adds nothing.
-template <int H>
+template <int H, bool BITS>
 __device__ __forceinline__ void ring_back(const float (&m)[2 * H], float sc, unsigned* __restrict__ a, int pitch,
                                           int wlh) {
+  auto units = [&](float v) { return BITS ? __float_as_uint(v * sc) : (unsigned)fmaf(v, sc, 0.5f); };
 #pragma unroll
   for (int i0 = 0; i0 < H; i0 += 2) {
     if (i0 < wlh) {  // wavefront-uniform
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         if (i0 + q >= H) continue;
-        atomicAdd(&a[(H - 1 - i0 - q) * pitch], (unsigned)fmaf(m[H - 1 - i0 - q], sc, 0.5f));
-        atomicAdd(&a[(H + i0 + q) * pitch], (unsigned)fmaf(m[H + i0 + q], sc, 0.5f));
+        atomicAdd(&a[(H - 1 - i0 - q) * pitch], units(m[H - 1 - i0 - q]));
+        atomicAdd(&a[(H + i0 + q) * pitch], units(m[H + i0 + q]));
       }
     }
   }
@@ -199,7 +208,6 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
   const int rbase = ty * p.TY - p.HY;
   const int kbase = kmin + tz * p.TZ - p.HZ;
   const float pixf = uniform_f((float)g.pixel), pix2 = uniform_f(pixf * pixf);
-  const float kUnit = uniform_f(__builtin_ldexpf(1.0f, p.acc_shift));
 
   // a block's constants (16 bytes per lane to LDS), words and ring tails
   uint32_t word[kWords];
@@ -216,24 +224,35 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     tails = *reinterpret_cast<const uint2*>(blk + ring_tails(kEvents, false));
   };
   if (wave < nblk) fetch(wave, 0);
-  if (tid == 0) ps.zero = ps.bad = 0u;
+  if (tid == 0) ps.zero = ps.bad = ps.odd = 0u;
   for (int r = tid; r < p.RY; r += blockDim.x) off_s[r] = shear_offset(g, tc, rbase + r);
-  __syncthreads();
-  for (int cl = wave; cl < p.W; cl += waves) {
-    const int kc = kbase + cl;
-    for (int rl = lane; rl < pitch; rl += WAVE) {
-      const int q = cl * pitch + rl;
-      const int r = rbase + rl;
-      float v = 0.0f;
-      if (rl < p.RY && r >= 0 && r < g.n_y) {
-        const int k = kc + off_s[rl];
-        if (k >= 0 && k < g.n_z) v = rho[(int64_t)r * g.n_z + k];
+  bool bits = p.acc_shift <= kBitsShift;
+  for (;;) {
+    const float scale = bits ? __builtin_ldexpf(1.0f, -kBitsScale) : 1.0f;
+    bool odd = false;
+    __syncthreads();
+    for (int cl = wave; cl < p.W; cl += waves) {
+      const int kc = kbase + cl;
+      for (int rl = lane; rl < pitch; rl += WAVE) {
+        const int q = cl * pitch + rl;
+        const int r = rbase + rl;
+        float v = 0.0f;
+        if (rl < p.RY && r >= 0 && r < g.n_y) {
+          const int k = kc + off_s[rl];
+          if (k >= 0 && k < g.n_z) v = rho[(int64_t)r * g.n_z + k];
+        }
+        odd |= v != 0.0f && !(v >= __builtin_ldexpf(1.0f, -66) && v < 16777216.0f);
+        rho_s[q] = v * scale;
+        acc_s[q] = 0u;
       }
-      rho_s[q] = v;
-      acc_s[q] = 0u;
     }
+    if (bits && odd) ps.odd = 1u;
+    __syncthreads();
+    if (!bits || ps.odd == 0u) break;  // uniform over the workgroup
+    bits = false;                      // once more, as it is
   }
-  __syncthreads();
+  const float kUnit = uniform_f(__builtin_ldexpf(1.0f, bits ? p.acc_shift - 149 : p.acc_shift));
+  const float tiny = uniform_f(bits ? 0.0f : 1e-28f);
 
   int buf = 0;
   for (int q = wave; q < nblk; q += waves, buf ^= 1) {
@@ -252,7 +271,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     auto denominator = [&](float D) {
       if (c.index < 0) return;  // no event
       if (!(D > 0.0f)) atomicAdd(&ps.zero, 1u);
-      if (D_out) D_out[c.index] = (float)((double)D * g.cnorm);
+      if (D_out) D_out[c.index] = (float)((double)D * g.cnorm * (bits ? __builtin_ldexp(1.0, kBitsScale) : 1.0));
     };
     auto tail = [&](int k) { return ((k < 2 ? t01 : t23) >> (16 * (k & 1))) & 0xffffu; };
     auto row = [&](int k, int H) { return ring_row(w[k >> 1] >> (16 * (k & 1)), c.mid + lrow + k * lstep, H); };
@@ -297,14 +316,16 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
       float Dlo, Dhi;
       const float De = event_sum(D, Dlo, Dhi);  // the event's denominator
       // (a unit / D overflows a float only for D < 1e-28: such blocks take the way below)
-      if (!(Dlo > 0.0f && Dlo < 1e-28f) && !(Dhi > 0.0f && Dhi < 1e-28f)) {  // wavefront-uniform
+      if (!(Dlo > 0.0f && Dlo < tiny) && !(Dhi > 0.0f && Dhi < tiny)) {  // wavefront-uniform
         if (l == 0) denominator(De);
         const float sc = De > 0.0f ? kUnit * __builtin_amdgcn_rcpf(De) : 0.0f;
         each_ring<0, RINGS>([&](auto kk) {
           constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
           const int wlh = (int)((tail(k) & 127u) + 1) >> 1;
-          if (at[k] != kNoRow && sc > 0.0f)
-            ring_back<H>(cache.template ring<k>(), sc * F[k], acc_s + at[k], pitch, wlh);
+          if (at[k] != kNoRow && sc > 0.0f) {
+            if (bits) ring_back<H, true>(cache.template ring<k>(), sc * F[k], acc_s + at[k], pitch, wlh);
+            else ring_back<H, false>(cache.template ring<k>(), sc * F[k], acc_s + at[k], pitch, wlh);
+          }
         });
         continue;
       }
@@ -328,7 +349,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const float De = event_sum(D, Dlo, Dhi);
     if (l == 0) denominator(De);
     if (!(De > 0.0f)) continue;
-    const float sc = (float)((double)kUnit / ((double)De * 18446744073709551616.0));
+    const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / ((double)De * 18446744073709551616.0));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
       const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);

@@ -159,3 +159,19 @@ def check_log_likelihood(kw, ev_np, mask):
     assert errs[2] <= 1e-3 * abs(dd) + 1e-5 * n / kw["sigma_dl"], (value[2], dd)
     alone = jpet.loglik_grad(g, ev, rho, s=s, sigma_mask=mask, value_only=True)
     assert alone.value[0].item() == pytest.approx(l, rel=1e-6)
+
+
+@pytest.mark.parametrize("image", ["plain", "zero band", "tiny band", "bright spot"])
+def test_large_items_take_their_units_from_the_bits(image):
+    """Items of 128 events and more form their units without a conversion, but for regions with pixels outside
+    the range that allows it, here a band of 1e-25 and a spot of 1e9: the same bounds hold for all."""
+    sz, sdl = resolution(2, 1, 12)
+    kw = dict(R=450.0, L=500.0, sigma_z=sz, sigma_dl=sdl, pixel=PIXEL, n_y=101, n_z=83)
+    ev = simulate_events(c1_phantom(), 450.0, 500.0, sz, sdl, 140_000, 3, workers=4)
+    assert jpet.launch_info(jpet.geometry(**kw), len(ev))["events_per_workgroup"] >= 128
+    rho = np.linspace(0.5, 1.5, 101 * 83).reshape(101, 83)
+    if image != "plain":
+        rho[40:60] *= {"zero band": 0.0, "tiny band": 1e-25, "bright spot": 1.0}[image]
+    if image == "bright spot":
+        rho[50, 40] = 1e9
+    check(kw, ev, rho)
