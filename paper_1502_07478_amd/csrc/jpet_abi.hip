@@ -909,7 +909,9 @@ int jpet_mlem_denominators(const jpet_geometry* g, const float* events, int64_t 
   if (e != hipSuccess) return hip_fail(e);
   rc = timed_event_pass(geo, p, n, w, rho, st, gran, D_out);
   if (rc) return rc;
-  if ((e = launch_fill_u64(w.acc, npix_of(g), st)) != hipSuccess) return hip_fail(e);
+  // (the pass on ring blocks forms the sums alone)
+  if (!(p.rings && gran == kPassPlanned) && (e = launch_fill_u64(w.acc, npix_of(g), st)) != hipSuccess)
+    return hip_fail(e);
   if (stats) return read_stats(w, n, stats, st);
   return JPET_OK;
 }

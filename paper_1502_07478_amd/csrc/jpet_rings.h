@@ -178,8 +178,9 @@ struct RingCache {
 // One workgroup item (see event_pass_item in jpet_binned.h for the region and the units).  LDS: per
 // wavefront two buffers of a block's constants (the next block's are copied in while this one runs),
 // the column shift of every region row, then from p.lds_img the image and the accumulators, with
-// p.slack columns free before and after them that masked reads and additions of 0 may touch.
-template <int RINGS, int LEN, bool SOLO, int PITCH>
+// p.slack columns free before and after them that masked reads and additions of 0 may touch.  FORWARD:
+// the forward sums alone, to D_out (778k events on 400^2: 553 -> 425 us with the back-projection left out).
+template <int RINGS, int LEN, bool SOLO, int PITCH, bool FORWARD = false>
 __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const unsigned char* __restrict__ blocks,
                                           const BinItem it, const float* __restrict__ rho,
                                           unsigned long long* __restrict__ acc, unsigned long long* __restrict__ cnt,
@@ -243,7 +244,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
         }
         odd |= v != 0.0f && !(v >= __builtin_ldexpf(1.0f, -66) && v < 16777216.0f);
         rho_s[q] = v * scale;
-        acc_s[q] = 0u;
+        if constexpr (!FORWARD) acc_s[q] = 0u;
       }
     }
     if (bits && odd) ps.odd = 1u;
@@ -271,7 +272,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     auto denominator = [&](float D) {
       if (c.index < 0) return;  // no event
       if (!(D > 0.0f)) atomicAdd(&ps.zero, 1u);
-      if (D_out) D_out[c.index] = (float)((double)D * g.cnorm * (bits ? __builtin_ldexp(1.0, kBitsScale) : 1.0));
+      if constexpr (FORWARD) D_out[c.index] = (float)((double)D * g.cnorm * (bits ? __builtin_ldexp(1.0, kBitsScale) : 1.0));
     };
     auto tail = [&](int k) { return ((k < 2 ? t01 : t23) >> (16 * (k & 1))) & 0xffffu; };
     auto row = [&](int k, int H) { return ring_row(w[k >> 1] >> (16 * (k & 1)), c.mid + lrow + k * lstep, H); };
@@ -318,6 +319,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
       // (a unit / D overflows a float only for D < 1e-28: such blocks take the way below)
       if (!(Dlo > 0.0f && Dlo < tiny) && !(Dhi > 0.0f && Dhi < tiny)) {  // wavefront-uniform
         if (l == 0) denominator(De);
+        if constexpr (FORWARD) continue;
         const float sc = De > 0.0f ? kUnit * __builtin_amdgcn_rcpf(De) : 0.0f;
         each_ring<0, RINGS>([&](auto kk) {
           constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
@@ -348,7 +350,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     float Dlo, Dhi;
     const float De = event_sum(D, Dlo, Dhi);
     if (l == 0) denominator(De);
-    if (!(De > 0.0f)) continue;
+    if (FORWARD || !(De > 0.0f)) continue;
     const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / ((double)De * 18446744073709551616.0));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
@@ -367,7 +369,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
   // less (lanes along the region's columns, free of conflicts: every atomic a line of its own)
   const int flush_shift = 32 - p.acc_shift;
   const float inv_w = 1.0f / (float)p.W;
-  for (int q = tid; q < p.RY * p.W; q += (int)blockDim.x) {
+  for (int q = FORWARD ? p.RY * p.W : tid; q < p.RY * p.W; q += (int)blockDim.x) {
     const int rl = (int)(((float)q + 0.5f) * inv_w), cl = q - rl * p.W;
     const unsigned long long a = (unsigned long long)acc_s[cl * pitch + rl] << flush_shift;
     if (a == 0ull) continue;
@@ -381,7 +383,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
   }
 }
 
-template <int SHAPE, int PITCH>
+template <int SHAPE, int PITCH, bool FORWARD>
 __global__ void __launch_bounds__((shape_threads(SHAPE)), (shape_waves_per_simd(SHAPE)))
     k_event_pass_rings(Geo g, Plan p, const unsigned char* __restrict__ blocks, const BinItem* __restrict__ items,
                        const float* __restrict__ rho, unsigned long long* __restrict__ acc,
@@ -389,8 +391,8 @@ __global__ void __launch_bounds__((shape_threads(SHAPE)), (shape_waves_per_simd(
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ RingShared ps;
   if ((unsigned long long)blockIdx.x >= cnt[C_ITEMS]) return;  // uniform over the workgroup
-  ring_item<shape_rings(SHAPE), shape_len(SHAPE), (SHAPE >= 1000), PITCH>(g, p, blocks, items[blockIdx.x], rho, acc,
-                                                                          cnt, smem, ps, D_out);
+  ring_item<shape_rings(SHAPE), shape_len(SHAPE), (SHAPE >= 1000), PITCH, FORWARD>(g, p, blocks, items[blockIdx.x],
+                                                                                   rho, acc, cnt, smem, ps, D_out);
 }
 
 // The same over a class of a batch's instances (see k_event_pass_batched in jpet_binned.h).
@@ -419,8 +421,11 @@ template <int SHAPE>
 hipError_t Rings<SHAPE>::event_pass(const Geo& g, const Plan& p, const Workspace& ws, const float* rho, float* D_out,
                                     hipStream_t st) {
   if (p.pitch != shape_pitch(SHAPE, 0) && p.pitch != shape_pitch(SHAPE, 1)) return hipErrorInvalidValue;
-  auto kern = p.pitch == shape_pitch(SHAPE, 0) ? k_event_pass_rings<SHAPE, shape_pitch(SHAPE, 0)>
-                                               : k_event_pass_rings<SHAPE, shape_pitch(SHAPE, 1)>;
+  constexpr int kFirst = shape_pitch(SHAPE, 0), kSecond = shape_pitch(SHAPE, 1);
+  auto kern = p.pitch == kFirst ? (D_out ? k_event_pass_rings<SHAPE, kFirst, true>
+                                         : k_event_pass_rings<SHAPE, kFirst, false>)
+                                : (D_out ? k_event_pass_rings<SHAPE, kSecond, true>
+                                         : k_event_pass_rings<SHAPE, kSecond, false>);
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), p.lds_bytes, st, g, p, ws.batches,

@@ -8,7 +8,7 @@ namespace jpet {
 namespace {
 
 // Single-precision kernel constants along one pixel row (Eq. 7-12) as functions of the pixel's offset
-// x in the row, from its first pixel (jpet_binned.h) or from its centre (jpet_paired.h):
+// x in the row, from its first pixel (jpet_binned.h) or from its centre (jpet_rings.h):
 //   kappa = kap0 + x dkap,  sqrt(S) gamma = gs0 + x dgs,  S q = (qa x + qb) x + qc
 // (qa = S 2u pixel^2 depends on the event through its sigma_z)
 // and P / (sqrt(det C^-1) / 2 pi) = kappa^-1/2 exp2(S gamma^2 / kappa - S q), S = log2(e) / 2.
