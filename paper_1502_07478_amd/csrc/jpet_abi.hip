@@ -211,18 +211,6 @@ static int ring_slack(int shape, int HZ, double slope, double hy_px) {
 // take 17 us, above that the larger items leave the last round of workgroups emptier).
 constexpr double kItemPairs = 7000.0;
 
-// LDS per CU, and the granule it is allotted in: measured on gfx950, three workgroups of 51,984 bytes each
-// run on one CU but three of 54,032 bytes do not (the pass then runs 27% slower), so a workgroup's LDS is
-// counted in whole 2 KB granules.
-constexpr size_t kLdsPerCU = 160 * 1024, kLdsGranule = 2048;
-
-// Workgroups of a plan on ring blocks resident per CU, by registers and LDS.
-static int ring_resident(const Plan& p) {
-  const int shape = pass_kernel(p) - 10000;
-  return std::max(1, std::min(4 * shape_waves_per_simd(shape, p.loglik != 0) / p.waves,
-                              (int)(kLdsPerCU / align_up(p.lds_bytes + 256, kLdsGranule))));
-}
-
 // Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set.
 static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, Plan& p) {
   const double pix = g->pixel;
@@ -262,14 +250,7 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   if (p.rings && (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W) per = n / 512;
   if (per < p.ev_per_batch) per = p.ev_per_batch;
   const int64_t most = p.rings ? kRingItem : 128 * p.ev_per_batch;
-  if (per > most) {
-    per = most;
-    if (p.rings) {
-      // a whole number of rounds of the resident workgroups
-      const int64_t round = 256 * (int64_t)ring_resident(p), items = (n + most * round - 1) / (most * round) * round;
-      per = std::min(most, ((n + items - 1) / items + 1) / 2 * 2);
-    }
-  }
+  if (per > most) per = most;
   // 32-bit accumulators hold 2^-s units: one event adds at most 2^s to a pixel, so an item of up
   // to 2^(32-s) - 1 events cannot overflow before the flush.  Items of at most 511 events keep
   // s = 23 (a rounding step of 2^-23 of a count per pair).
@@ -351,8 +332,11 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
       segs = 2;
     }
     const int simd_waves = loglik ? (maxlen <= 16 ? 6 : 4) : maxlen <= 16 ? 8 : maxlen <= 32 ? 6 : maxlen <= 48 ? 5 : 4;
-    // the passes' static LDS: per-event denominators (the log-likelihood pass also its derivative sums)
-    const size_t kStatic = loglik ? 3 * 1024 : 1024;
+    // LDS per CU, the passes' static LDS (per-event denominators; the log-likelihood pass also its
+    // derivative sums), and the allocation granule: measured on gfx950, three workgroups of 51,984
+    // bytes each run on one CU but three of 54,032 bytes do not (the pass then runs 27% slower), so
+    // a workgroup's LDS is counted in whole 2 KB granules.
+    const size_t kLdsPerCU = 160 * 1024, kStatic = loglik ? 3 * 1024 : 1024, kGranule = 2048;
     const double pairs_per_event = 3.14159265358979323846 * hy_px * (3.0 * msz / sqrt(2.0) / pix);
     const double nn = (double)(n > 0 ? n : 1);
     for (int waves : {8, 16}) {
@@ -360,7 +344,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
       for (int wgs = 1; wgs <= 4; ++wgs) {
         const int occ = wgs * waves / 4;  // resident wavefronts per SIMD
         if (occ > simd_waves) continue;
-        const size_t budget = kLdsPerCU / (size_t)wgs / kLdsGranule * kLdsGranule - kStatic;
+        const size_t budget = kLdsPerCU / (size_t)wgs / kGranule * kGranule - kStatic;
         const double occ_factor = pow(4.0 / (double)occ, 0.58) * (waves == 16 ? 1.1 : 1.0) * (segs > 1 ? 1.3 : 1.0);
         for (int acc32 = 0; acc32 <= 1; ++acc32) {
           if (acc32 && !allow_acc32) continue;
@@ -406,14 +390,14 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
                 const int fit = std::max(1, std::min(wgs, (most + waves / 2) / waves)), each = std::max(4, std::min(waves, most / fit) / 4 * 4);
                 const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
                 const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, loglik).bytes;
-                if (lds <= kLdsPerCU / (size_t)fit / kLdsGranule * kLdsGranule - 256) {
+                if (lds <= kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
                   p.rings = shape_rings(shape);
                   p.solo = shape >= 1000;
                   p.ring_len = shape_len(shape);
                   for (int k = 0; k < p.rings; ++k) p.ring_half[k] = ring_half_of(p.rings, p.ring_len, k);
                   p.slack = slack;
                   p.waves = each;
-                  simd = std::min(most / each, (int)(kLdsPerCU / align_up(lds + 256, kLdsGranule))) * each / 4;  // (ring_resident)
+                  simd = std::min(most / each, (int)(kLdsPerCU / align_up(lds + 256, kGranule))) * each / 4;
                 }
               }
               if (dt != 0.0) {
