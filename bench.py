@@ -454,7 +454,7 @@ def main():
         "unit": "T VALU-slot/s",
         "frac": round(achieved / PEAK_SLOTS, 4),
         "traffic": MEASURED_TRAFFIC.get(f"{kernel_source_hash()}:{g.plan}"),
-        "kernel": "k_event_pass_tiled",
+        "kernel": "k_event_pass_rings",
         "avg_launch_ms": round(avg_pass_s * 1e3, 4),
         "launches": launches,
         "pairs_per_launch": n_pairs,
