@@ -248,6 +248,13 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   // ring blocks: where a workgroup's share of the events is worth less than staging and flushing the
   // region, fewer and larger items
   if (p.rings && (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W) per = n / 512;
+  if (p.rings) {
+    // a block for every wavefront, two where that leaves an item for every CU.  (Below some 16,000 events the
+    // region's staging and flush are most of an item: 400^2, five iterations of 3,000 events 417 -> 184 us, of
+    // 20,000 390 -> 330, against items of n / 1024 events.)
+    const int64_t round = (int64_t)p.ev_per_batch * p.waves;
+    per = std::max(per, std::max(round, std::min(2 * round, n / 256)));
+  }
   if (per < p.ev_per_batch) per = p.ev_per_batch;
   const int64_t most = p.rings ? kRingItem : 128 * p.ev_per_batch;
   if (per > most) per = most;
