@@ -211,9 +211,22 @@ static int ring_slack(int shape, int HZ, double slope, double hy_px) {
 // take 17 us, above that the larger items leave the last round of workgroups emptier).
 constexpr double kItemPairs = 7000.0;
 
-// Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set.
-static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, Plan& p) {
+// Columns of the grid in the sheared frame of a plan's t bins: the widest over them.
+static int sheared_span(const jpet_geometry* g, const Plan& p) {
   const double pix = g->pixel;
+  const double y0 = (0.5 - 0.5 * (double)g->n_y) * pix, y1 = y0 + (g->n_y - 1) * pix;
+  int span = g->n_z;
+  for (int b = 0; b < p.ntb; ++b) {
+    const double tc = p.ntb > 1 ? p.tmin + (b + 0.5) * p.dt : 0.0;
+    const int o0 = (int)rint(tc * y0 / pix), o1 = (int)rint(tc * y1 / pix);
+    span = std::max(span, g->n_z + std::abs(o1 - o0));
+  }
+  return span;
+}
+
+// Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set; span: its
+// sheared_span.
+static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, int span, Plan& p) {
   if (p.rings) {
     p.ev_per_batch = p.solo ? 1 : 2;
     const RingLds lds = ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, p.loglik != 0);
@@ -230,16 +243,6 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
         (int)(((unsigned)p.cbytes + 4u * (64u + kBlockTailWords) * (unsigned)p.waves + 255u) / 256u * 256u);
   }
   p.nty = (g->n_y + p.TY - 1) / p.TY;
-  // sheared column span: the widest over the t bins
-  int span = g->n_z;
-  for (int b = 0; b < p.ntb; ++b) {
-    const double tc = p.ntb > 1 ? p.tmin + (b + 0.5) * p.dt : 0.0;
-    const double y0 = (0.5 - 0.5 * (double)g->n_y) * pix, y1 = y0 + (g->n_y - 1) * pix;
-    const int o0 = (int)rint(tc * y0 / pix), o1 = (int)rint(tc * y1 / pix);
-    const int lo = o0 < o1 ? o0 : o1, hi = o0 < o1 ? o1 : o0;
-    const int sp = g->n_z + (hi - lo);
-    if (sp > span) span = sp;
-  }
   p.ntz = (span + p.TZ - 1) / p.TZ;
   p.nbins = p.ntb * p.nty * p.ntz;
   // events per workgroup item: enough items to fill the chip, at most 128 batches (the region's
@@ -277,8 +280,13 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   p.tiled = 1;
 }
 
-void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik,
-                     std::vector<PlanCand>* out) {
+// Every plan that fits (want = 0) in the order of the enumeration, the one of that code, or the cheapest (the
+// first of equals).  Calls of small
+// event lists are bound by this on the host: what does not depend on the innermost loops is formed once, and a
+// plan is chosen without sorting them (a call's plan: 88 -> 17 us for 61 x 77 pixels).
+constexpr int32_t kCheapest = -1;
+static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik, int32_t want,
+                            std::vector<PlanCand>* out) {
   out->clear();
   const bool allow_acc32 = !loglik;
   msz *= 1.0 + g->sigma_z_edge;  // the largest ellipse: sigma_z at the strip ends
@@ -305,6 +313,12 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
     return;
   }
   const int HY = (int)ceil(hy_px + 0.5) + 1;
+  if (want == 0) out->reserve(256);
+  int span[kPlanDtCount] = {};  // 0: not formed yet
+  double by_simd[9], by_waves[5];  // factors of the cost of ring plans
+  for (int k = 1; k <= 8; ++k) by_simd[k] = pow(4.0 / (double)k, 0.62);
+  for (int k = 1; k <= 4; ++k) by_waves[k] = pow(k / 2.0, 0.25);
+  const int ring[2] = {0, ring_shape(hy_px, 0.5 * chord_px)};
   // Candidate regions: workgroups of 8 or 16 wavefronts, 1 to 4 of them resident per CU (their
   // LDS regions share the CU's 160 KB with the static batch buffers), 64-bit or 32-bit
   // accumulators (12 or 8 bytes per region pixel); for each, no shear or t bins of a given width,
@@ -355,7 +369,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
         const double occ_factor = pow(4.0 / (double)occ, 0.58) * (waves == 16 ? 1.1 : 1.0) * (segs > 1 ? 1.3 : 1.0);
         for (int acc32 = 0; acc32 <= 1; ++acc32) {
           if (acc32 && !allow_acc32) continue;
-          const int shape = (acc32 != 0) != loglik && segs == 1 ? ring_shape(hy_px, 0.5 * chord_px) : 0;
+          const int shape = ring[(acc32 != 0) != loglik && segs == 1];
           for (int dti = 0; dti < kPlanDtCount; ++dti) {
             const double dt = kPlanDt[dti];
             // largest |t - t_c| / c inside a bin (no shear: |t| / c <= sin(atan(tmax)))
@@ -364,6 +378,7 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
             const int HZ = (int)ceil(hz / pix + 1.0) + 1;
             for (int ti = 0; ti < kPlanTileCount; ++ti) {
               const int T = kPlanTile[ti];
+              if (want > 0 && plan_code(waves, acc32, wgs, dti, ti, cache) != want) continue;
               // LDS: float image, then the accumulators, column-major with the row pitch rounded
               // up to the bank alignment; masked reads up to maxlen columns past the image must stay
               // in the accumulator array (W columns of 4 or 8 bytes)
@@ -413,22 +428,24 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
                 p.dt = dt;
                 p.tmin = -0.5 * dt * p.ntb;
               }
-              finish_plan(g, rows_max, pairs_per_event, n, p);
+              if (span[dti] == 0) span[dti] = sheared_span(g, p);
+              finish_plan(g, rows_max, pairs_per_event, n, span[dti], p);
               // (some: the bins an object fills; rests: those that make an item of fewer events)
               const double some = (p.rings ? 0.6 : 0.35) * (double)p.nbins, rests = some * (1.0 - exp(-nn / some));
-              double cost;
+              double cost = 10.0 * (double)p.nbins;  // (the preparation's kernels over the bins, over ten passes)
               if (p.rings) {
-                const double unit = 0.5 * pow(4.0 / (double)simd, 0.62) * pow(p.waves / 8.0, 0.25);
+                const double unit = 0.5 * by_simd[simd] * by_waves[p.waves / 4];
                 const double items = std::max(nn / p.ev_per_wg + 0.56 * rests, rests);
                 const double resident = std::min(256.0 * 4.0 * simd / p.waves, items);
                 const double last = std::min(nn, (double)p.ev_per_wg) * std::min(1.0, resident / rests);
-                cost = (nn + 0.26 * resident * last) * pairs_per_event * unit +
-                       (loglik ? 3.1 : 1.35) * items * (double)RY * (double)W;
+                cost += (nn + 0.26 * resident * last) * pairs_per_event * unit +
+                        (loglik ? 3.1 : 1.35) * items * (double)RY * (double)W;
               } else {
-                cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
-                       4.5 * (nn / p.ev_per_wg + rests) * (double)RY * (double)W;
+                cost += nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
+                        4.5 * (nn / p.ev_per_wg + rests) * (double)RY * (double)W;
               }
-              out->push_back({p, cost});
+              if (want != kCheapest || out->empty()) out->push_back({p, cost});
+              else if (cost < out->front().cost) out->front() = {p, cost};
             }
           }
         }
@@ -439,13 +456,24 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
     out->push_back({none, 0.0});
     return;
   }
-  std::stable_sort(out->begin(), out->end(), [](const PlanCand& a, const PlanCand& b) { return a.cost < b.cost; });
+}
+
+void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik,
+                     std::vector<PlanCand>* out) {
+  std::vector<PlanCand> all;
+  enumerate_plans(g, msz, mdl, n, loglik, 0, &all);
+  std::vector<int> order(all.size());
+  for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return all[a].cost < all[b].cost; });
+  out->clear();
+  out->reserve(all.size());
+  for (int k : order) out->push_back(all[k]);
 }
 
 Plan make_plan(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik) {
-  std::vector<PlanCand> c;
-  plan_candidates(g, msz, mdl, n, loglik, &c);
   const int32_t want = g->plan;
+  std::vector<PlanCand> c;
+  if (want != kPlanGeneric) enumerate_plans(g, msz, mdl, n, loglik, want == 0 ? kCheapest : want, &c);
   if (want == 0) return c[0].p;
   if (want == kPlanGeneric) {
     Plan p;
@@ -458,7 +486,8 @@ Plan make_plan(const jpet_geometry* g, double msz, double mdl, int64_t n, bool l
   }
   for (const PlanCand& x : c)
     if (x.p.code == want) return x.p;
-  Plan bad = c[0].p;
+  Plan bad;
+  memset(&bad, 0, sizeof(bad));
   bad.invalid = 1;
   bad.code = want;
   return bad;
