@@ -224,9 +224,32 @@ static int sheared_span(const jpet_geometry* g, const Plan& p) {
   return span;
 }
 
+// Events per workgroup item on batches of rows of epb events: enough items to fill the chip, at most 128
+// batches (the region's staging and flush are amortised over the item); with 32-bit accumulators at most
+// 511 events.
+static int row_item_events(int64_t n, int epb, int acc32) {
+  int64_t per = std::min<int64_t>(std::max<int64_t>(n / 1024, epb), 128 * epb);
+  if (acc32) per = std::min<int64_t>(per, 511);
+  return (int)(per / epb * epb);
+}
+
+// 32-bit accumulators hold 2^-s units: one event adds at most 2^s to a pixel, so an item of up to 2^(32-s) - 1
+// events cannot overflow before the flush.  Items of at most 511 events keep s = 23 (a rounding step of 2^-23
+// of a count per pair).
+static int unit_shift(int events) {
+  int bits = 0;
+  while ((1 << bits) <= events) ++bits;  // events < 2^bits
+  return 32 - bits;
+}
+
+// The unit of a plan's accumulators, as the power of two it divides a count by.
+static int plan_unit(const Plan& p) { return p.tiled && p.acc32 ? p.acc_shift : 32; }
+
 // Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set; span: its
 // sheared_span.
-static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, int span, Plan& p) {
+// row_item: row_item_events of the same code on batches of rows.
+static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, int span,
+                        int row_item, Plan& p) {
   if (p.rings) {
     p.ev_per_batch = p.solo ? 1 : 2;
     const RingLds lds = ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, p.loglik != 0);
@@ -245,32 +268,22 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   p.nty = (g->n_y + p.TY - 1) / p.TY;
   p.ntz = (span + p.TZ - 1) / p.TZ;
   p.nbins = p.ntb * p.nty * p.ntz;
-  // events per workgroup item: enough items to fill the chip, at most 128 batches (the region's
-  // staging and flush are amortised over the item)
-  int64_t per = n / 1024;
-  // ring blocks: where a workgroup's share of the events is worth less than staging and flushing the
-  // region, fewer and larger items
-  if (p.rings && (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W) per = n / 512;
   if (p.rings) {
-    // a block for every wavefront, two where that leaves an item for every CU.  (Below some 16,000 events the
-    // region's staging and flush are most of an item: 400^2, five iterations of 3,000 events 417 -> 184 us, of
-    // 20,000 390 -> 330, against items of n / 1024 events.)
+    // ring blocks: where a workgroup's share of the events is worth less than staging and flushing the region,
+    // fewer and larger items; a block for every wavefront, two where that leaves an item for every CU.
     const int64_t round = (int64_t)p.ev_per_batch * p.waves;
-    per = std::max(per, std::max(round, std::min(2 * round, n / 256)));
+    int64_t per = (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W ? n / 512 : n / 1024;
+    per = std::min<int64_t>(std::max(per, std::max(round, std::min(2 * round, n / 256))), kRingItem);
+    // Never more events than the accumulators' units on batches of rows allow: larger items would hold the
+    // image in coarser units, and a pixel that little reaches (a column beside the strips' ends) shows their
+    // rounding, ten iterations of it amplified (10 iterations of 264,253 events on 256^2: relative L2 to exact
+    // sums 3.3e-6 in units of 2^-24, 8.2e-6 in 2^-23).
+    if (p.acc32) per = std::min<int64_t>(per, ((int64_t)1 << (32 - unit_shift(row_item))) - 1);
+    p.ev_per_wg = (int)(per / p.ev_per_batch * p.ev_per_batch);
+  } else {
+    p.ev_per_wg = row_item;
   }
-  if (per < p.ev_per_batch) per = p.ev_per_batch;
-  const int64_t most = p.rings ? kRingItem : 128 * p.ev_per_batch;
-  if (per > most) per = most;
-  // 32-bit accumulators hold 2^-s units: one event adds at most 2^s to a pixel, so an item of up
-  // to 2^(32-s) - 1 events cannot overflow before the flush.  Items of at most 511 events keep
-  // s = 23 (a rounding step of 2^-23 of a count per pair).
-  if (p.acc32 && per > 511) per = 511;
-  p.ev_per_wg = (int)((per / p.ev_per_batch) * p.ev_per_batch);
-  if (p.acc32) {
-    int bits = 0;
-    while ((1 << bits) <= p.ev_per_wg) ++bits;  // ev_per_wg < 2^bits
-    p.acc_shift = 32 - bits;
-  }
+  if (p.acc32) p.acc_shift = unit_shift(p.ev_per_wg);
   const int64_t nonempty = n < p.nbins ? n : p.nbins;
   p.max_items = (n + p.ev_per_wg - 1) / p.ev_per_wg + nonempty;
   if (p.max_items < 1) p.max_items = 1;
@@ -284,6 +297,11 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
 // first of equals).  Calls of small
 // event lists are bound by this on the host: what does not depend on the innermost loops is formed once, and a
 // plan is chosen without sorting them (a call's plan: 88 -> 17 us for 61 x 77 pixels).
+//
+// The accumulators' units are part of the result, so the choice of a plan for its speed may not coarsen them:
+// a plan is the cheapest of those whose units are at least as fine as those of the cheapest plan on batches of
+// rows by that layout's own figure (row_unit; batch_unit: with 32-bit accumulators, which a batch takes).
+// The others follow in the list, their figures times 2^64 for each of the two that they miss.
 constexpr int32_t kCheapest = -1;
 static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik, int32_t want,
                             std::vector<PlanCand>* out) {
@@ -319,6 +337,11 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
   for (int k = 1; k <= 8; ++k) by_simd[k] = pow(4.0 / (double)k, 0.62);
   for (int k = 1; k <= 4; ++k) by_waves[k] = pow(k / 2.0, 0.25);
   const int ring[2] = {0, ring_shape(hy_px, 0.5 * chord_px)};
+  int row_unit = 0, batch_unit = 0;
+  double row_best = HUGE_VAL, batch_best = HUGE_VAL;  // figures of the plans that gave them
+  PlanCand best[33];                                  // kCheapest: the cheapest plan of each unit
+  int at[33], seen = 0;                               // and its place in the enumeration
+  for (PlanCand& c : best) c.cost = HUGE_VAL;
   // Candidate regions: workgroups of 8 or 16 wavefronts, 1 to 4 of them resident per CU (their
   // LDS regions share the CU's 160 KB with the static batch buffers), 64-bit or 32-bit
   // accumulators (12 or 8 bytes per region pixel); for each, no shear or t bins of a given width,
@@ -384,8 +407,8 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
               // in the accumulator array (W columns of 4 or 8 bytes)
               const int RY = T + 2 * HY, W = T + 2 * HZ;
               const int pitch = (RY + kBankAlign - 1) / kBankAlign * kBankAlign;
-              const size_t bytes = tiled_lds_layout(pitch, W, RY, acc32, events_per_batch(waves, rows_max * segs),
-                                                    loglik, nullptr, nullptr);
+              const int epb = events_per_batch(waves, rows_max * segs);
+              const size_t bytes = tiled_lds_layout(pitch, W, RY, acc32, epb, loglik, nullptr, nullptr);
               const int reach = acc32 ? W : 2 * W;
               // thread words address columns with 8 bits and rows with 9 bits
               if (bytes > budget || reach < maxlen || W > 256 || RY > 512) continue;
@@ -429,7 +452,15 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 p.tmin = -0.5 * dt * p.ntb;
               }
               if (span[dti] == 0) span[dti] = sheared_span(g, p);
-              finish_plan(g, rows_max, pairs_per_event, n, span[dti], p);
+              const int row_item = row_item_events(n, epb, acc32);
+              finish_plan(g, rows_max, pairs_per_event, n, span[dti], row_item, p);
+              if (!loglik) {  // as the layout on batches of rows is priced: 1.6 x region pixels x items, all bins filled
+                const double row_cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
+                                        1.6 * (nn / row_item + std::min(nn, (double)p.nbins)) * (double)pitch * (double)W;
+                const int unit = acc32 ? unit_shift(row_item) : 32;
+                if (row_cost < row_best) row_best = row_cost, row_unit = unit;
+                if (acc32 && row_cost < batch_best) batch_best = row_cost, batch_unit = unit;
+              }
               // (some: the bins an object fills; rests: those that make an item of fewer events)
               const double some = (p.rings ? 0.6 : 0.35) * (double)p.nbins, rests = some * (1.0 - exp(-nn / some));
               double cost = 10.0 * (double)p.nbins;  // (the preparation's kernels over the bins, over ten passes)
@@ -444,18 +475,30 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 cost += nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
                         4.5 * (nn / p.ev_per_wg + rests) * (double)RY * (double)W;
               }
-              if (want != kCheapest || out->empty()) out->push_back({p, cost});
-              else if (cost < out->front().cost) out->front() = {p, cost};
+              ++seen;
+              if (want != kCheapest) out->push_back({p, cost});
+              else if (cost < best[plan_unit(p)].cost) best[plan_unit(p)] = {p, cost}, at[plan_unit(p)] = seen;
             }
           }
         }
       }
     }
   }
-  if (out->empty()) {
-    out->push_back({none, 0.0});
-    return;
+  auto figure = [&](int unit, double cost) {
+    return ldexp(cost, 64 * ((unit < row_unit ? 1 : 0) + (unit < batch_unit ? 1 : 0)));
+  };
+  if (want == kCheapest) {
+    int first = -1;
+    for (int unit = 0; unit <= 32; ++unit) {
+      const double cost = best[unit].cost = figure(unit, best[unit].cost);
+      if (!(cost < HUGE_VAL)) continue;
+      if (first < 0 || cost < best[first].cost || (cost == best[first].cost && at[unit] < at[first])) first = unit;
+    }
+    if (first >= 0) out->push_back(best[first]);
+  } else {
+    for (PlanCand& c : *out) c.cost = figure(plan_unit(c.p), c.cost);
   }
+  if (out->empty()) out->push_back({none, 0.0});
 }
 
 void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik,
