@@ -571,9 +571,9 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
 
 // Layout of a batched workspace: the instance table, then one ordinary workspace per instance.
 // Every instance that fits the binned pass takes the plan its geometry names or the cost model's
-// cheapest plan with 32-bit accumulators.  Instances whose plans share the register cache, the
-// wavefronts per workgroup, the workgroups resident per CU and the region's row pitch (64, 128,
-// 256 or any other) form a class, served by one batched launch per iteration with the class's
+// cheapest plan with 32-bit accumulators.  Instances whose plans share the kernel (pass_kernel), the
+// wavefronts per workgroup, the workgroups resident per CU and the region's row pitch (batched_pitch)
+// form a class, served by one batched launch per iteration with the class's
 // largest LDS region; a batch of like instances is one class.  Within a class the table lists the instances heaviest workgroup
 // item first, so that the longest items are pulled earliest.  Instances that fit only the generic
 // pass follow the classes, with their own launches.
@@ -637,7 +637,7 @@ BatchLayout batch_layout(const jpet_instance* inst, int count) {
     }
     L.plan[k] = p;
     if (p.tiled) {
-      key[k] = ((batched_pitch_class(p.pitch) * 2048 + pass_kernel(p)) * 32 + p.waves) * 8 + p.wgs;
+      key[k] = ((batched_pitch(p) * 2048 + pass_kernel(p)) * 32 + p.waves) * 8 + p.wgs;
       // pixels of a typical ellipse (App. B half sizes at theta = 0) times events per workgroup
       work[k] = (1.5 * g.sigma_dl / g.pixel) * (3.0 * g.sigma_z / sqrt(2.0) / g.pixel) * p.ev_per_wg;
     }
@@ -659,7 +659,7 @@ BatchLayout batch_layout(const jpet_instance* inst, int count) {
       c.first = t;
       c.waves = p.waves;
       c.wgs = p.wgs;
-      c.pitch = batched_pitch_class(p.pitch);
+      c.pitch = batched_pitch(p);
       L.cls.push_back(c);
     }
     BatchClass& c = L.cls.back();

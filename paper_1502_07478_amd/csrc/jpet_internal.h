@@ -374,16 +374,17 @@ hipError_t launch_update(const Geo& g, const float* s, float* rho, const Workspa
 hipError_t launch_write_insts(const InstWrite& w, BatchInst* table, hipStream_t st);
 hipError_t launch_batched_reset(const BatchInst* table, int count, hipStream_t st);
 // the batched pass over one class of a batch (table: the class's entries): 32-bit accumulators,
-// register cache maxlen (16, 32, 48 or 64), waves (8 or 16) wavefronts per workgroup, region row pitch
-// (64, 128, 192, 256, or 0 for any other), one workgroup per item of the class (items in total)
-hipError_t launch_event_pass_batched(const BatchInst* table, int count, int maxlen, int waves, int pitch,
+// kernel (see pass_kernel), waves wavefronts per workgroup, region row pitch (batched_pitch), one workgroup
+// per item of the class (items in total)
+hipError_t launch_event_pass_batched(const BatchInst* table, int count, int kernel, int waves, int pitch,
                                      size_t lds_bytes, int64_t items, hipStream_t st);
-// the pitch a batched class is compiled for: 64, 128, 192 or 256, else 0 (a runtime value)
-inline int batched_pitch_class(int pitch) {
-  return pitch == 64 || pitch == 128 || pitch == 192 || pitch == 256 ? pitch : 0;
+// the pitch a batched class is compiled for: on ring blocks the plan's own; on batches of rows 64, 128, 192 or
+// 256, else 0 (a runtime value)
+inline int batched_pitch(const Plan& p) {
+  return p.rings || p.pitch == 64 || p.pitch == 128 || p.pitch == 192 || p.pitch == 256 ? p.pitch : 0;
 }
 // raises a batched pass's dynamic LDS limit (call before launching or capturing it)
-hipError_t set_batched_lds(int maxlen, int waves, int pitch, size_t lds_bytes);
+hipError_t set_batched_lds(int kernel, int waves, int pitch, size_t lds_bytes);
 hipError_t launch_update_batched(const BatchInst* table, int count, int64_t max_npix, hipStream_t st);
 // value_only: l alone (out3[1], out3[2] are NaN, grad_rho must be null)
 hipError_t launch_loglik(const Geo& g, const Plan& p, int64_t n, const Workspace& ws, const float* rho,

@@ -199,17 +199,18 @@ hipError_t launch_batched_reset(const BatchInst* table, int count, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_event_pass_batched(const BatchInst* table, int count, int maxlen, int waves, int pitch,
+hipError_t launch_event_pass_batched(const BatchInst* table, int count, int kernel, int waves, int pitch,
                                      size_t lds_bytes, int64_t items, hipStream_t st) {
   if (count <= 0 || items <= 0) return hipSuccess;
   if (items > 0x7fffffffll) return hipErrorInvalidValue;
-  return by_kernel(maxlen, [&](auto b) { return b.batched(table, count, waves, pitch, (unsigned)items, lds_bytes, st); });
+  return by_kernel(kernel, [&](auto b) { return b.batched(table, count, waves, pitch, (unsigned)items, lds_bytes, st); });
 }
 
-hipError_t set_batched_lds(int maxlen, int waves, int pitch, size_t lds_bytes) {
-  return by_kernel(maxlen, [&](auto b) {
-    return hipFuncSetAttribute(b.batched_kernel(waves, pitch), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds_bytes);
+hipError_t set_batched_lds(int kernel, int waves, int pitch, size_t lds_bytes) {
+  return by_kernel(kernel, [&](auto b) {
+    const void* f = b.batched_kernel(waves, pitch);
+    if (!f) return hipErrorInvalidValue;  // not compiled for this pitch
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   });
 }
 

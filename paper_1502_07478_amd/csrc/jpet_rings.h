@@ -446,8 +446,9 @@ hipError_t Rings<SHAPE>::batched(const BatchInst* table, int count, int waves, i
 
 template <int SHAPE>
 const void* Rings<SHAPE>::batched_kernel(int, int pitch) {
-  return pitch == shape_pitch(SHAPE, 0) ? (const void*)k_event_pass_rings_batched<SHAPE, shape_pitch(SHAPE, 0)>
-                                        : (const void*)k_event_pass_rings_batched<SHAPE, shape_pitch(SHAPE, 1)>;
+  return pitch == shape_pitch(SHAPE, 0)   ? (const void*)k_event_pass_rings_batched<SHAPE, shape_pitch(SHAPE, 0)>
+         : pitch == shape_pitch(SHAPE, 1) ? (const void*)k_event_pass_rings_batched<SHAPE, shape_pitch(SHAPE, 1)>
+                                          : nullptr;
 }
 
 }  // namespace jpet

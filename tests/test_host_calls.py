@@ -1,0 +1,117 @@
+"""What the library's calls ask of the HIP runtime, on a runtime that runs nothing (tests/host/calls.cpp; no GPU):
+the kernels launched, their limits of dynamic LDS, streams, events and captures."""
+
+import math
+import os
+import subprocess
+
+import pytest
+
+from paper_1502_07478_amd import jpet
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PIXEL = 2.0
+# the register caches of the passes on ring blocks: 1000 (one event per wavefront) + 100 rings + pixels of a row
+SHAPES = [108, 112, 116, 124, 210, 214, 218, 222, 228, 314, 318, 322, 326, 1132, 1148, 1164, 1216, 1222, 1228, 1236,
+          1248, 1264, 1318, 1324, 1332, 1344, 1354, 1364, 1420, 1428, 1440, 1454]
+# ellipses of these sizes leave the regions of the log-likelihood (doubles) no room in LDS: the pass without binning
+LOGLIK_GENERIC = (1264, 1344, 1354, 1364, 1440, 1454)
+
+
+def resolution(shape, half_rows=None):
+    """sigma_z and sigma_dl whose largest ellipse just fits a shape (122.4 rows: a region of 256 rows)."""
+    if half_rows is None:
+        half_rows = min((32 if shape >= 1000 else 16) * (shape % 1000 // 100) - 0.6, 122.4)
+    return (shape % 100 - 0.5) * PIXEL * math.sqrt(2.0) / 6.0, half_rows * PIXEL / 1.5
+
+
+@pytest.fixture(scope="module")
+def calls(tmp_path_factory):
+    lib = jpet.LIB_PATH
+    if not os.path.exists(lib):
+        from paper_1502_07478_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("host") / "calls")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(rocm, "include"), os.path.join(ROOT, "tests", "host", "calls.cpp"), "-rdynamic",
+                    lib, f"-Wl,-rpath,{os.path.dirname(lib)}", f"-Wl,-rpath-link,{rocm}/lib", "-o", exe], check=True)
+
+    def run(call, *geometries):
+        """The log of a call: geometries are (sigma_z, sigma_dl, pixel, n_y, n_z, n, plan[, R, L])."""
+        args = [call]
+        for k, (sz, sdl, pixel, n_y, n_z, n, plan, *strips) in enumerate(geometries):
+            R, L = strips or (450.0, 500.0)
+            args += ([";"] if k else []) + [repr(float(v)) for v in (R, L, sz, sdl, pixel)] + [str(v) for v in (n_y, n_z, n, plan)]
+        res = subprocess.run([exe, *args], capture_output=True, text=True, timeout=60)
+        assert res.returncode == 0, (res.returncode, res.stderr)
+        return [line.split() for line in res.stdout.splitlines()]
+    return run
+
+
+def codes(log):
+    return {line[1]: int(line[2]) for line in log if line[0] == "rc"}
+
+
+def launches(log, name):
+    """(kernel with its arguments, line) of every launch of a kernel by its name without arguments."""
+    return [(line[1], line) for line in log if line[0] == "launch" and line[1].split("<")[0] == name]
+
+
+def limits_hold(log):
+    """Every launch has a raised limit where it needs one, of at least its dynamic LDS."""
+    limit = {}
+    for line in log:
+        if line[0] == "limit":
+            limit[line[1]] = int(line[3])
+        elif line[0] == "launch":
+            lds = int(line[line.index("lds") + 1])
+            assert lds <= limit.get(line[1], 64 * 1024), line
+            assert int(line[line.index("block") + 1]) <= 1024
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_shapes_reach_their_kernels(calls, shape):
+    """An ellipse that just fits a register cache launches the kernels compiled for it: alone and in a batch, the
+    pass and the forward sums, the log-likelihood and its value."""
+    sz, sdl = resolution(shape)
+    n = 257
+    g = jpet.geometry(R=450.0, L=500.0, sigma_z=sz, sigma_dl=sdl, pixel=PIXEL, n_y=101, n_z=83)
+    plan = next(c for c, _ in jpet.plan_candidates(g, n) if c & 4 and c >> 12 == 0)
+    geo = (sz, sdl, PIXEL, 101, 83, n, plan)
+    for call, kernel, rest in (("iterate", "k_event_pass_rings", ",false"), ("denominators", "k_event_pass_rings", ",true"),
+                               ("batch", "k_event_pass_rings_batched", "")):
+        log = calls(call, geo)
+        assert set(codes(log).values()) == {0}, log
+        limits_hold(log)
+        found = [name for name, _ in launches(log, kernel)]
+        assert found, log
+        for name in found:
+            args = name[name.index("<") + 1:-1].split(",", 2)
+            assert int(args[0]) == shape and "," + args[2] == rest if rest else len(args) == 2 and int(args[0]) == shape, name
+    geo = geo[:-1] + (0,)
+    log = calls("loglik", geo)
+    limits_hold(log)
+    assert codes(log)["loglik"] == 0
+    if shape in LOGLIK_GENERIC:
+        assert launches(log, "k_loglik_pass")
+        return
+    assert launches(log, "k_loglik_rings")[0][0].startswith(f"k_loglik_rings<{shape},")
+    log = calls("value", geo)
+    limits_hold(log)
+    rings, solo = shape % 1000 // 100, "true" if shape >= 1000 else "false"
+    assert codes(log)["loglik"] == 0 and launches(log, "k_loglik_rings_value")[0][0] == f"k_loglik_rings_value<{rings},{solo}>"
+
+
+@pytest.mark.parametrize("half_rows", [95.6, 96.0, 103.0, 111.0, 118.0, 122.0, 123.0, 126.0, 126.9])
+@pytest.mark.parametrize("length", [8, 20, 28])
+def test_batches_of_tall_ellipses(calls, half_rows, length):
+    """Regions of more than 256 rows (a pitch of 320) run in a batch as they do alone."""
+    sz, sdl = resolution(1400 + length, half_rows)
+    geo = (sz, sdl, PIXEL, 300, 300, 50_000, 0)
+    alone, log, graph = calls("iterate", geo), calls("batch", geo), calls("graph", geo)
+    for got in (alone, log, graph):
+        assert set(codes(got).values()) == {0}, codes(got)
+        limits_hold(got)
+    kernels = {name for name, line in launches(log, "k_event_pass_rings_batched")}
+    assert len(kernels) == 1 and kernels == {name for name, line in launches(graph, "k_event_pass_rings_batched")}
