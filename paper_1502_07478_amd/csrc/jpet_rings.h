@@ -243,7 +243,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
           if (k >= 0 && k < g.n_z) v = rho[(int64_t)r * g.n_z + k];
         }
         odd |= v != 0.0f && !(v >= __builtin_ldexpf(1.0f, -66) && v < 16777216.0f);
-        rho_s[q] = v * scale;
+        rho_s[q] = fmaf(v, scale, 0.0f);  // (and -0 as 0: its bits would be 2^31 units)
         if constexpr (!FORWARD) acc_s[q] = 0u;
       }
     }
