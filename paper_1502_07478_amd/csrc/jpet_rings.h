@@ -44,13 +44,16 @@ struct RingShared {
   unsigned zero, bad, odd;
 };
 
-// Accumulator units without a conversion.  A single-precision number below 2^-124 is, bit for bit, the
+// Accumulator units without a conversion.  A single-precision number up to 2^-125 is, bit for bit, the
 // count of its 2^-149: with the image scaled by 2^-kBitsScale and the unit by 2^-149 on top, the product of
-// pass 2 is the addend itself, rounded to nearest.  Scaled so, no intermediate of an item whose image lies in
-// [2^-66, 2^24) (or is 0) leaves the normal range: P rho >= 2^-13 2^-66 2^-44, unit F / D >= 2^-126.  Other
+// pass 2 is the addend itself (at most 2^24 units), rounded to nearest.  Scaled so, the pixels' exp2(E) rho of an
+// item whose image lies in [2^-66, 2^24) (or is 0) stay in the normal range: at least 2^-13 2^-66 2^-44.  The
+// denominators need not: they carry kappa^-1/2, about sigma_z / (R sqrt 2).  Blocks with one below kBitsTiny,
+// where 1 / D would leave the range, go pixel by pixel, with the image scaled up again.  Other
 // images, and items of units finer than 2^-24 (fewer than 128 events), convert.  Ten iterations of 10M events on
 // 400^2: 58.8 -> 57.7 ms, on 64 x 76: 21.9 -> 21.0.
 constexpr int kBitsScale = 44, kBitsShift = 24;
+constexpr float kBitsTiny = 0x1p-120f;
 
 // Pass 1 along a lane's row of one ring (see pass1_poly in jpet_binned.h): chunks below the
 // wavefront's shortest row without masks, the others with the reads past the row's ends discarded
@@ -253,7 +256,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     bits = false;                      // once more, as it is
   }
   const float kUnit = uniform_f(__builtin_ldexpf(1.0f, bits ? p.acc_shift - 149 : p.acc_shift));
-  const float tiny = uniform_f(bits ? 0.0f : 1e-28f);
+  const float tiny = uniform_f(bits ? kBitsTiny : 1e-28f);
 
   int buf = 0;
   for (int q = wave; q < nblk; q += waves, buf ^= 1) {
@@ -269,10 +272,10 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     if (q + waves < nblk) fetch(q + waves, buf ^ 1);
 
     // an event's denominator (on one of its lanes)
-    auto denominator = [&](float D) {
+    auto denominator = [&](double D) {
       if (c.index < 0) return;  // no event
-      if (!(D > 0.0f)) atomicAdd(&ps.zero, 1u);
-      if constexpr (FORWARD) D_out[c.index] = (float)((double)D * g.cnorm * (bits ? __builtin_ldexp(1.0, kBitsScale) : 1.0));
+      if (!(D > 0.0)) atomicAdd(&ps.zero, 1u);
+      if constexpr (FORWARD) D_out[c.index] = (float)(D * g.cnorm * (bits ? __builtin_ldexp(1.0, kBitsScale) : 1.0));
     };
     auto tail = [&](int k) { return ((k < 2 ? t01 : t23) >> (16 * (k & 1))) & 0xffffu; };
     auto row = [&](int k, int H) { return ring_row(w[k >> 1] >> (16 * (k & 1)), c.mid + lrow + k * lstep, H); };
@@ -333,25 +336,27 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
       }
     }
 
-    // pixel by pixel, evaluated in both passes; P rho scaled by 2^64 against overflow of unit / D.
+    // pixel by pixel, evaluated in both passes; P rho scaled by 2^64 against overflow of unit / D, and in D too
+    // where the image is scaled down.
     // (Rolled, and with the constants read again: shared with the way above they would take 26 vector
     // registers through it.)
     asm volatile("" ::: "memory");
     float D = 0.0f;
     int nbad = 0, again = 0;
     const int first = opaque(0);
+    const float up = bits ? 18446744073709551616.0f : 1.0f;
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
       const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
       for (int j = -r.nl; j < r.nr; ++j)
-        D = fmaf(exact_at(rk, (float)j + 0.5f, &nbad), rho_s[(r.kc + j) * pitch + r.rl], D);
+        D = fmaf(exact_at(rk, (float)j + 0.5f, &nbad), rho_s[(r.kc + j) * pitch + r.rl] * up, D);
     }
     if (nbad) atomicAdd(&ps.bad, (unsigned)nbad);
     float Dlo, Dhi;
-    const float De = event_sum(D, Dlo, Dhi);
+    const double De = (double)event_sum(D, Dlo, Dhi) / up;
     if (l == 0) denominator(De);
-    if (FORWARD || !(De > 0.0f)) continue;
-    const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / ((double)De * 18446744073709551616.0));
+    if (FORWARD || !(De > 0.0)) continue;
+    const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / (De * 18446744073709551616.0));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
       const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);

@@ -39,6 +39,18 @@ def step(kw, ev_np, rho_np, want, sto, plan=0):
     assert err <= tol, (err, tol)
 
 
+def ring_plan(kw, events=2, pitch=None):
+    """The cost model's first plan on ring blocks of that many events, items of 128 events and more."""
+    g = jpet.geometry(**kw)
+    for code, _ in jpet.plan_candidates(g, N):
+        i = jpet.launch_info(jpet.with_plan(g, code), N)
+        rows = i["tile_rows"] + 2 * i["halo_rows"]
+        if (i["accumulator_bits"] == 32 and i["row_segments"] == 1 and i["events_per_batch"] == events and
+                i["events_per_workgroup"] >= 128 and (pitch is None or (rows + 63) // 64 * 64 == pitch)):
+            return code
+    return None
+
+
 def test_negative_zeros():
     """-0 is a pixel without activity."""
     sz, sdl = 11.5 * PIXEL * math.sqrt(2.0) / 6.0, 15.4 * PIXEL / 1.5
@@ -49,3 +61,36 @@ def test_negative_zeros():
     want, sto = oracle.mlem(oracle.geometry(**kw), ev, rho.astype(np.float64), 1)
     rho[40:60:3] = -0.0
     step(kw, ev, rho, want, sto)
+
+
+def test_denominators_below_the_bits_range():
+    """An image just above 2^-66 and a sharp, far detector: P is 2^-14 to 2^-20, and with the image scaled down by
+    2^-44 the denominators lie below 2^-120, down to where their reciprocals overflow.  Such blocks go pixel by
+    pixel; the step is that of the same image times 2^65, whose blocks do not.
+
+    Tolerances: both take the same row constants, so an event's denominators differ by the roundings of two
+    evaluations of the exponent, at most 13 in magnitude, three roundings of 2^-24 each: 5e-6.  The images differ by
+    2e-6 and the roundings to units of both."""
+    kw = dict(R=2000.0, L=500.0, sigma_z=0.25, sigma_dl=1.0, pixel=PIXEL, n_y=61, n_z=53)
+    ev_np = simulate_events(c1_phantom(), kw["R"], kw["L"], kw["sigma_z"], kw["sigma_dl"], N, 3, workers=4)
+    g = jpet.geometry(**kw, plan=ring_plan(kw))
+    info = jpet.launch_info(g, N)
+    assert 0 < info["accumulator_shift"] <= 24
+    ev = torch.from_numpy(ev_np).to(DEV)
+    rho = torch.linspace(0.6, 1.9, 61 * 53, device=DEV).reshape(61, 53)
+    D = jpet.denominators(g, ev, rho).double().cpu().numpy()
+    live = D > 0
+    cnorm = 1.0 / (kw["sigma_z"] ** 2 * kw["sigma_dl"] * 2.0 * math.pi)
+    scaled = D[live] / cnorm * 2.0 ** -(65 + 44)
+    assert scaled.max() < 2.0 ** -120 and scaled.min() < 2.0 ** -126
+    small = jpet.denominators(g, ev, rho * 2.0 ** -65).double().cpu().numpy() * 2.0 ** 65
+    assert np.array_equal(small > 0, live)
+    assert np.max(np.abs(small[live] / D[live] - 1)) <= 5e-6
+    one, other = rho.clone(), rho * 2.0 ** -65
+    st = jpet.mlem_iterate(g, ev, one, 1, want_stats=True)
+    assert jpet.mlem_iterate(g, ev, other, 1, want_stats=True) == st and st["n_zero_denominator"] == 0
+    a, b = other.double().cpu().numpy(), one.double().cpu().numpy()
+    tol = 2e-6 + 2 * 3 * 0.29 * 2.0 ** -info["accumulator_shift"] * math.sqrt(st["n_pairs"]) / np.linalg.norm(b)
+    err = float(np.linalg.norm(a - b) / np.linalg.norm(b))
+    print(f"rel L2 {err:.2e} (tolerance {tol:.2e})", flush=True)
+    assert err <= tol
