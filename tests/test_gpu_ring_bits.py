@@ -51,6 +51,25 @@ def ring_plan(kw, events=2, pitch=None):
     return None
 
 
+# (events per wavefront, pixels of the longest row, half height in rows, row pitch of the region): every number of
+# rings, with the lower and the higher pitch it is compiled for
+ROWS = [(2, 12, 15.4, 64), (2, 12, 15.4, 128), (2, 18, 26.0, 64), (2, 18, 31.4, 128), (2, 22, 47.4, 128), (2, 22, 47.4, 192),
+        (1, 32, 26.0, 64), (1, 32, 31.4, 128), (1, 22, 57.0, 128), (1, 22, 63.4, 192), (1, 24, 89.0, 192), (1, 24, 95.4, 256),
+        (1, 28, 122.4, 256), (1, 28, 126.0, 320)]
+
+
+@pytest.mark.parametrize("events,length,half_rows,pitch", ROWS)
+def test_every_number_of_rings(events, length, half_rows, pitch):
+    sz, sdl = (length - 0.5) * PIXEL * math.sqrt(2.0) / 6.0, half_rows * PIXEL / 1.5
+    kw = dict(R=450.0, L=500.0, sigma_z=sz, sigma_dl=sdl, pixel=PIXEL, n_y=33, n_z=33)
+    plan = ring_plan(kw, events, pitch)
+    assert plan is not None
+    ev = simulate_events(c1_phantom(), 450.0, 500.0, sz, sdl, N, 3, workers=4)
+    rho = np.linspace(0.5, 1.5, 33 * 33, dtype=np.float32).reshape(33, 33)
+    want, sto = oracle.mlem(oracle.geometry(**kw), ev, rho.astype(np.float64), 1)
+    step(kw, ev, rho, want, sto, plan)
+
+
 def test_negative_zeros():
     """-0 is a pixel without activity."""
     sz, sdl = 11.5 * PIXEL * math.sqrt(2.0) / 6.0, 15.4 * PIXEL / 1.5

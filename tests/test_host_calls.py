@@ -115,3 +115,25 @@ def test_batches_of_tall_ellipses(calls, half_rows, length):
         limits_hold(got)
     kernels = {name for name, line in launches(log, "k_event_pass_rings_batched")}
     assert len(kernels) == 1 and kernels == {name for name, line in launches(graph, "k_event_pass_rings_batched")}
+
+
+@pytest.mark.parametrize("shape,half_rows,pitch", [(112, 15.4, 64), (112, 15.4, 128), (218, 26.0, 64), (218, 31.4, 128),
+                                                   (322, 47.4, 128), (322, 47.4, 192), (1132, 26.0, 64), (1132, 31.4, 128),
+                                                   (1222, 57.0, 128), (1222, 63.4, 192), (1324, 89.0, 192), (1324, 95.4, 256),
+                                                   (1428, 122.4, 256), (1428, 126.0, 320)])
+def test_large_items_reach_both_pitches(calls, shape, half_rows, pitch):
+    """The kernels of the plans that the GPU tests of items of 128 events and more name."""
+    sz, sdl = resolution(shape, half_rows)
+    n = 140_000
+    g = jpet.geometry(R=450.0, L=500.0, sigma_z=sz, sigma_dl=sdl, pixel=PIXEL, n_y=33, n_z=33)
+    for plan, _ in jpet.plan_candidates(g, n):
+        i = jpet.launch_info(jpet.with_plan(g, plan), n)
+        rows = i["tile_rows"] + 2 * i["halo_rows"]
+        if (i["accumulator_bits"] == 32 and i["row_segments"] == 1 and i["events_per_batch"] == (1 if shape >= 1000 else 2) and
+                i["events_per_workgroup"] >= 128 and (rows + 63) // 64 * 64 == pitch):
+            break
+    else:
+        pytest.fail("no plan")
+    log = calls("iterate", (sz, sdl, PIXEL, 33, 33, n, plan))
+    limits_hold(log)
+    assert {name for name, _ in launches(log, "k_event_pass_rings")} == {f"k_event_pass_rings<{shape},{pitch},false>"}
