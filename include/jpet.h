@@ -193,10 +193,10 @@ int jpet_mlem_backproject(const jpet_geometry* g, const float* events, int64_t n
 /* The forward sums of the MLEM event pass: runs the pass of jpet_mlem_iterate (same plan and
  * kernel, with the same workspace rules and flags) on the image rho and writes each event's
  * denominator D_j = sum_{i in ellipse} P_ji rho_i (Sec. 4 listing, first loop; the denominator of
- * Eq. 3), P including its constant factor, as that pass forms it (FP32 terms and row sums;
- * plans on batches of rows add the wavefronts' partial sums in double precision), rounded to float.
- * Dropped events get 0.  A back-projection the
- * pass may form with them goes to the workspace's accumulator and is discarded.
+ * Eq. 3), P including its constant factor, as that pass forms it (FP32 terms, summed in FP32 within a
+ * wavefront's rows or a lane's, and those partial sums in double precision), rounded to float.
+ * Dropped events get 0.  A back-projection the pass may form with them goes to the workspace's
+ * accumulator and is discarded.
  *   D_out: device float [n], written entirely.  stats: as for jpet_mlem_iterate. */
 int jpet_mlem_denominators(const jpet_geometry* g, const float* events, int64_t n, const float* rho, float* D_out,
                            void* ws, size_t ws_bytes, uint32_t flags, jpet_stats* stats, void* stream);

@@ -151,23 +151,23 @@ static size_t tiled_lds_layout(int pitch, int W, int RY, int acc32, int epb, boo
   return align_up(off + 4u * (size_t)RY, 16);
 }
 
-// Events per workgroup item of the passes on ring blocks, at most (32-bit accumulators: see finish_plan).
+// Events per workgroup item of the passes on ring blocks, at most.
 constexpr int kRingItem = 510;
 
 // Dynamic LDS of the passes on ring blocks: two buffers of a block's constants per wavefront, the per-row
-// column shifts (log-likelihood: three sums per event of an item), the image and the 32-bit accumulators
+// column shifts (log-likelihood: a double and two floats per event of the item), the image and the 32-bit accumulators
 // (doubles), with the slack columns before the image (the buffers are part of it) and after the
 // accumulators (the log-likelihood pass only reads there).
 struct RingLds {
   int off, sum, img;
   size_t bytes;
 };
-static RingLds ring_lds_layout(int pitch, int W, int RY, int waves, int events, int slack, bool loglik) {
+static RingLds ring_lds_layout(int pitch, int W, int RY, int waves, int events, int slack, int item, bool loglik) {
   const size_t free = (size_t)slack * (size_t)pitch * 4u;
   RingLds L;
   L.off = waves * 2 * ring_tails(events, loglik);
   L.sum = L.off + 4 * RY;
-  L.img = (int)align_up(std::max((size_t)L.sum + (loglik ? 12u * kRingItem : 0u), free), 256);
+  L.img = (int)align_up(std::max((size_t)L.sum + (loglik ? 16u * (unsigned)item : 0u), free), 256);
   L.bytes = (size_t)L.img + (loglik ? 12u : 8u) * (size_t)pitch * (size_t)W + (loglik ? 0u : free);
   return L;
 }
@@ -211,19 +211,6 @@ static int ring_slack(int shape, int HZ, double slope, double hy_px) {
 // take 17 us, above that the larger items leave the last round of workgroups emptier).
 constexpr double kItemPairs = 7000.0;
 
-// Columns of the grid in the sheared frame of a plan's t bins: the widest over them.
-static int sheared_span(const jpet_geometry* g, const Plan& p) {
-  const double pix = g->pixel;
-  const double y0 = (0.5 - 0.5 * (double)g->n_y) * pix, y1 = y0 + (g->n_y - 1) * pix;
-  int span = g->n_z;
-  for (int b = 0; b < p.ntb; ++b) {
-    const double tc = p.ntb > 1 ? p.tmin + (b + 0.5) * p.dt : 0.0;
-    const int o0 = (int)rint(tc * y0 / pix), o1 = (int)rint(tc * y1 / pix);
-    span = std::max(span, g->n_z + std::abs(o1 - o0));
-  }
-  return span;
-}
-
 // Events per workgroup item on batches of rows of epb events: enough items to fill the chip, at most 128
 // batches (the region's staging and flush are amortised over the item); with 32-bit accumulators at most
 // 511 events.
@@ -245,14 +232,42 @@ static int unit_shift(int events) {
 // The unit of a plan's accumulators, as the power of two it divides a count by.
 static int plan_unit(const Plan& p) { return p.tiled && p.acc32 ? p.acc_shift : 32; }
 
+// Events per workgroup item on ring blocks of epb events: where a workgroup's share of the events is worth less
+// than staging and flushing the region, fewer and larger items; a block for every wavefront, two where that
+// leaves an item for every CU.  (Below some 16,000 events the region's staging and flush are most of an item.)
+// With 32-bit accumulators never more events than the units on batches of rows (row_item) allow: larger items
+// would hold the image in coarser units, and a pixel that little reaches (a column beside the strips' ends) shows
+// their rounding, ten iterations of it amplified (10 iterations of 264,253 events on 256^2: relative L2 to exact
+// sums 3.3e-6 in units of 2^-24, 8.2e-6 in 2^-23).
+static int ring_item_events(int64_t n, double pairs_per_event, int RY, int W, int epb, int waves, int row_item, bool acc32) {
+  const int64_t round = (int64_t)epb * waves;
+  int64_t per = (double)n * pairs_per_event < kItemPairs * (double)RY * (double)W ? n / 512 : n / 1024;
+  per = std::min<int64_t>(std::max(per, std::max(round, std::min(2 * round, n / 256))), kRingItem);
+  if (acc32) per = std::min<int64_t>(per, ((int64_t)1 << (32 - unit_shift(row_item))) - 1);
+  return (int)(per / epb * epb);
+}
+
+// Columns of the grid in the sheared frame of a plan's t bins: the widest over them.
+static int sheared_span(const jpet_geometry* g, const Plan& p) {
+  const double pix = g->pixel;
+  const double y0 = (0.5 - 0.5 * (double)g->n_y) * pix, y1 = y0 + (g->n_y - 1) * pix;
+  int span = g->n_z;
+  for (int b = 0; b < p.ntb; ++b) {
+    const double tc = p.ntb > 1 ? p.tmin + (b + 0.5) * p.dt : 0.0;
+    const int o0 = (int)rint(tc * y0 / pix), o1 = (int)rint(tc * y1 / pix);
+    span = std::max(span, g->n_z + std::abs(o1 - o0));
+  }
+  return span;
+}
+
 // Derived fields of a binned plan whose region (waves, acc32, tile, halo, t bins) is set; span: its
-// sheared_span.
-// row_item: row_item_events of the same code on batches of rows.
+// sheared_span; row_item: row_item_events of the same code on batches of rows.
 static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_event, int64_t n, int span,
                         int row_item, Plan& p) {
   if (p.rings) {
     p.ev_per_batch = p.solo ? 1 : 2;
-    const RingLds lds = ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, p.loglik != 0);
+    p.ev_per_wg = ring_item_events(n, pairs_per_event, p.RY, p.W, p.ev_per_batch, p.waves, row_item, p.acc32 != 0);
+    const RingLds lds = ring_lds_layout(p.pitch, p.W, p.RY, p.waves, p.ev_per_batch, p.slack, p.ev_per_wg, p.loglik != 0);
     p.lds_off = lds.off;
     p.lds_sum = lds.sum;
     p.lds_img = lds.img;
@@ -260,6 +275,7 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
     p.batch_bytes = ring_block_bytes(p.ev_per_batch, p.rings, p.loglik != 0);
   } else {
     p.ev_per_batch = events_per_batch(p.waves, rows_max * p.segs);
+    p.ev_per_wg = row_item;
     p.cbytes = p.ev_per_batch * event_const_bytes(p.loglik != 0);
     p.lds_bytes = tiled_lds_layout(p.pitch, p.W, p.RY, p.acc32, p.ev_per_batch, p.loglik != 0, &p.lds_ev, &p.lds_off);
     p.batch_bytes =
@@ -268,21 +284,6 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
   p.nty = (g->n_y + p.TY - 1) / p.TY;
   p.ntz = (span + p.TZ - 1) / p.TZ;
   p.nbins = p.ntb * p.nty * p.ntz;
-  if (p.rings) {
-    // ring blocks: where a workgroup's share of the events is worth less than staging and flushing the region,
-    // fewer and larger items; a block for every wavefront, two where that leaves an item for every CU.
-    const int64_t round = (int64_t)p.ev_per_batch * p.waves;
-    int64_t per = (double)n * pairs_per_event < kItemPairs * (double)p.RY * (double)p.W ? n / 512 : n / 1024;
-    per = std::min<int64_t>(std::max(per, std::max(round, std::min(2 * round, n / 256))), kRingItem);
-    // Never more events than the accumulators' units on batches of rows allow: larger items would hold the
-    // image in coarser units, and a pixel that little reaches (a column beside the strips' ends) shows their
-    // rounding, ten iterations of it amplified (10 iterations of 264,253 events on 256^2: relative L2 to exact
-    // sums 3.3e-6 in units of 2^-24, 8.2e-6 in 2^-23).
-    if (p.acc32) per = std::min<int64_t>(per, ((int64_t)1 << (32 - unit_shift(row_item))) - 1);
-    p.ev_per_wg = (int)(per / p.ev_per_batch * p.ev_per_batch);
-  } else {
-    p.ev_per_wg = row_item;
-  }
   if (p.acc32) p.acc_shift = unit_shift(p.ev_per_wg);
   const int64_t nonempty = n < p.nbins ? n : p.nbins;
   p.max_items = (n + p.ev_per_wg - 1) / p.ev_per_wg + nonempty;
@@ -409,6 +410,7 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
               const int pitch = (RY + kBankAlign - 1) / kBankAlign * kBankAlign;
               const int epb = events_per_batch(waves, rows_max * segs);
               const size_t bytes = tiled_lds_layout(pitch, W, RY, acc32, epb, loglik, nullptr, nullptr);
+              const int row_item = row_item_events(n, epb, acc32);
               const int reach = acc32 ? W : 2 * W;
               // thread words address columns with 8 bits and rows with 9 bits
               if (bytes > budget || reach < maxlen || W > 256 || RY > 512) continue;
@@ -434,7 +436,8 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 const int most = 4 * shape_waves_per_simd(shape, loglik);
                 const int fit = std::max(1, std::min(wgs, (most + waves / 2) / waves)), each = std::max(4, std::min(waves, most / fit) / 4 * 4);
                 const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
-                const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, loglik).bytes;
+                const int item = ring_item_events(n, pairs_per_event, RY, W, shape >= 1000 ? 1 : 2, each, row_item, acc32 != 0);
+                const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, item, loglik).bytes;
                 if (lds <= kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
                   p.rings = shape_rings(shape);
                   p.solo = shape >= 1000;
@@ -452,7 +455,6 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 p.tmin = -0.5 * dt * p.ntb;
               }
               if (span[dti] == 0) span[dti] = sheared_span(g, p);
-              const int row_item = row_item_events(n, epb, acc32);
               finish_plan(g, rows_max, pairs_per_event, n, span[dti], row_item, p);
               if (!loglik) {  // as the layout on batches of rows is priced: 1.6 x region pixels x items, all bins filled
                 const double row_cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +

@@ -6,7 +6,7 @@
 // pixels in registers between the two passes.  Against the batch layout (jpet_binned.h, one row per
 // thread, all events of a batch between two workgroup barriers) this leaves out the barriers, the
 // LDS denominators and the per-wavefront reductions over rows of several events: one reduction over
-// an event's lanes gives its denominator.
+// an event's lanes (in double precision, as between the wavefronts there) gives its denominator.
 //
 // Bound: VALU issue.  Per pixel the pass needs v_exp_f32, 3 FMAs for the exponent, P rho, D += P rho,
 // and the scale and conversion of the back-projection; one LDS read and one LDS atomic go beside them.
@@ -279,15 +279,16 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     };
     auto tail = [&](int k) { return ((k < 2 ? t01 : t23) >> (16 * (k & 1))) & 0xffffu; };
     auto row = [&](int k, int H) { return ring_row(w[k >> 1] >> (16 * (k & 1)), c.mid + lrow + k * lstep, H); };
-    // the sum over an event's lanes, to all of them
-    auto event_sum = [&](float v, float& lo, float& hi) {
+    // the sum over an event's lanes, to all of them: of the lanes' single-precision sums over their rows, in double
+    // precision, so that a denominator is rounded no more often than its rows are
+    auto event_sum = [&](float v, double& lo, double& hi) {
       if constexpr (SOLO) {
-        lo = hi = wave_sum_dpp(v);
+        lo = hi = wave_sum_dpp_d((double)v);
         return lo;
       } else {
-        const float h = half_sums_dpp(v);
-        lo = lane_value(h, 31);
-        hi = lane_value(h, 63);
+        const double h = half_sums_dpp_d((double)v);
+        lo = lane_value_d(h, 31);
+        hi = lane_value_d(h, 63);
         return ln < 32 ? lo : hi;
       }
     };
@@ -317,13 +318,14 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
         if (r.nr > 0) D = fmaf(F[k], S, D);
         else at[k] = kNoRow;
       });
-      float Dlo, Dhi;
-      const float De = event_sum(D, Dlo, Dhi);  // the event's denominator
+      double Dlo, Dhi;
+      const double De = event_sum(D, Dlo, Dhi);  // the event's denominator
       // (a unit / D overflows a float only for D < 1e-28: such blocks take the way below)
-      if (!(Dlo > 0.0f && Dlo < tiny) && !(Dhi > 0.0f && Dhi < tiny)) {  // wavefront-uniform
+      const float flo = (float)Dlo, fhi = (float)Dhi;
+      if (!(flo > 0.0f && flo < tiny) && !(fhi > 0.0f && fhi < tiny)) {  // wavefront-uniform
         if (l == 0) denominator(De);
         if constexpr (FORWARD) continue;
-        const float sc = De > 0.0f ? kUnit * __builtin_amdgcn_rcpf(De) : 0.0f;
+        const float sc = De > 0.0 ? kUnit * __builtin_amdgcn_rcpf((float)De) : 0.0f;
         each_ring<0, RINGS>([&](auto kk) {
           constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
           const int wlh = (int)((tail(k) & 127u) + 1) >> 1;
@@ -352,8 +354,8 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
         D = fmaf(exact_at(rk, (float)j + 0.5f, &nbad), rho_s[(r.kc + j) * pitch + r.rl] * up, D);
     }
     if (nbad) atomicAdd(&ps.bad, (unsigned)nbad);
-    float Dlo, Dhi;
-    const double De = (double)event_sum(D, Dlo, Dhi) / up;
+    double Dlo, Dhi;
+    const double De = event_sum(D, Dlo, Dhi) / up;
     if (l == 0) denominator(De);
     if (FORWARD || !(De > 0.0)) continue;
     const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / (De * 18446744073709551616.0));

@@ -199,7 +199,9 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
   float* const rho_s = reinterpret_cast<float*>(smem + p.lds_img);
   double* const acc_s = reinterpret_cast<double*>(rho_s + npx);
   int* const off_s = reinterpret_cast<int*>(smem + p.lds_off);
-  float* const sum_s = reinterpret_cast<float*>(smem + p.lds_sum);
+  double* const D_s = reinterpret_cast<double*>(smem + p.lds_sum);
+  float* const Du_s = reinterpret_cast<float*>(D_s + p.ev_per_wg);
+  float* const Dw_s = Du_s + p.ev_per_wg;
   const int tid = threadIdx.x;
   const int lane = tid & (WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -279,14 +281,20 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
       const float lo = lane_value(h, 31), hi = lane_value(h, 63);
       return ln < 32 ? lo : hi;
     };
+    auto event_sum_d = [&](float v) {  // the same in double precision, for D'
+      if constexpr (SOLO) return wave_sum_dpp_d((double)v);
+      const double h = half_sums_dpp_d((double)v);
+      const double lo = lane_value_d(h, 31), hi = lane_value_d(h, 63);
+      return ln < 32 ? lo : hi;
+    };
     // an event's sums (one lane each)
-    auto finish = [&](float D, float Du, float Dw) {
+    auto finish = [&](double D, float Du, float Dw) {
       const int e = kEvents * q + (SOLO ? 0 : ln >> 5);
       if (l != 0 || e >= it.count) return;
-      sum_s[e] = D;
+      D_s[e] = D;
       if constexpr (!VALUE) {
-        sum_s[p.ev_per_wg + e] = Du;
-        sum_s[2 * p.ev_per_wg + e] = Dw;
+        Du_s[e] = Du;
+        Dw_s[e] = Dw;
       }
     };
 
@@ -312,7 +320,7 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
           }
           if (r.nr > 0) D = fmaf(F, S, D);
         });
-        finish(event_sum(D), 0.0f, 0.0f);
+        finish(event_sum_d(D), 0.0f, 0.0f);
       } else {
         RingCache<RINGS, LEN> cache;
         float F[RINGS];
@@ -347,9 +355,9 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
             Dw = fmaf(F[k], dw, Dw);
           }
         });
-        D = event_sum(D);
-        finish(D, event_sum(Du), event_sum(Dw));
-        const float invD = D > 0.0f ? (float)(1.0 / (double)D) : 0.0f;
+        const double De = event_sum_d(D);
+        finish(De, event_sum(Du), event_sum(Dw));
+        const float invD = De > 0.0 ? (float)(1.0 / De) : 0.0f;
         each_ring<0, RINGS>([&](auto kk) {
           constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
           const uint32_t tw = tail(k);
@@ -398,12 +406,12 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
       }
     }
     if (nbad) atomicAdd(&ps.bad, (unsigned)nbad);
-    D = event_sum(D);
+    const double De = event_sum_d(D);
     if constexpr (VALUE) {
-      finish(D, 0.0f, 0.0f);
+      finish(De, 0.0f, 0.0f);
     } else {
-      finish(D, event_sum(Du), event_sum(Dw));
-      const float invD = D > 0.0f ? (float)(1.0 / (double)D) : 0.0f;
+      finish(De, event_sum(Du), event_sum(Dw));
+      const float invD = De > 0.0 ? (float)(1.0 / De) : 0.0f;
       for (int k = first; k < RINGS; ++k) {
         const RingRow r = row(k, 0);
         const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], lg.pix, lg.pix2);
@@ -418,12 +426,12 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
   double a[3] = {0.0, 0.0, 0.0};
   unsigned zero = 0;
   for (int e = tid; e < it.count; e += (int)blockDim.x) {
-    const double D = (double)sum_s[e];
+    const double D = D_s[e];
     if (D > 0.0) {
       a[0] += log(D);
       if constexpr (!VALUE) {
-        a[1] += (double)sum_s[p.ev_per_wg + e] / D;
-        a[2] += (double)sum_s[2 * p.ev_per_wg + e] / D;
+        a[1] += (double)Du_s[e] / D;
+        a[2] += (double)Dw_s[e] / D;
       }
     } else {
       ++zero;
