@@ -295,9 +295,10 @@ int jpet_mlem_batched_graph_destroy(jpet_batched_graph* graph);
  * results are those of jpet_mlem_iterate, except:
  *   - flags must be 0 (else JPET_EINVAL): every call prepares its events, and runs the planned
  *     event pass;
- *   - a geometry and event count whose workspace (jpet_mlem_workspace_size) exceeds
- *     JPET_NOALLOC_SCRATCH_BYTES returns JPET_EWORKSPACE before anything is enqueued (about
- *     300k events at 400 x 400 px of 2 mm, 500k at 64 x 64 px of 4 mm);
+ *   - a geometry and event count that no plan (with g->plan set, not that one either) fits into
+ *     JPET_NOALLOC_SCRATCH_BYTES returns JPET_EWORKSPACE before anything is enqueued (from about
+ *     645k events at 400 x 400 px of 2 mm on, 945k at 64 x 64 px of 4 mm); near the limit the call
+ *     may take another plan than jpet_mlem_iterate, one with a smaller workspace;
  *   - all calls on one GPU share its array, which keeps the last call's contents: calls that
  *     overlap on one GPU (different streams or threads without ordering between them) race and
  *     give undefined results.  Order them on one stream or synchronise between them. */

@@ -304,8 +304,11 @@ static void finish_plan(const jpet_geometry* g, int rows_max, double pairs_per_e
 // rows by that layout's own figure (row_unit; batch_unit: with 32-bit accumulators, which a batch takes).
 // The others follow in the list, their figures times 2^64 for each of the two that they miss.
 constexpr int32_t kCheapest = -1;
+//
+// limit: the workspace's bytes, for callers that cannot have more.  A code whose ring blocks (up to 608 bytes an
+// event) exceed them stays on batches of rows, and plans that fit rank before those that do not.
 static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik, int32_t want,
-                            std::vector<PlanCand>* out) {
+                            size_t limit, std::vector<PlanCand>* out) {
   out->clear();
   const bool allow_acc32 = !loglik;
   msz *= 1.0 + g->sigma_z_edge;  // the largest ellipse: sigma_z at the strip ends
@@ -429,6 +432,14 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
               p.wgs = wgs;
               p.loglik = loglik ? 1 : 0;
               p.code = plan_code(waves, acc32, wgs, dti, ti, cache);
+              if (dt != 0.0) {
+                p.ntb = (int)ceil(2.0 * tmax / dt);
+                if (p.ntb < 1) p.ntb = 1;
+                p.dt = dt;
+                p.tmin = -0.5 * dt * p.ntb;
+              }
+              if (span[dti] == 0) span[dti] = sheared_span(g, p);
+              const Plan rows = p;
               // ring blocks where a cache holds a whole event's rows and the LDS still lets as many
               // wavefronts run as the registers do (that many, shared by the workgroups of the code)
               int simd = occ;
@@ -448,14 +459,13 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                   simd = std::min(most / each, (int)(kLdsPerCU / align_up(lds + 256, kGranule))) * each / 4;
                 }
               }
-              if (dt != 0.0) {
-                p.ntb = (int)ceil(2.0 * tmax / dt);
-                if (p.ntb < 1) p.ntb = 1;
-                p.dt = dt;
-                p.tmin = -0.5 * dt * p.ntb;
-              }
-              if (span[dti] == 0) span[dti] = sheared_span(g, p);
               finish_plan(g, rows_max, pairs_per_event, n, span[dti], row_item, p);
+              bool over = limit < SIZE_MAX && workspace_layout(p, n, npix_of(g), nullptr, nullptr) > limit;
+              if (over && p.rings) {
+                p = rows;
+                finish_plan(g, rows_max, pairs_per_event, n, span[dti], row_item, p);
+                over = workspace_layout(p, n, npix_of(g), nullptr, nullptr) > limit;
+              }
               if (!loglik) {  // as the layout on batches of rows is priced: 1.6 x region pixels x items, all bins filled
                 const double row_cost = nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
                                         1.6 * (nn / row_item + std::min(nn, (double)p.nbins)) * (double)pitch * (double)W;
@@ -477,6 +487,7 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 cost += nn * pairs_per_event * occ_factor * (acc32 ? 0.82 : 1.0) +
                         4.5 * (nn / p.ev_per_wg + rests) * (double)RY * (double)W;
               }
+              if (over) cost = ldexp(cost, 192);
               ++seen;
               if (want != kCheapest) out->push_back({p, cost});
               else if (cost < best[plan_unit(p)].cost) best[plan_unit(p)] = {p, cost}, at[plan_unit(p)] = seen;
@@ -506,7 +517,7 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
 void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik,
                      std::vector<PlanCand>* out) {
   std::vector<PlanCand> all;
-  enumerate_plans(g, msz, mdl, n, loglik, 0, &all);
+  enumerate_plans(g, msz, mdl, n, loglik, 0, SIZE_MAX, &all);
   std::vector<int> order(all.size());
   for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return all[a].cost < all[b].cost; });
@@ -515,10 +526,10 @@ void plan_candidates(const jpet_geometry* g, double msz, double mdl, int64_t n, 
   for (int k : order) out->push_back(all[k]);
 }
 
-Plan make_plan(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik) {
+Plan make_plan(const jpet_geometry* g, double msz, double mdl, int64_t n, bool loglik, size_t limit) {
   const int32_t want = g->plan;
   std::vector<PlanCand> c;
-  if (want != kPlanGeneric) enumerate_plans(g, msz, mdl, n, loglik, want == 0 ? kCheapest : want, &c);
+  if (want != kPlanGeneric) enumerate_plans(g, msz, mdl, n, loglik, want == 0 ? kCheapest : want, limit, &c);
   if (want == 0) return c[0].p;
   if (want == kPlanGeneric) {
     Plan p;
@@ -563,7 +574,7 @@ size_t workspace_layout(const Plan& p, int64_t n, int64_t npix, void* base, Work
   w.bin_count = (uint32_t*)take(sizeof(uint32_t) * nb);
   w.bin_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.item_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
-  w.rest_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
+  w.rest_start = (uint32_t*)take(sizeof(uint32_t) * nb);
   w.batch_start = (uint32_t*)take(sizeof(uint32_t) * (nb + 1));
   w.items = (BinItem*)take(p.tiled ? sizeof(BinItem) * (size_t)p.max_items : 0);
   w.bytes = off;
@@ -736,6 +747,43 @@ static int pass_granularity(uint32_t flags) {
   return wv ? kPassWavePerEvent : th ? kPassThreadPerEvent : kPassPlanned;
 }
 
+int jpet::plan_within(const jpet_geometry* g, int64_t n, size_t limit, Plan* p) {
+  const int rc = check_geometry(g);
+  if (rc) return rc;
+  if (n < 0 || n > kMaxEvents) return JPET_EINVAL;
+  *p = make_plan(g, g->sigma_z, g->sigma_dl, n, false, limit);
+  return p->invalid ? JPET_EDOMAIN : JPET_OK;  // (the named plan does not fit this geometry)
+}
+
+int jpet::iterate_with_plan(const Plan& p, const jpet_geometry* g, const float* events, int64_t n, const float* s,
+                            float* rho, int32_t n_iter, void* ws, size_t ws_bytes, uint32_t flags, jpet_stats* stats,
+                            void* stream) {
+  const int gran = pass_granularity(flags);
+  Workspace w;
+  int rc = carve(p, g, n, ws, ws_bytes, &w);
+  if (rc) return rc;
+  hipStream_t st = (hipStream_t)stream;
+  const Geo geo = make_geo(g, g->sigma_z, g->sigma_dl);
+  hipError_t e;
+  if (!(flags & JPET_WS_PREPARED)) {
+    w.clear_acc = npix_of(g);  // the preparation clears the accumulators too
+    rc = do_prepare(geo, p, events, n, w, st);
+    if (rc) return rc;
+  } else {
+    if ((e = launch_fill_u64(w.acc, npix_of(g), st)) != hipSuccess) return hip_fail(e);
+    if (n_iter > 0 && (e = launch_fill_u64(w.cnt + C_ZERO_DEN, 2, st)) != hipSuccess) return hip_fail(e);
+  }
+  for (int it = 0; it < n_iter; ++it) {
+    rc = timed([&] { return launch_event_pass(geo, p, n, w, rho, st, gran); }, st);
+    if (rc) return rc;
+    w.more = it + 1 < n_iter;
+    e = launch_update(geo, s, rho, w, st);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  if (stats) return read_stats(w, n, stats, st);
+  return JPET_OK;
+}
+
 extern "C" {
 
 const char* jpet_strerror(int status) {
@@ -898,33 +946,10 @@ int jpet_mlem_iterate(const jpet_geometry* g, const float* events, int64_t n, co
   int rc = check_geometry(g);
   if (rc) return rc;
   if (n < 0 || n > kMaxEvents || (n > 0 && !events) || !rho || n_iter < 0) return JPET_EINVAL;
-  const int gran = pass_granularity(flags);
-  if (gran < 0) return JPET_EINVAL;
-  const Plan p = make_plan(g, g->sigma_z, g->sigma_dl, n);
-  if (p.invalid) return JPET_EDOMAIN;  // the named plan does not fit this geometry
-  Workspace w;
-  rc = carve(p, g, n, ws, ws_bytes, &w);
-  if (rc) return rc;
-  hipStream_t st = (hipStream_t)stream;
-  const Geo geo = make_geo(g, g->sigma_z, g->sigma_dl);
-  hipError_t e;
-  if (!(flags & JPET_WS_PREPARED)) {
-    w.clear_acc = npix_of(g);  // the preparation clears the accumulators too
-    rc = do_prepare(geo, p, events, n, w, st);
-    if (rc) return rc;
-  } else {
-    if ((e = launch_fill_u64(w.acc, npix_of(g), st)) != hipSuccess) return hip_fail(e);
-    if (n_iter > 0 && (e = launch_fill_u64(w.cnt + C_ZERO_DEN, 2, st)) != hipSuccess) return hip_fail(e);
-  }
-  for (int it = 0; it < n_iter; ++it) {
-    rc = timed([&] { return launch_event_pass(geo, p, n, w, rho, st, gran); }, st);
-    if (rc) return rc;
-    w.more = it + 1 < n_iter;
-    e = launch_update(geo, s, rho, w, st);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  if (stats) return read_stats(w, n, stats, st);
-  return JPET_OK;
+  if (pass_granularity(flags) < 0) return JPET_EINVAL;
+  Plan p;
+  if ((rc = plan_within(g, n, SIZE_MAX, &p))) return rc;
+  return iterate_with_plan(p, g, events, n, s, rho, n_iter, ws, ws_bytes, flags, stats, stream);
 }
 
 int jpet_mlem_backproject(const jpet_geometry* g, const float* events, int64_t n, const float* rho, uint64_t* acc,

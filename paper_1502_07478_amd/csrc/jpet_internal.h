@@ -38,9 +38,8 @@ struct EventRec {
   double hs;     // 0.5 / (um su): a row's half chord is sqrt(hs (9 - 4 wm c^2 dy^2))
   int32_t r0;    // first pixel row of the 3-sigma ellipse (App. B), clipped to the grid
   int32_t r1;    // last row; r1 < r0 marks an invalid (dropped) event
-  int32_t index; // position of the event in the caller's array
-  int32_t pad;
 };
+static_assert(sizeof(EventRec) == 56, "the no-alloc entry point's array holds a fixed number of them");
 
 // Per-event constants of the binned event pass (64 bytes), written at prepare time.  With Y the
 // row's y, dy = Y - y~ and b1 = z - z~ - dy tan (Eq. 8-12):
@@ -312,8 +311,16 @@ constexpr uint32_t kNoBin = 0xffffffffu;
 // The plan of a pass: the one g->plan names, or with g->plan = 0 the cheapest candidate under the
 // cost model.  loglik: plan for the log-likelihood pass (64-bit region slots for its doubles, its
 // own register budget) instead of the MLEM pass.  A named plan that does not fit the geometry
-// comes back with invalid = 1.
-Plan make_plan(const jpet_geometry* g, double mask_sz, double mask_sdl, int64_t n, bool loglik = false);
+// comes back with invalid = 1.  limit: the bytes a workspace may have; a plan that needs more is returned
+// only when none fits.
+Plan make_plan(const jpet_geometry* g, double mask_sz, double mask_sdl, int64_t n, bool loglik = false,
+               size_t limit = SIZE_MAX);
+
+// jpet_mlem_iterate in two steps: the plan for a workspace of at most limit bytes (validates g, n and g->plan), and
+// the iterations with it.
+int plan_within(const jpet_geometry* g, int64_t n, size_t limit, Plan* p);
+int iterate_with_plan(const Plan& p, const jpet_geometry* g, const float* events, int64_t n, const float* s, float* rho,
+                      int32_t n_iter, void* ws, size_t ws_bytes, uint32_t flags, jpet_stats* stats, void* stream);
 
 // Every binned plan that fits the geometry, with its cost-model figure (lower is faster), sorted
 // by that figure; the generic pass is listed last when no binned plan fits.

@@ -48,12 +48,12 @@ extern "C" int jpet_mlem_iterate_noalloc(const jpet_geometry* g, const float* ev
   // every call prepares its events (the array holds whatever the last call on this device left),
   // with the planned pass: flags must be 0
   if (flags != 0u || n_iter < 0 || !rho || (n > 0 && !events)) return JPET_EINVAL;
-  size_t need = 0;
-  int rc = jpet_mlem_workspace_size(g, n, &need);  // validates the geometry, n and the plan
+  jpet::Plan p;
+  int rc = jpet::plan_within(g, n, kScratchBytes, &p);  // validates the geometry, n and the plan
   if (rc) return rc;
-  if (need > kScratchBytes) return JPET_EWORKSPACE;
+  if (jpet::workspace_layout(p, n, (int64_t)g->n_y * g->n_z, nullptr, nullptr) > kScratchBytes) return JPET_EWORKSPACE;
   void* ws = nullptr;
   if ((rc = scratch_of_current_device(&ws))) return rc;
   // the workspace's counters and accumulators are cleared by kernels inside this call
-  return jpet_mlem_iterate(g, events, n, s, rho, n_iter, ws, kScratchBytes, flags, stats, stream);
+  return jpet::iterate_with_plan(p, g, events, n, s, rho, n_iter, ws, kScratchBytes, flags, stats, stream);
 }

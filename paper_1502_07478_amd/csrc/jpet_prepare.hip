@@ -41,8 +41,6 @@ __device__ EventRec event_record(const Geo& g, const float* __restrict__ events,
   EventRec e;
   e.r0 = 0;
   e.r1 = -1;
-  e.index = (int32_t)j;
-  e.pad = 0;
   e.t = e.c = e.y = e.z = e.hs = 0.0;
   e.su = 1.0;
   const double hl = 0.5 * g.L;
@@ -304,7 +302,7 @@ __global__ void __launch_bounds__(256) k_place(const uint32_t* __restrict__ key,
 // row rbase and (sheared) column kbase, in double precision.  With r the region row, the row's
 // y is Y = Yb + pix r and dy = Y - y~ = pix r - yr, both linear in r; each row constant of the
 // kernel (Eq. 7-12; see EvRow) is then a polynomial of degree <= 2 in r, expanded here.
-__device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int rbase, int kbase) {
+__device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int index, int rbase, int kbase) {
   const double pix = g.pixel, t = e.t, c = e.c, c2 = c * c, f = g.fa;
   const double u = g.u * e.su, w = g.w;  // u: this event's sigma_z^-2
   const double Yb = g.y0 + (double)rbase * pix;
@@ -340,7 +338,7 @@ __device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int rbase,
   k.qa = (float)(s2u * pix * pix);
   k.QB = (float)(2.0 * s2u * pix);
   k.s2u = (float)s2u;
-  k.index = e.index;
+  k.index = index;
   k.mid = 0;
   return k;
 }
@@ -430,7 +428,8 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
     uint32_t* words = reinterpret_cast<uint32_t*>(blk + p.cbytes);
     __syncthreads();
     if (tid < nb) {
-      const EventRec e = ev[order[it.start + e0 + tid]];
+      const int j = order[it.start + e0 + tid];
+      const EventRec e = ev[j];
       ev_s[tid] = e;
       grp_r0[tid] = 0;
       grp_n[tid] = e.r1 - e.r0 + 1;
@@ -452,7 +451,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
         EvConst k;
         k.yr = (float)(e.y - (g.y0 + (double)rbase * g.pixel));
         k.zr = (float)(e.z - (g.z0 + (double)kbase * g.pixel));
-        k.index = e.index;
+        k.index = j;
         k.S2u = (float)(kHalfLog2e * 2.0 * (g.u * e.su));
         k.t = t;
         k.A1 = 2.0f * u * c2 * c2;
@@ -470,7 +469,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
         k.pad[0] = k.pad[1] = 0;
         reinterpret_cast<EvConst*>(blk)[tid] = k;
       } else {
-        reinterpret_cast<EvRow*>(blk)[tid] = event_row_constants(g, e, rbase, kbase);
+        reinterpret_cast<EvRow*>(blk)[tid] = event_row_constants(g, e, j, rbase, kbase);
       }
     }
     __syncthreads();
@@ -701,13 +700,13 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
   int* const off_s = reinterpret_cast<int*>(rows_s + p.ev_per_wg + 1);
   for (int r = tid; r < p.RY; r += blockDim.x) off_s[r] = shear_offset(g, tc, rbase + r) + kbase;
   for (int e = tid; e < nblk * epb; e += blockDim.x) {
-    const EventRec er = ev[order[it.start + min(e, it.count - 1)]];
+    const int j = order[it.start + min(e, it.count - 1)];
+    const EventRec er = ev[j];
     // polynomials in the rows from the event's central row on: the rounding of their coefficients
     // then stays below that of the rows' own values
     const int mid = centre_row(g, er);
-    EvRow k = event_row_constants(g, er, mid, kbase);
+    EvRow k = event_row_constants(g, er, e < it.count ? j : -1, mid, kbase);  // (-1: no event)
     k.mid = mid - rbase;
-    if (e >= it.count) k.index = -1;  // no event
     reinterpret_cast<EvRow*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes)[e % epb] = k;
     if (p.loglik) {
       const double w = g.w, c2 = er.c * er.c, t2 = er.t * er.t;

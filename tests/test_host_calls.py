@@ -137,3 +137,33 @@ def test_large_items_reach_both_pitches(calls, shape, half_rows, pitch):
     log = calls("iterate", (sz, sdl, PIXEL, 33, 33, n, plan))
     limits_hold(log)
     assert {name for name, _ in launches(log, "k_event_pass_rings")} == {f"k_event_pass_rings<{shape},{pitch},false>"}
+
+
+# the most events jpet_mlem_iterate_noalloc took on batches of rows, and for a named plan (R, L, sigma_z, sigma_dl,
+# pixel, n_y, n_z): (events, (events, plan) or None)
+NOALLOC = {
+    (450, 500, 14.2, 17.2, 2.21, 344, 500): (884704, None),
+    (450, 500, 19.8, 15.9, 1.79, 73, 200): (849564, (809586, 2253)),
+    (450, 500, 19.2, 11.6, 1.31, 609, 609): (828252, (764740, 2061)),
+    (450, 500, 8.7, 14.0, 1.05, 134, 134): (719465, (676356, 2253)),
+    (450, 500, 4.2, 13.3, 4.63, 39, 300): (997184, (956800, 2253)),
+    (450, 500, 13.6, 28.1, 1.89, 119, 119): (677611, (645843, 2253)),
+    (450, 500, 19.4, 47.4, 0.23, 1004, 300): (4393033, None),
+    (450, 500, 30, 63, 1, 400, 400): (4430692, None),
+    (450, 500, 10, 63, 2, 400, 400): (403470, None),
+    (450, 500, 10, 63, 4, 64, 64): (631900, None),
+    (130, 300, 10, 40, 4, 64, 76): (784512, None),
+}
+
+
+@pytest.mark.parametrize("geo", list(NOALLOC))
+def test_noalloc_takes_what_fits_on_batches_of_rows(calls, geo):
+    """Its array has a fixed size: where ring blocks need more, the call takes a plan that fits, or the named plan
+    on batches of rows."""
+    R, L, sz, sdl, pixel, n_y, n_z = geo
+    most, named = NOALLOC[geo]
+    for n, plan in ((most, 0), (int(0.9 * most), 0), *([named] if named else [])):
+        log = calls("noalloc", (sz, sdl, pixel, n_y, n_z, n, plan, float(R), float(L)))
+        assert codes(log)["noalloc"] == 0, (n, plan)
+        limits_hold(log)
+    assert codes(calls("noalloc", (sz, sdl, pixel, n_y, n_z, 20_000_000, 0, float(R), float(L))))["noalloc"] == jpet.JPET_EWORKSPACE
