@@ -1252,51 +1252,74 @@ static int batched_setup(const jpet_instance* inst, int32_t count, const BatchLa
   return JPET_OK;
 }
 
-// The batched pass's side streams on the current device (default priority) with the fork event
-// and one join event each: created on first use, outside any capture (batched_begin), kept until
-// the process ends.
+// The batched pass's side streams (default priority) with the fork event and one join event each.
 struct SideStream {
   hipStream_t s[kBatchStreams - 1] = {};
   hipEvent_t fork = nullptr, join[kBatchStreams - 1] = {};
 };
+
+static hipError_t make_side_stream(SideStream* S) {
+  hipError_t e;
+  for (int q = 0; q < kBatchStreams - 1; ++q) {
+    if ((e = hipStreamCreateWithFlags(&S->s[q], hipStreamNonBlocking)) != hipSuccess) return e;
+    if ((e = hipEventCreateWithFlags(&S->join[q], hipEventDisableTiming)) != hipSuccess) return e;
+  }
+  return hipEventCreateWithFlags(&S->fork, hipEventDisableTiming);
+}
+
+static void drop_side_stream(const SideStream& S) {
+  for (int q = 0; q < kBatchStreams - 1; ++q) {
+    if (S.join[q]) (void)hipEventDestroy(S.join[q]);
+    if (S.s[q]) (void)hipStreamDestroy(S.s[q]);
+  }
+  if (S.fork) (void)hipEventDestroy(S.fork);
+}
+
+// Eager batches share one set per device, created on first use kept until the process ends and never
+// captured.  g_side_mu is held over an iteration's fork, launches and join: a wait takes an event's latest
+// record, and two threads' records of one event must not come between each other's records and waits.
 static std::mutex g_side_mu;
 static std::vector<SideStream> g_side;  // per device
 
-static int side_stream(SideStream* out) {
+static int side_stream_locked(SideStream* out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
-  std::lock_guard<std::mutex> lk(g_side_mu);
   if ((int)g_side.size() <= dev) g_side.resize((size_t)dev + 1);
-  SideStream& S = g_side[(size_t)dev];
-  if (!S.fork) {
-    for (int q = 0; q < kBatchStreams - 1; ++q) {
-      if ((e = hipStreamCreateWithFlags(&S.s[q], hipStreamNonBlocking)) != hipSuccess) return hip_fail(e);
-      if ((e = hipEventCreateWithFlags(&S.join[q], hipEventDisableTiming)) != hipSuccess) return hip_fail(e);
+  if (!g_side[(size_t)dev].fork) {
+    SideStream S;
+    if ((e = make_side_stream(&S)) != hipSuccess) {
+      drop_side_stream(S);
+      return hip_fail(e);
     }
-    if ((e = hipEventCreateWithFlags(&S.fork, hipEventDisableTiming)) != hipSuccess) return hip_fail(e);
+    g_side[(size_t)dev] = S;
   }
-  *out = S;
+  *out = g_side[(size_t)dev];
   return JPET_OK;
 }
 
 // n_iter iterations of a set-up batch: per iteration the counters' reset, one batched pass per
 // class over its instances' items (the classes shared by the caller's stream and the side
 // streams, joined before the update), the generic instances' passes and the pixel update of all.
+// own: the side streams of a capture; null for an eager batch.
 static int batched_iterations(const jpet_instance* inst, int32_t count, int32_t n_iter, const BatchLayout& L,
-                              const std::vector<Workspace>& w, const std::vector<Geo>& geo, void* ws, bool timing,
-                              hipStream_t st) {
+                              const std::vector<Workspace>& w, const std::vector<Geo>& geo, void* ws,
+                              const SideStream* own, hipStream_t st) {
   BatchInst* table = reinterpret_cast<BatchInst*>(ws);
   hipError_t e;
-  SideStream side;
   const int ns = L.streams;
-  if (ns > 1) {
-    const int rc = side_stream(&side);
-    if (rc) return rc;
-  }
   for (int it = 0; it < n_iter; ++it) {
     if ((e = launch_batched_reset(table, count, st)) != hipSuccess) return hip_fail(e);
     if (!L.cls.empty()) {
+      std::unique_lock<std::mutex> lk(g_side_mu, std::defer_lock);
+      SideStream side;
+      if (own) {
+        side = *own;
+      } else if (ns > 1) {
+        lk.lock();
+        const int rc = side_stream_locked(&side);
+        if (rc) return rc;
+      }
       auto pass = [&] {
         hipError_t r = hipSuccess;
         if (ns > 1) r = hipEventRecord(side.fork, st);
@@ -1312,7 +1335,7 @@ static int batched_iterations(const jpet_instance* inst, int32_t count, int32_t 
         }
         return r;
       };
-      if (timing) {
+      if (!own) {
         const int rc = timed(pass, st);
         if (rc) return rc;
       } else if ((e = pass()) != hipSuccess) {
@@ -1354,10 +1377,6 @@ static int batched_begin(const jpet_instance* inst, int32_t count, void* ws, siz
   }
   std::vector<int64_t> item_begin;
   if ((rc = batched_items(count, L, *w, st, &item_begin))) return rc;
-  if (L->streams > 1) {
-    SideStream side;
-    if ((rc = side_stream(&side))) return rc;
-  }
   return batched_setup(inst, count, *L, *w, *geo, item_begin, ws, st);
 }
 
@@ -1378,7 +1397,7 @@ int jpet_mlem_batched_iterate(const jpet_instance* inst, int32_t count, int32_t 
   std::vector<Geo> geo;
   int rc = batched_begin(inst, count, ws, ws_bytes, flags, st, &L, &w, &geo);
   if (rc) return rc;
-  rc = batched_iterations(inst, count, n_iter, L, w, geo, ws, true, st);
+  rc = batched_iterations(inst, count, n_iter, L, w, geo, ws, nullptr, st);
   if (rc) return rc;
   if (stats) {
     for (int k = 0; k < count; ++k) {
@@ -1399,25 +1418,29 @@ int jpet_mlem_batched_graph_create(const jpet_instance* inst, int32_t count, int
   std::vector<Geo> geo;
   int rc = batched_begin(inst, count, ws, ws_bytes, flags, st, &L, &w, &geo);
   if (rc) return rc;
-  // capture the iterations on a stream of the library's own, at the default priority
-  hipStream_t cs = nullptr;
-  hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+  // capture the iterations on streams and events of this call's own, at the default priority, which no other
+  // call uses: work that another thread enqueued on a stream under capture would become part of the graph.
+  // They live until the graph is instantiated.
+  struct Capture {
+    hipStream_t s = nullptr;
+    SideStream side;
+    hipGraph_t graph = nullptr;
+    ~Capture() {
+      if (graph) (void)hipGraphDestroy(graph);
+      drop_side_stream(side);
+      if (s) (void)hipStreamDestroy(s);
+    }
+  } c;
+  hipError_t e = hipStreamCreateWithFlags(&c.s, hipStreamNonBlocking);
+  if (e == hipSuccess) e = make_side_stream(&c.side);
+  if (e == hipSuccess) e = hipStreamBeginCapture(c.s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hip_fail(e);
-  hipGraph_t graph = nullptr;
-  e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-  if (e == hipSuccess) {
-    rc = batched_iterations(inst, count, n_iter, L, w, geo, ws, false, cs);
-    e = hipStreamEndCapture(cs, &graph);
-  }
-  (void)hipStreamDestroy(cs);
-  if (rc) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return rc;
-  }
+  rc = batched_iterations(inst, count, n_iter, L, w, geo, ws, &c.side, c.s);
+  e = hipStreamEndCapture(c.s, &c.graph);
+  if (rc) return rc;
   if (e != hipSuccess) return hip_fail(e);
   hipGraphExec_t exec = nullptr;
-  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(graph);
+  e = hipGraphInstantiate(&exec, c.graph, nullptr, nullptr, 0);
   if (e != hipSuccess) return hip_fail(e);
   jpet_batched_graph* gr = new (std::nothrow) jpet_batched_graph;
   if (!gr) {

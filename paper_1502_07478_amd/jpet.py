@@ -490,14 +490,16 @@ class BatchedMLEM:
         _check(_lib().jpet_mlem_batched_graph_launch(h, _stream(stream)), "jpet_mlem_batched_graph_launch")
 
     def close_graphs(self):
+        """Releases the captured graphs, once their launches have ended (a graph that is executing must not be
+        destroyed)."""
+        if self._graphs:
+            torch.cuda.synchronize(self.ws.device)
         for h in self._graphs.values():
             _lib().jpet_mlem_batched_graph_destroy(h)
         self._graphs = {}
 
     def __del__(self):
         try:
-            if self._graphs:
-                torch.cuda.synchronize()
             self.close_graphs()
         except Exception:
             pass

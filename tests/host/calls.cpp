@@ -4,15 +4,19 @@
 //
 //   calls CALL R L sigma_z sigma_dl pixel n_y n_z n plan [; R L ... ]     (a batch: several geometries)
 //
-// CALL: iterate, denominators, loglik, value, noalloc, batch (eager), graph (created, launched, destroyed).
+// CALL: iterate, denominators, loglik, value, noalloc, batch (eager), graph (created, launched, destroyed), mixed
+// (eager, graph created, eager, graph launched and destroyed), threads (two threads, each eager on its own stream).
 #include <cxxabi.h>
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
+#include <chrono>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "jpet.h"
@@ -34,12 +38,14 @@ static std::string name_of(const void* f) {
   for (size_t at; (at = s.find(' ')) != std::string::npos;) s.erase(at, 1);
   return s;
 }
-static int ids = 0;
+static std::atomic<int> ids{0};
+static thread_local int me = 0;  // the thread's number, in the log of records and waits
+static std::atomic<bool> slow{false};
 static void* fresh() { return (void*)(size_t)(++ids * 16); }
 static long id(const void* p) { return (long)((size_t)p / 16); }
-static dim3 cfg_g, cfg_b;
-static size_t cfg_s;
-static hipStream_t cfg_st;
+static thread_local dim3 cfg_g, cfg_b;
+static thread_local size_t cfg_s;
+static thread_local hipStream_t cfg_st;
 
 extern "C" {
 void** __hipRegisterFatBinary(const void*) {
@@ -101,11 +107,12 @@ hipError_t hipEventDestroy(hipEvent_t e) {
   return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-  printf("record %ld stream %ld\n", id(e), id(s));
+  printf("record %ld stream %ld thread %d\n", id(e), id(s), me);
+  if (slow) std::this_thread::sleep_for(std::chrono::milliseconds(1));  // (lets the other thread come between)
   return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
-  printf("wait %ld stream %ld\n", id(e), id(s));
+  printf("wait %ld stream %ld thread %d\n", id(e), id(s), me);
   return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
@@ -166,6 +173,26 @@ int main(int argc, char** argv) {
       result("launch", jpet_mlem_batched_graph_launch(gr, nullptr));
       result("destroy", jpet_mlem_batched_graph_destroy(gr));
     }
+  } else if (call == "mixed") {
+    const int count = (int)inst.size();
+    if (result("size", jpet_mlem_batched_workspace_size(inst.data(), count, &bytes))) return 0;
+    jpet_batched_graph* gr = nullptr;
+    result("iterate", jpet_mlem_batched_iterate(inst.data(), count, 2, fake, bytes, 0, nullptr, nullptr));
+    if (result("create", jpet_mlem_batched_graph_create(inst.data(), count, 2, fake, bytes, 0, nullptr, &gr))) return 0;
+    result("again", jpet_mlem_batched_iterate(inst.data(), count, 2, fake, bytes, 0, nullptr, nullptr));
+    result("launch", jpet_mlem_batched_graph_launch(gr, nullptr));
+    result("destroy", jpet_mlem_batched_graph_destroy(gr));
+  } else if (call == "threads") {
+    const int count = (int)inst.size();
+    if (result("size", jpet_mlem_batched_workspace_size(inst.data(), count, &bytes))) return 0;
+    slow = true;
+    std::vector<std::thread> team;
+    for (int k = 1; k <= 2; ++k)
+      team.emplace_back([&, k] {
+        me = k;
+        jpet_mlem_batched_iterate(inst.data(), count, 20, fake, bytes, 0, nullptr, (hipStream_t)(size_t)(16000 * k));
+      });
+    for (std::thread& t : team) t.join();
   } else if (call == "iterate") {
     if (result("size", jpet_mlem_workspace_size(&one.g, one.n, &bytes))) return 0;
     result("iterate", jpet_mlem_iterate(&one.g, fake, one.n, nullptr, fake, 2, fake, bytes, 0, nullptr, nullptr));

@@ -34,7 +34,7 @@ def calls(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("host") / "calls")
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
-                    "-I", os.path.join(rocm, "include"), os.path.join(ROOT, "tests", "host", "calls.cpp"), "-rdynamic",
+                    "-I", os.path.join(rocm, "include"), "-pthread", os.path.join(ROOT, "tests", "host", "calls.cpp"), "-rdynamic",
                     lib, f"-Wl,-rpath,{os.path.dirname(lib)}", f"-Wl,-rpath-link,{rocm}/lib", "-o", exe], check=True)
 
     def run(call, *geometries):
@@ -167,3 +167,74 @@ def test_noalloc_takes_what_fits_on_batches_of_rows(calls, geo):
         assert codes(log)["noalloc"] == 0, (n, plan)
         limits_hold(log)
     assert codes(calls("noalloc", (sz, sdl, pixel, n_y, n_z, 20_000_000, 0, float(R), float(L))))["noalloc"] == jpet.JPET_EWORKSPACE
+
+
+TWO_CLASSES = ((10.0, 63.0, 2.0, 200, 200, 50_000, 0), (4.0, 20.0, 2.0, 100, 100, 4_000, 0))
+
+
+def test_a_capture_has_its_streams_and_events_to_itself(calls):
+    """Streams and events of a graph's capture are made for it, used by nothing else and kept until the graph is
+    instantiated: work that another call enqueued on them would become part of the graph."""
+    log = calls("mixed", *TWO_CLASSES)
+    assert set(codes(log).values()) == {0}
+    at = {key: next(k for k, line in enumerate(log) if line[0] == key) for key in ("capture+", "capture-", "instantiate")}
+    start = max(k for k, line in enumerate(log[:at["capture+"]]) if line[0] == "launch") + 1  # the batch's set-up ends
+
+    def used(lines):
+        streams = {line[line.index("stream") + 1] for line in lines if "stream" in line}
+        return streams, {line[1] for line in lines if line[0] in ("record", "wait")}
+
+    inside = used(log[at["capture+"]:at["capture-"] + 1])
+    made = log[start:at["capture+"]]
+    assert len(inside[0]) == 2 and len(inside[1]) == 2
+    assert inside[0] == {line[1] for line in made if line[0] == "stream+"}
+    assert inside[1] == {line[1] for line in made if line[0] == "event+"}
+    outside = used(log[:start] + log[at["capture-"] + 1:])
+    assert not inside[0] & outside[0] and not inside[1] & outside[1]
+    for line in log[:at["instantiate"]]:
+        assert line[0] not in ("stream-", "event-")
+    gone = log[at["instantiate"]:]
+    assert inside[0] == {line[1] for line in gone if line[0] == "stream-"}
+    assert inside[1] == {line[1] for line in gone if line[0] == "event-"}
+
+
+def test_threads_do_not_mix_their_forks_and_joins(calls):
+    """Eager batches of two threads share the side stream and its events: a wait takes an event's latest record, so
+    between one thread's record and its wait the other records nothing."""
+    log = [line for line in calls("threads", *TWO_CLASSES) if line[0] in ("record", "wait")]
+    assert {line[-1] for line in log} == {"1", "2"}
+    latest = {}
+    for line in log:
+        if line[0] == "record":
+            latest[line[1]] = line[-1]
+        else:
+            assert latest[line[1]] == line[-1], line
+
+
+def test_graphs_are_closed_after_their_launches(monkeypatch):
+    """A graph that is created again (another number of iterations, or after eager iterations) replaces one whose last
+    launch may still run; destroying it waits for the device first."""
+    import ctypes
+
+    import torch
+    done = []
+
+    class Library:
+        def jpet_mlem_batched_graph_create(self, *a):
+            done.append("create")
+            return 0
+
+        def jpet_mlem_batched_graph_destroy(self, h):
+            done.append("destroy")
+            return 0
+
+    monkeypatch.setattr(jpet, "_lib", lambda: Library())
+    monkeypatch.setattr(jpet, "_stream", lambda stream: None)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a: done.append("wait"))
+    b = jpet.BatchedMLEM.__new__(jpet.BatchedMLEM)
+    b.arr, b.count, b.ws = None, 0, torch.empty(256, dtype=torch.uint8)
+    b._graphs, b._table_of = {2: ctypes.c_void_p(1)}, 2
+    b.graph(3)
+    assert done == ["wait", "destroy", "create"]
+    b.close_graphs()
+    assert done == ["wait", "destroy", "create", "wait", "destroy"]
