@@ -303,7 +303,7 @@ hipError_t launch_loglik(const Geo& g, const Plan& p, int64_t n, const Workspace
   int nparts = 1;
   // the binned pass accumulates B unless the value alone is asked for, the other one where grad_rho is
   double* const B = (p.tiled ? !value_only : grad_rho != nullptr) ? ws.B : nullptr;
-  const int dots = grid_for(npix, 256, kDotBlocks);
+  const int dots = grid_for(D_out && n > npix ? n : npix, 256, kDotBlocks);  // (blocks for the longer of the two)
   hipLaunchKernelGGL(k_loglik_begin, dim3(dots), dim3(256), 0, st, npix, n, rho, s, B, D_out, ws.red, ws.cnt);
   if (p.tiled) {
     const hipError_t e = launch_loglik_tiled(g, p, n, ws, rho, D_out, value_only, st);

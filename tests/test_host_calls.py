@@ -238,3 +238,13 @@ def test_graphs_are_closed_after_their_launches(monkeypatch):
     assert done == ["wait", "destroy", "create"]
     b.close_graphs()
     assert done == ["wait", "destroy", "create", "wait", "destroy"]
+
+
+def test_denominators_of_long_lists_are_cleared_by_many_blocks(calls):
+    """A list of 10M events on a 4 x 4 grid: the launch that clears its denominators (and reads the image) has blocks
+    for the list, not for the 16 pixels alone."""
+    for call in ("loglik", "value"):
+        (name, line), = launches(calls(call, (10.0, 63.0, 4.0, 4, 4, 10_000_000, 0)), "k_loglik_begin")
+        assert int(line[line.index("grid") + 1]) == 256
+    (name, line), = launches(calls("loglik", (10.0, 63.0, 4.0, 4, 4, 300, 0)), "k_loglik_begin")
+    assert int(line[line.index("grid") + 1]) == 2
