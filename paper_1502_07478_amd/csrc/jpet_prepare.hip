@@ -4,6 +4,7 @@
 //   k_prepare      direct reconstruction (Eq. 2), ellipse rows (App. B, Sec. 3), validity; for the binned
 //                  passes each event's bin and its rank in it, for the others the pixel count
 //   k_scan         exclusive prefix sums over the bins of events, workgroup items and batch blocks; the items' order
+//                  (k_scan_sums before it where there are many bins)
 //   k_place        events in bin order, and the workgroup items: (bin, first event, count) with at most
 //                  ev_per_wg events
 //   k_build_rings, k_build_batches   the blocks the passes read, and the pixel count
@@ -183,36 +184,84 @@ __global__ void __launch_bounds__(1024) k_prepare(Geo g, Plan p, const float* __
 // ones fill the chip's last round.  Against rests in the order of the bins, the pass over 375,000 events on
 // 256^2 takes 252 us instead of 295, over 100,000 on 400^2 115 instead of 125, over 10M there 5.98 ms
 // instead of 6.16.  Latency bounds the scan: every block of 1024 bins sums the bins before its own for itself,
-// out of L2, where one block with 100 bins per thread took 155 us for 103,000 of them.
+// out of L2, where one block with 100 bins per thread took 155 us for 103,000 of them.  That is quadratic in the
+// bins, so above kScanBins of them the blocks, at most kScanBlocks of them, read sums that k_scan_sums has formed
+// of each block's bins (the whole preparation of 20,000 events on 1024^2: 46,440 bins 146 us either way, 185,760
+// 248 -> 148, 3.06M 14,330 -> 357; of 100,000 events on 4096^2, 6.6M bins: 64.7 -> 0.63 ms).
+constexpr int kScanBins = 1 << 16, kScanBlocks = 2048;
 constexpr int kRestClasses = 8;
 __device__ inline int rest_class(uint32_t rest, int ev_per_wg) {  // 0: the largest; rest in [1, ev_per_wg)
   return kRestClasses - 1 - (int)(rest * (uint32_t)kRestClasses / (uint32_t)ev_per_wg);
 }
 
-__global__ void __launch_bounds__(1024) k_scan(int nbins, int ev_per_wg, int ev_per_batch,
-                                               const uint32_t* __restrict__ bin_count, uint32_t* __restrict__ bin_start,
-                                               uint32_t* __restrict__ item_start, uint32_t* __restrict__ rest_start,
-                                               uint32_t* __restrict__ batch_start,
+// What a bin adds to the sums: its events, full items and batches, and its rest's class (-1: no rest).
+constexpr int kScanOwn = 3, kScanPer = kScanOwn + kRestClasses;
+struct BinSums {
+  uint32_t own[kScanOwn];
+  int cls;
+  __device__ BinSums(uint32_t c, int ev_per_wg, int ev_per_batch)
+      : own{c, c / ev_per_wg, (c + ev_per_batch - 1) / ev_per_batch},
+        cls(c % ev_per_wg ? rest_class(c % ev_per_wg, ev_per_wg) : -1) {}
+};
+
+// The sums of each block's bins (chunks of 1024), kScanPer words a block.
+__global__ void __launch_bounds__(1024) k_scan_sums(int nbins, int chunks, int ev_per_wg, int ev_per_batch,
+                                                    const uint32_t* __restrict__ bin_count, uint32_t* __restrict__ sums) {
+  __shared__ uint32_t part[kScanPer];
+  if (threadIdx.x < kScanPer) part[threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t v[kScanPer] = {};
+  for (int ch = 0; ch < chunks; ++ch) {
+    const int64_t b = ((int64_t)blockIdx.x * chunks + ch) * 1024 + threadIdx.x;
+    const BinSums s(b < nbins ? bin_count[b] : 0u, ev_per_wg, ev_per_batch);
+    for (int q = 0; q < kScanOwn; ++q) v[q] += s.own[q];
+#pragma unroll
+    for (int q = 0; q < kRestClasses; ++q) v[kScanOwn + q] += s.cls == q ? 1u : 0u;
+  }
+#pragma unroll
+  for (int q = 0; q < kScanPer; ++q) {
+    for (int off = WAVE / 2; off > 0; off >>= 1) v[q] += __shfl_down(v[q], off);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && v[q]) atomicAdd(&part[q], v[q]);
+  }
+  __syncthreads();
+  if (threadIdx.x < kScanPer) sums[(int64_t)blockIdx.x * kScanPer + threadIdx.x] = part[threadIdx.x];
+}
+
+// sums: k_scan_sums's, or null for blocks of one chunk that sum the bins themselves.
+__global__ void __launch_bounds__(1024) k_scan(int nbins, int chunks, int ev_per_wg, int ev_per_batch,
+                                               const uint32_t* __restrict__ bin_count, const uint32_t* __restrict__ sums,
+                                               uint32_t* __restrict__ bin_start, uint32_t* __restrict__ item_start,
+                                               uint32_t* __restrict__ rest_start, uint32_t* __restrict__ batch_start,
                                                unsigned long long* __restrict__ cnt) {
-  constexpr int kBefore = 3, kAll = kBefore + kRestClasses, kSums = kAll + 1 + kRestClasses;
+  constexpr int kBefore = kScanOwn, kAll = kScanPer, kSums = kAll + 1 + kRestClasses;
   // events, full items, batches and the classes' rests of the bins before this block's; full items and the
   // classes' rests of all bins
   __shared__ uint32_t part[kSums][1024 / WAVE], base[kSums];
-  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, first = blockIdx.x * blockDim.x;
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+  const int64_t first = (int64_t)blockIdx.x * chunks * 1024;
   uint32_t v[kSums] = {};
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-    const uint32_t c = bin_count[b], full = c / ev_per_wg, rest = c % ev_per_wg;
-    const int cls = rest ? rest_class(rest, ev_per_wg) : -1;
-    const uint32_t before = b < first ? 1u : 0u;
-    v[0] += before * c;
-    v[1] += before * full;
-    v[2] += before * ((c + ev_per_batch - 1) / ev_per_batch);
-    v[kAll] += full;
+  if (sums) {
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += 1024) {
+      const uint32_t before = k < (int)blockIdx.x ? 1u : 0u;
+      for (int q = 0; q < kScanPer; ++q) {
+        const uint32_t x = sums[(int64_t)k * kScanPer + q];
+        v[q] += before * x;
+        if (q == 1) v[kAll] += x;
+        if (q >= kBefore) v[kAll + 1 + q - kBefore] += x;
+      }
+    }
+  } else {
+    for (int b = threadIdx.x; b < nbins; b += 1024) {
+      const BinSums s(bin_count[b], ev_per_wg, ev_per_batch);
+      const uint32_t before = b < first ? 1u : 0u;
+      for (int q = 0; q < kBefore; ++q) v[q] += before * s.own[q];
+      v[kAll] += s.own[1];
 #pragma unroll
-    for (int q = 0; q < kRestClasses; ++q) {
-      const uint32_t one = cls == q ? 1u : 0u;
-      v[kBefore + q] += before * one;
-      v[kAll + 1 + q] += one;
+      for (int q = 0; q < kRestClasses; ++q) {
+        const uint32_t one = s.cls == q ? 1u : 0u;
+        v[kBefore + q] += before * one;
+        v[kAll + 1 + q] += one;
+      }
     }
   }
 #pragma unroll
@@ -223,53 +272,57 @@ __global__ void __launch_bounds__(1024) k_scan(int nbins, int ev_per_wg, int ev_
   __syncthreads();
   if (threadIdx.x < kSums) {
     uint32_t sum = 0;
-    for (int w = 0; w < (int)blockDim.x / WAVE; ++w) sum += part[threadIdx.x][w];
+    for (int w = 0; w < 1024 / WAVE; ++w) sum += part[threadIdx.x][w];
     base[threadIdx.x] = sum;
   }
   __syncthreads();
-  // this block's own bins: sums over the wavefront's lanes, then over the wavefronts before
-  const int b = first + (int)threadIdx.x;
-  const uint32_t c = b < nbins ? bin_count[b] : 0u, rest = c % ev_per_wg;
-  const int cls = rest ? rest_class(rest, ev_per_wg) : -1;
-  const uint32_t own[kBefore] = {c, c / ev_per_wg, (c + ev_per_batch - 1) / ev_per_batch};
-  uint32_t run[kBefore], rank = 0;
+  // this block's own bins, a chunk at a time: sums over the wavefront's lanes, then over the wavefronts before
+  for (int ch = 0; ch < chunks; ++ch) {
+    const int64_t b = first + (int64_t)ch * 1024 + threadIdx.x;
+    const BinSums s(b < nbins ? bin_count[b] : 0u, ev_per_wg, ev_per_batch);
+    uint32_t run[kBefore], rank = 0;
 #pragma unroll
-  for (int q = 0; q < kBefore; ++q) {
-    run[q] = own[q];
-    for (int off = 1; off < WAVE; off <<= 1) {
-      const uint32_t up = __shfl_up(run[q], off);
-      if (lane >= off) run[q] += up;
+    for (int q = 0; q < kBefore; ++q) {
+      run[q] = s.own[q];
+      for (int off = 1; off < WAVE; off <<= 1) {
+        const uint32_t up = __shfl_up(run[q], off);
+        if (lane >= off) run[q] += up;
+      }
+      if (lane == WAVE - 1) part[q][wave] = run[q];
+      run[q] -= s.own[q];
     }
-    if (lane == WAVE - 1) part[q][wave] = run[q];
-    run[q] -= own[q];
-  }
 #pragma unroll
-  for (int q = 0; q < kRestClasses; ++q) {
-    const unsigned long long in = __ballot(cls == q);
-    if (cls == q) rank = (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
-    if (lane == 0) part[kBefore + q][wave] = (uint32_t)__popcll(in);
-  }
-  __syncthreads();
-  for (int q = 0; q < kBefore; ++q) {
-    run[q] += base[q];
-    for (int w = 0; w < wave; ++w) run[q] += part[q][w];
-  }
-  if (cls >= 0) {
-    rank += base[kAll] + base[kBefore + cls];
-    for (int q = 0; q < cls; ++q) rank += base[kAll + 1 + q];
-    for (int w = 0; w < wave; ++w) rank += part[kBefore + cls][w];
-  }
-  if (b < nbins) {
-    bin_start[b] = run[0];
-    item_start[b] = run[1];
-    batch_start[b] = run[2];
-    rest_start[b] = rank;
-  }
-  if (b == nbins - 1) {
-    bin_start[nbins] = run[0] + own[0];
-    uint32_t items = base[kAll];
-    for (int q = 0; q < kRestClasses; ++q) items += base[kAll + 1 + q];
-    cnt[C_ITEMS] = items;
+    for (int q = 0; q < kRestClasses; ++q) {
+      const unsigned long long in = __ballot(s.cls == q);
+      if (s.cls == q) rank = (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
+      if (lane == 0) part[kBefore + q][wave] = (uint32_t)__popcll(in);
+    }
+    __syncthreads();
+    for (int q = 0; q < kBefore; ++q) {
+      run[q] += base[q];
+      for (int w = 0; w < wave; ++w) run[q] += part[q][w];
+    }
+    if (s.cls >= 0) {
+      rank += base[kAll] + base[kBefore + s.cls];
+      for (int q = 0; q < s.cls; ++q) rank += base[kAll + 1 + q];
+      for (int w = 0; w < wave; ++w) rank += part[kBefore + s.cls][w];
+    }
+    if (b < nbins) {
+      bin_start[b] = run[0];
+      item_start[b] = run[1];
+      batch_start[b] = run[2];
+      rest_start[b] = rank;
+    }
+    if (b == nbins - 1) {
+      bin_start[nbins] = run[0] + s.own[0];
+      uint32_t items = base[kAll];
+      for (int q = 0; q < kRestClasses; ++q) items += base[kAll + 1 + q];
+      cnt[C_ITEMS] = items;
+    }
+    __syncthreads();
+    if (threadIdx.x < kScanPer)
+      for (int w = 0; w < 1024 / WAVE; ++w) base[threadIdx.x] += part[threadIdx.x][w];
+    __syncthreads();
   }
 }
 
@@ -819,8 +872,17 @@ hipError_t launch_prepare(const Geo& g, const Plan& p, const float* events, int6
                          ws.ev, ws.key, ws.rank, ws.bin_count, ws.cnt);
     }
   }
-  hipLaunchKernelGGL(k_scan, dim3(blocks_for(nb, 1024)), dim3(1024), 0, st, p.nbins, p.ev_per_wg, p.ev_per_batch, ws.bin_count,
-                     ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.cnt);
+  // (the sums of many bins lie in ws.B, which only the log-likelihood's pass uses, cleared before; an image too small
+  // for them, of very wide strips, leaves the blocks to sum the bins)
+  const bool many = nb > kScanBins && (int64_t)g.n_y * g.n_z * (int64_t)sizeof(double) >=
+                                          (int64_t)sizeof(uint32_t) * kScanPer * kScanBlocks;
+  uint32_t* const sums = many ? reinterpret_cast<uint32_t*>(ws.B) : nullptr;
+  const int chunks = many ? blocks_for(nb, 1024 * kScanBlocks) : 1, scan = blocks_for(nb, 1024 * chunks);
+  if (many)
+    hipLaunchKernelGGL(k_scan_sums, dim3(scan), dim3(1024), 0, st, p.nbins, chunks, p.ev_per_wg, p.ev_per_batch,
+                       ws.bin_count, sums);
+  hipLaunchKernelGGL(k_scan, dim3(scan), dim3(1024), 0, st, p.nbins, chunks, p.ev_per_wg, p.ev_per_batch, ws.bin_count,
+                     sums, ws.bin_start, ws.item_start, ws.rest_start, ws.batch_start, ws.cnt);
   if (n <= 0) return hipGetLastError();
   hipLaunchKernelGGL(k_place, dim3(blocks_for(n > nb ? n : nb, 256)), dim3(256), 0, st, ws.key, ws.rank, n, p.nbins,
                      p.ev_per_wg, p.ev_per_batch, ws.bin_count, ws.bin_start, ws.item_start, ws.rest_start,

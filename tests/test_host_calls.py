@@ -248,3 +248,15 @@ def test_denominators_of_long_lists_are_cleared_by_many_blocks(calls):
         assert int(line[line.index("grid") + 1]) == 256
     (name, line), = launches(calls("loglik", (10.0, 63.0, 4.0, 4, 4, 300, 0)), "k_loglik_begin")
     assert int(line[line.index("grid") + 1]) == 2
+
+
+def test_scan_of_many_bins_is_not_quadratic(calls):
+    """A fine grid has millions of bins: at most 2048 blocks scan them, from sums of each block's bins."""
+    geo = (1.5, 8.0, 0.2, 4096, 4096, 100_000, 0, 450.0, 1000.0)
+    g = jpet.geometry(R=450.0, L=1000.0, sigma_z=1.5, sigma_dl=8.0, pixel=0.2, n_y=4096, n_z=4096)
+    assert jpet.launch_info(g, 100_000)["bins"] > 2_097_152
+    log = calls("iterate", geo)
+    grids = [int(launches(log, name)[0][1][3]) for name in ("k_scan_sums", "k_scan")]
+    assert grids[0] == grids[1] <= 2048
+    # few bins: no sums
+    assert not launches(calls("iterate", TWO_CLASSES[0]), "k_scan_sums")
