@@ -384,7 +384,8 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
     // derivative sums), and the allocation granule: measured on gfx950, three workgroups of 51,984
     // bytes each run on one CU but three of 54,032 bytes do not (the pass then runs 27% slower), so
     // a workgroup's LDS is counted in whole 2 KB granules.
-    const size_t kLdsPerCU = 160 * 1024, kStatic = loglik ? 3 * 1024 : 1024, kGranule = 2048;
+    constexpr size_t kLdsPerCU = 160 * 1024, kGranule = 2048;
+    const size_t kStatic = loglik ? 3 * 1024 : 1024;
     const double pairs_per_event = 3.14159265358979323846 * hy_px * (3.0 * msz / sqrt(2.0) / pix);
     const double nn = (double)(n > 0 ? n : 1);
     for (int waves : {8, 16}) {
@@ -449,6 +450,7 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 const int slack = ring_slack(shape, HZ, dt == 0.0 ? tmax : 0.5 * dt, hy_px);
                 const int item = ring_item_events(n, pairs_per_event, RY, W, shape >= 1000 ? 1 : 2, each, row_item, acc32 != 0);
                 const size_t lds = ring_lds_layout(pitch, W, RY, each, shape >= 1000 ? 1 : 2, slack, item, loglik).bytes;
+                static_assert(kLdsPerCU - 256 == (size_t)kRingLdsLimit, "one workgroup of a CU stays within its limit");
                 if (lds <= kLdsPerCU / (size_t)fit / kGranule * kGranule - 256) {
                   p.rings = shape_rings(shape);
                   p.solo = shape >= 1000;

@@ -206,6 +206,11 @@ constexpr int shape_pitch(int shape, int which) {
   const int first = rows <= 64 ? 64 : rows <= 128 ? 128 : rows <= 192 ? 192 : 256;
   return first + 64 * which;
 }
+// Dynamic LDS that a kernel may be launched with, raised to the same value by every call: a limit of the call's own
+// need would be lowered by another thread's call between this one's limit and its launch.  (The passes on ring
+// blocks keep 256 bytes of the CU's 160 KB for their static variables.)
+constexpr int kRingLdsLimit = 160 * 1024 - 256, kPrepareLdsLimit = 144 * 1024;
+
 // The event pass's kernel as a number (a batch's classes): the register cache of the pass on batches of
 // rows, or 10000 + the shape.
 inline int pass_kernel(const Plan& p) {

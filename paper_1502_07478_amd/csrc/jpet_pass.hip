@@ -210,7 +210,7 @@ hipError_t set_batched_lds(int kernel, int waves, int pitch, size_t lds_bytes) {
   return by_kernel(kernel, [&](auto b) {
     const void* f = b.batched_kernel(waves, pitch);
     if (!f) return hipErrorInvalidValue;  // not compiled for this pitch
-    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kernel > 10000 ? kRingLdsLimit : (int)lds_bytes);
   });
 }
 

@@ -861,9 +861,9 @@ hipError_t launch_prepare(const Geo& g, const Plan& p, const float* events, int6
     // per event (else the counts are few, and clearing and adding them costs more)
     const int per = (int)std::min<int64_t>(32, std::max<int64_t>(1, n / (1024 * 256)));
     const size_t lds = sizeof(uint32_t) * (size_t)nb;
-    if (lds <= 144 * 1024 && nb <= 8 * 1024 * per) {
+    if (lds <= (size_t)kPrepareLdsLimit && nb <= 8 * 1024 * per) {
       const hipError_t e = hipFuncSetAttribute((const void*)k_prepare<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds);
+                                               kPrepareLdsLimit);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(k_prepare<true>, dim3(blocks_for(n, 1024 * per)), dim3(1024), lds, st, g, p, events, n, per,
                          ws.ev, ws.key, ws.rank, ws.bin_count, ws.cnt);

@@ -433,7 +433,7 @@ hipError_t Rings<SHAPE>::event_pass(const Geo& g, const Plan& p, const Workspace
                                          : k_event_pass_rings<SHAPE, kFirst, false>)
                                 : (D_out ? k_event_pass_rings<SHAPE, kSecond, true>
                                          : k_event_pass_rings<SHAPE, kSecond, false>);
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
+  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsLimit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), p.lds_bytes, st, g, p, ws.batches,
                      ws.items, rho, ws.acc, ws.cnt, D_out);

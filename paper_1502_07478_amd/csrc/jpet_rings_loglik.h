@@ -483,7 +483,7 @@ hipError_t Rings<SHAPE>::loglik(const Geo& g, const Plan& p, const Workspace& ws
   if (p.pitch != shape_pitch(SHAPE, 0) && p.pitch != shape_pitch(SHAPE, 1)) return hipErrorInvalidValue;
   auto kern = p.pitch == shape_pitch(SHAPE, 0) ? k_loglik_rings<SHAPE, shape_pitch(SHAPE, 0)>
                                                : k_loglik_rings<SHAPE, shape_pitch(SHAPE, 1)>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
+  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsLimit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), p.lds_bytes, st, g, p, ws.batches,
                      ws.items, rho, ws.B, D_out, ws.red, ws.cnt, ws.order);

@@ -29,7 +29,7 @@ hipError_t launch_loglik_rings_value(const Geo& g, const Plan& p, const Workspac
                                        : k_loglik_rings_value<3, false>);
   // the image alone, with the slack after it
   const size_t lds = (size_t)p.lds_img + 4u * (size_t)p.pitch * (size_t)(p.W + p.slack);
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsLimit);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.max_items), dim3(64 * p.waves), lds, st, g, p, ws.batches, ws.items, rho,
                      D_out, ws.red, ws.cnt, ws.order);

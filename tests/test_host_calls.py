@@ -260,3 +260,27 @@ def test_scan_of_many_bins_is_not_quadratic(calls):
     assert grids[0] == grids[1] <= 2048
     # few bins: no sums
     assert not launches(calls("iterate", TWO_CLASSES[0]), "k_scan_sums")
+
+
+def test_limits_do_not_depend_on_the_call(calls):
+    """A kernel's limit of dynamic LDS is process-wide: were it each call's own need, two threads could lower it under
+    each other's launches.  The preparation and the passes on ring blocks, small plans and large ones."""
+    limits = {}
+    for shape in (112, 322, 1344):
+        sz, sdl = resolution(shape)
+        for grid in (30, 400):
+            n = 140_000
+            g = jpet.geometry(R=450.0, L=500.0, sigma_z=sz, sigma_dl=sdl, pixel=PIXEL, n_y=grid, n_z=grid)
+            plans = [c for c, _ in jpet.plan_candidates(g, n) if c & 4 and c >> 12 == 0]
+            for plan in (plans[0], plans[-1]):
+                geo = (sz, sdl, PIXEL, grid, grid, n, plan)
+                for call in ("iterate", "denominators", "batch"):
+                    for line in calls(call, geo):
+                        if line[0] == "limit" and ("rings" in line[1] or "prepare" in line[1]):
+                            limits.setdefault(line[1], set()).add(int(line[3]))
+            for call in ("loglik", "value"):
+                for line in calls(call, geo[:-1] + (0,)):
+                    if line[0] == "limit" and ("rings" in line[1] or "prepare" in line[1]):
+                        limits.setdefault(line[1], set()).add(int(line[3]))
+    assert "k_prepare<true>" in limits and len(limits) > 8
+    assert all(len(v) == 1 for v in limits.values()), limits
