@@ -247,6 +247,10 @@ static int ring_item_events(int64_t n, double pairs_per_event, int RY, int W, in
   return (int)(per / epb * epb);
 }
 
+// Bins of a plan, at most: they are counted and indexed in 32 bits (32768^2 pixels in tiles of 8 and 89 t bins have
+// 3.1e9).
+constexpr int64_t kMaxBins = 2147480000;
+
 // Columns of the grid in the sheared frame of a plan's t bins: the widest over them.
 static int sheared_span(const jpet_geometry* g, const Plan& p) {
   const double pix = g->pixel;
@@ -440,6 +444,7 @@ static void enumerate_plans(const jpet_geometry* g, double msz, double mdl, int6
                 p.tmin = -0.5 * dt * p.ntb;
               }
               if (span[dti] == 0) span[dti] = sheared_span(g, p);
+              if ((int64_t)p.ntb * ((g->n_y + T - 1) / T) * ((span[dti] + T - 1) / T) > kMaxBins) continue;
               const Plan rows = p;
               // ring blocks where a cache holds a whole event's rows and the LDS still lets as many
               // wavefronts run as the registers do (that many, shared by the workgroups of the code)

@@ -1,4 +1,4 @@
-"""The units of the 32-bit accumulators (host code, no GPU): a plan is chosen for its speed, never at the
+"""Plans (host code, no GPU).  The units of the 32-bit accumulators: a plan is chosen for its speed, never at the
 price of coarser units than batches of rows give the same call.
 
 UNITS holds, for a geometry and a number of events, the power of two a count was divided by when every plan
@@ -69,3 +69,18 @@ def test_named_plans_keep_their_units(geo):
             item = min(max(n // 1024, per_batch), 511) // per_batch * per_batch
             assert unit_of(info) >= 32 - item.bit_length(), (n, code)
             assert info["events_per_workgroup"] < 2 ** (32 - unit_of(info)), (n, code)
+
+
+@pytest.mark.parametrize("n", [1, 100_000, 3_000_000])
+def test_bins_of_the_finest_grids_are_counted(n):
+    """32768 x 32768 pixels: a plan of more bins than 32 bits count has a negative number of them, and a workspace
+    whose parts overlap."""
+    for pixel, sz, sdl in ((0.025, 0.2, 1.0), (0.027, 0.05, 0.3)):
+        g = jpet.geometry(R=450.0, L=1000.0, sigma_z=sz, sigma_dl=sdl, pixel=pixel, n_y=32768, n_z=32768)
+        for code, _ in jpet.plan_candidates(g, n):
+            named = jpet.with_plan(g, code)
+            info = jpet.launch_info(named, n)
+            rows, cols = -(-32768 // info["tile_rows"]), -(-32768 // info["tile_cols"])
+            assert info["bins"] >= info["t_bins"] * rows * cols
+            # the accumulators and the log-likelihood's image, and five words a bin
+            assert jpet.workspace_size(named, n) > 16 * 32768 ** 2 + 16 * info["bins"]
