@@ -320,9 +320,10 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
       });
       double Dlo, Dhi;
       const double De = event_sum(D, Dlo, Dhi);  // the event's denominator
-      // (a unit / D overflows a float only for D < 1e-28: such blocks take the way below)
-      const float flo = (float)Dlo, fhi = (float)Dhi;
-      if (!(flo > 0.0f && flo < tiny) && !(fhi > 0.0f && fhi < tiny)) {  // wavefront-uniform
+      // (a unit / D overflows a float only for D < 1e-28, its reciprocal vanishes above 2^126, and rows without their
+      // factor F overflow first: such blocks take the way below)
+      auto plain = [&](float v) { return v <= 0.0f || (v >= tiny && v <= 0x1p126f); };
+      if (plain((float)Dlo) && plain((float)Dhi)) {  // wavefront-uniform
         if (l == 0) denominator(De);
         if constexpr (FORWARD) continue;
         const float sc = De > 0.0 ? kUnit * __builtin_amdgcn_rcpf((float)De) : 0.0f;
@@ -338,8 +339,8 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
       }
     }
 
-    // pixel by pixel, evaluated in both passes; P rho scaled by 2^64 against overflow of unit / D, and in D too
-    // where the image is scaled down.
+    // pixel by pixel, evaluated in both passes; P rho scaled by 2^64 against overflow of unit / D for D below 1 (P rho
+    // is below D), and in D too where the image is scaled down.
     // (Rolled, and with the constants read again: shared with the way above they would take 26 vector
     // registers through it.)
     asm volatile("" ::: "memory");
@@ -358,13 +359,14 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const double De = event_sum(D, Dlo, Dhi) / up;
     if (l == 0) denominator(De);
     if (FORWARD || !(De > 0.0)) continue;
-    const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / (De * 18446744073709551616.0));
+    const float lift = De < 1.0 ? 18446744073709551616.0f : 1.0f;
+    const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / (De * lift));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
       const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
       for (int j = -r.nl; j < r.nr; ++j) {
         const int px = (r.kc + j) * pitch + r.rl;
-        const float m = exact_at(rk, (float)j + 0.5f, &again) * rho_s[px] * 18446744073709551616.0f;
+        const float m = exact_at(rk, (float)j + 0.5f, &again) * rho_s[px] * lift;
         atomicAdd(&acc_s[px], (unsigned)fmaf(m, sc, 0.5f));
       }
     }

@@ -177,6 +177,8 @@ __device__ __forceinline__ float ring_value(const RowP& p, const float* __restri
   return D0 + D1;
 }
 
+constexpr float kFloatMax = 3.402823466e38f;
+
 struct LogShared {
   unsigned zero, bad;
   double sum[3];
@@ -320,7 +322,11 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
           }
           if (r.nr > 0) D = fmaf(F, S, D);
         });
-        finish(event_sum_d(D), 0.0f, 0.0f);
+        const double De = event_sum_d(D);
+        if (!__any(!(De < kFloatMax))) {
+          finish(De, 0.0f, 0.0f);
+          continue;
+        }
       } else {
         RingCache<RINGS, LEN> cache;
         float F[RINGS];
@@ -356,22 +362,27 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
           }
         });
         const double De = event_sum_d(D);
-        finish(De, event_sum(Du), event_sum(Dw));
-        const float invD = De > 0.0 ? (float)(1.0 / De) : 0.0f;
-        each_ring<0, RINGS>([&](auto kk) {
-          constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
-          const uint32_t tw = tail(k);
-          const int wlh = (int)((tw & 127u) + 1) >> 1, wminh = (int)((tw >> 7) & 127u) >> 1;
-          const RingRow r = row(k, H);
-          if (r.nr > 0 && invD > 0.0f)
-            ring_back_f64<H>(cache.template ring<k>(), F[k] * invD, acc_s + (r.kc - H) * pitch + r.rl, pitch, r.nl,
-                             r.nr, wminh, wlh);
-        });
+        Du = event_sum(Du);
+        Dw = event_sum(Dw);
+        if (!__any(!(De < kFloatMax && fabsf(Du) < kFloatMax && fabsf(Dw) < kFloatMax))) {
+          finish(De, Du, Dw);
+          const float invD = De > 0.0 ? (float)(1.0 / De) : 0.0f;
+          each_ring<0, RINGS>([&](auto kk) {
+            constexpr int k = kk, H = ring_half_of(RINGS, LEN, k);
+            const uint32_t tw = tail(k);
+            const int wlh = (int)((tw & 127u) + 1) >> 1, wminh = (int)((tw >> 7) & 127u) >> 1;
+            const RingRow r = row(k, H);
+            if (r.nr > 0 && invD > 0.0f)
+              ring_back_f64<H>(cache.template ring<k>(), F[k] * invD, acc_s + (r.kc - H) * pitch + r.rl, pitch, r.nl,
+                               r.nr, wminh, wlh);
+          });
+          continue;
+        }
       }
-      continue;
     }
 
-    // pixel by pixel, evaluated in both passes
+    // pixel by pixel, evaluated in both passes: rows that need it, and images so large that the sums without their
+    // factor F, or the moments, overflow
     asm volatile("" ::: "memory");
     float D = 0.0f, Du = 0.0f, Dw = 0.0f;
     int nbad = 0, again = 0;
