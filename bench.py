@@ -23,11 +23,12 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# VALU issue slots of the event pass per (event, in-ellipse pixel) pair, the minimal instruction
-# stream: the exponent's polynomial along the row (6 FMAs or multiplies for the two pixels at +-x: 3),
-# v_exp_f32 at half the FMA rate (2), m = P rho and D += m (2), the back-projection's scale, whose
-# bits are the fixed-point addend (1).
-SLOTS_PER_PAIR = 8
+# (event, in-ellipse pixel) pairs per second of the event pass's own arithmetic with nothing beside it: the
+# exponent's polynomial along the row (6 FMAs or multiplications for the two pixels at +-x), v_exp_f32, m = P rho
+# and D += m, the back-projection's scale, whose bits are the fixed-point addend.  Measured by the microbenchmark
+# (profiles/microbench_rates.md): the classes of VALU instructions run at rates of their own, from 19e12
+# lanes a second (v_exp_f32) to 64e12 (v_add_f32), so no count of issue slots bounds a mix of them.
+PEAK_PAIRS = 5.36e12
 # HBM bytes per event pass, from rocprofv3 FETCH_SIZE and WRITE_SIZE counters scaled by what the same
 # counters read for a 256 MiB device copy, keyed by the hash of the kernel sources they were taken
 # on and the plan code (reported only while both are unchanged).
@@ -51,9 +52,6 @@ def kernel_source_hash() -> str:
     return h.hexdigest()[:16]
 
 
-# 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: FP32 VALU lane-instructions per second (one FMA each;
-# the packed-FP32 forms, which would double FMA throughput, are not generated by this build)
-PEAK_SLOTS = 256 * 4 * 16 * 2.4e9
 # Floating-point operations per pair of the kernel evaluation, forward sum and back-projection: 8.5
 # FLOP (FMA = 2) and the transcendental counted as one; priced against the published FP32 vector peak
 # of the MI355X (157.3 TFLOP/s, which counts packed FP32)
@@ -446,19 +444,19 @@ def main():
     ms_per_step = elapsed * 1e3 / args.steps
     value = len(ev_np) * w.n_iter * args.steps / elapsed
     avg_pass_s = pass_ms / 1e3 / max(launches, 1)
-    achieved = n_pairs * SLOTS_PER_PAIR / avg_pass_s
+    achieved = n_pairs / avg_pass_s
     roofline = {
         "bound": "alu",
         "achieved": round(achieved / 1e12, 3),
-        "peak": round(PEAK_SLOTS / 1e12, 3),
-        "unit": "T VALU-slot/s",
-        "frac": round(achieved / PEAK_SLOTS, 4),
+        "peak": round(PEAK_PAIRS / 1e12, 3),
+        "unit": "T pairs/s",
+        "frac": round(achieved / PEAK_PAIRS, 4),
         "traffic": MEASURED_TRAFFIC.get(f"{kernel_source_hash()}:{g.plan}"),
         "kernel": "k_event_pass_rings",
         "avg_launch_ms": round(avg_pass_s * 1e3, 4),
         "launches": launches,
         "pairs_per_launch": n_pairs,
-        "slots_per_pair": SLOTS_PER_PAIR,
+        "peak_source": "the pass's arithmetic per pair alone, without LDS, row set-up, masks or idle lanes (microbench)",
         "traffic_source": "rocprofv3 FETCH_SIZE + WRITE_SIZE of these kernel sources and plan, scaled by a device "
                           "copy (profiles/); null when either differs",
         "flops_per_pair": FLOPS_PER_PAIR,

@@ -243,7 +243,8 @@ int jpet_loglik_grad(const jpet_geometry* g, const double* sigma_mask, const flo
  * instances, the items in order of decreasing size.  The classes are shared by the caller's stream
  * and a second stream of the library's (one per device, default priority, created by the first
  * batched call and kept until the process ends), forked from and joined back into the caller's
- * stream within each iteration, so one class's last workgroups overlap another's work.  Instances
+ * stream within each iteration, so one class's last workgroups overlap another's work; calls of several
+ * threads share it and take turns at each iteration's launches.  Instances
  * that fit only the generic pass get their own launches.  A plan named in an instance's jpet_geometry.plan must be one the batched pass can run:
  * 32-bit accumulators (else JPET_EDOMAIN); plan 0 takes the cost model's cheapest such plan.  Each instance's result is that of jpet_mlem_iterate on it
  * alone with the same plan, to FP32 rounding of the denominators.
@@ -273,7 +274,8 @@ int jpet_mlem_batched_iterate(const jpet_instance* inst, int32_t count, int32_t 
 /* The same n_iter iterations captured once into a HIP graph (a reset, the batched passes, any
  * generic passes and the update per iteration, all kernels), for repeated launches with no host
  * work.  Creating the graph prepares the instances (unless JPET_WS_PREPARED) and writes the batch's
- * instance table and work list into the workspace on stream, in stream order, before capturing;
+ * instance table and work list into the workspace on stream, in stream order, before capturing (on
+ * streams of this call's own, gone when it returns);
  * each launch then runs n_iter iterations on the images as they are at that point in the stream.
  * The instance array's device pointers, the workspace and the event lists must stay valid and
  * unchanged while the graph exists; a later jpet_mlem_batched_iterate or a graph of another

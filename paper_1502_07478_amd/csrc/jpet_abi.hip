@@ -206,9 +206,9 @@ static int ring_slack(int shape, int HZ, double slope, double hy_px) {
   return slack;
 }
 
-// Pairs of all events per pixel of the region below which a pass takes half as many items (measured at
-// 64 x 64 pixels, 20,000 events: 16 us for the pass instead of 22; at 128 x 128 and 48,000 events both
-// take 17 us, above that the larger items leave the last round of workgroups emptier).
+// Pairs of all events per pixel of the region below which a pass takes half as many items, as far as their units allow
+// (measured at 64 x 64 pixels, 20,000 events, without that limit: 16 us for the pass instead of 22; at 128 x 128 and
+// 48,000 events both take 17 us, above that the larger items leave the last round of workgroups emptier).
 constexpr double kItemPairs = 7000.0;
 
 // Events per workgroup item on batches of rows of epb events: enough items to fill the chip, at most 128
@@ -234,7 +234,8 @@ static int plan_unit(const Plan& p) { return p.tiled && p.acc32 ? p.acc_shift : 
 
 // Events per workgroup item on ring blocks of epb events: where a workgroup's share of the events is worth less
 // than staging and flushing the region, fewer and larger items; a block for every wavefront, two where that
-// leaves an item for every CU.  (Below some 16,000 events the region's staging and flush are most of an item.)
+// leaves an item for every CU.  (Below some 16,000 events the region's staging and flush are most of an item: five
+// iterations of 3,000 events on 400^2 take 164 us, of 20,000 483, in items of 14; 595 and 2586 on batches of rows.)
 // With 32-bit accumulators never more events than the units on batches of rows (row_item) allow: larger items
 // would hold the image in coarser units, and a pixel that little reaches (a column beside the strips' ends) shows
 // their rounding, ten iterations of it amplified (10 iterations of 264,253 events on 256^2: relative L2 to exact

@@ -90,14 +90,14 @@ constexpr uint32_t kWordCol = 0, kWordRow = 8, kWordLen = 17, kWordEv = 24;
 // A batch block: ev_per_batch per-event constants (EvRow for the MLEM pass, EvConst for the
 // log-likelihood pass), then one thread word per thread of the workgroup, then two words per
 // wavefront:
-//   its longest row (pixels, bits 0-6) and, from bit kModeShift, how its rows' kernel is evaluated:
-//   kRowPoly5 or kRowPoly6 as the exponential of a polynomial of that degree, kRowExact pixel by
-//   pixel with the kappa <= 0 test (log-likelihood pass: kRowExact where a row may reach kappa <= 0,
-//   else 0);
+//   its longest row (pixels, bits 0-6) and, from bit kModeShift, kRowExact where one of its rows may reach
+//   kappa <= 0 and its pixels need the test, else 0;
 //   its shortest non-empty row (bits 0-7) and, with bit kHalfBit set, the one event of each
 //   half-wavefront's rows: lanes 0-31 in bits 8-12, lanes 32-63 in bits 16-20 (a half with no rows
 //   names the other half's event).
 constexpr int kBlockTailWords = 2;
+// How a ring block's rows are evaluated: as the exponential of a polynomial of degree 5 or 6, or pixel by pixel
+// with the kappa <= 0 test.
 constexpr uint32_t kModeShift = 30, kRowPoly5 = 0, kRowPoly6 = 1, kRowExact = 2;
 constexpr uint32_t kHalfBit = 31, kHalfLo = 8, kHalfHi = 16;
 
@@ -188,12 +188,15 @@ constexpr int kRingShapes[] = {108,  112,  116,  124,  210,  214,  218,  222,  2
                                1318, 1324, 1332, 1344, 1354, 1364, 1420, 1428, 1440, 1454};
 constexpr int shape_rings(int shape) { return shape % 1000 / 100; }
 constexpr int shape_len(int shape) { return shape % 100; }
-// Wavefronts per SIMD a shape is compiled for: the cache and some 50 registers beside it fit the 64, 80,
-// 128, 168 or 256 registers that leaves.
+// Wavefronts per SIMD a shape is compiled for, which leave 64, 80, 128, 168 or 256 registers for the cache and what
+// the passes need beside it: 45 to 60 registers, in the log-likelihood 70 to 80.  Where that is a few more than are
+// left the compiler spills: the event pass of 218, 326 and 1420 (2 registers), of 1344 (10; the 5 mm detector at
+// 0.5 mm pixels); batched also of 116, 1216 (2, 4) and 218 (22); the log-likelihood of 116, 1318, 1332, 1364 (1 to 4),
+// of 318 (12; sigma = (10, 63) at 2.5 mm pixels) and of 1454 (103).
 constexpr int shape_waves_per_simd(int shape, bool loglik = false) {
   int cache = 0;
   for (int k = 0; k < shape_rings(shape); ++k) cache += 2 * ring_half_of(shape_rings(shape), shape_len(shape), k);
-  if (loglik) return cache <= 16 ? 6 : cache <= 52 ? 4 : cache <= 100 ? 3 : 2;  // (some 70 registers beside it)
+  if (loglik) return cache <= 16 ? 6 : cache <= 52 ? 4 : cache <= 100 ? 3 : 2;
   return cache <= 16 ? 8 : cache <= 34 ? 6 : cache <= 72 ? 4 : cache <= 120 ? 3 : 2;
 }
 constexpr int shape_threads(int shape, bool loglik = false) {

@@ -51,11 +51,11 @@ struct RingShared {
 // denominators need not: they carry kappa^-1/2, about sigma_z / (R sqrt 2).  Blocks with one below kBitsTiny,
 // where 1 / D would leave the range, go pixel by pixel, with the image scaled up again.  Other
 // images, and items of units finer than 2^-24 (fewer than 128 events), convert.  Ten iterations of 10M events on
-// 400^2: 58.8 -> 57.7 ms, on 64 x 76: 21.9 -> 21.0.
+// 400^2: 59.6 -> 58.5 ms, on 64 x 76: 22.3 -> 22.1.
 constexpr int kBitsScale = 44, kBitsShift = 24;
 constexpr float kBitsTiny = 0x1p-120f;
 
-// Pass 1 along a lane's row of one ring (see pass1_poly in jpet_binned.h): chunks below the
+// Pass 1 along a lane's row of one ring: chunks below the
 // wavefront's shortest row without masks, the others with the reads past the row's ends discarded
 // (they stay inside the workgroup's LDS: the plan leaves H columns before the image and after the
 // accumulators).
@@ -182,7 +182,8 @@ struct RingCache {
 // wavefront two buffers of a block's constants (the next block's are copied in while this one runs),
 // the column shift of every region row, then from p.lds_img the image and the accumulators, with
 // p.slack columns free before and after them that masked reads and additions of 0 may touch.  FORWARD:
-// the forward sums alone, to D_out (778k events on 400^2: 553 -> 425 us with the back-projection left out).
+// the forward sums alone, to D_out (778k events on 400^2: 553 -> 425 us with the back-projection left out; 440 since
+// the lanes' sums are added in double precision).
 template <int RINGS, int LEN, bool SOLO, int PITCH, bool FORWARD = false>
 __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const unsigned char* __restrict__ blocks,
                                           const BinItem it, const float* __restrict__ rho,

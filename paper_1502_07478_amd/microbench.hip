@@ -1,7 +1,9 @@
-// Throughput of the instruction classes the event pass is built from, on one GPU: FP32 FMA, the
-// v_exp_f32 / v_rsq_f32 transcendentals alone and mixed with FMAs, LDS atomics of each width, and
-// global 32-bit float atomics.  These rates are the slot costs of the pass's
-// roofline (an FMA is one VALU issue slot; a transcendental, measured here, two).
+// Throughput of the instruction classes the event pass is built from, on one GPU: FP32 FMA,
+// multiplication and addition, the v_exp_f32 / v_rsq_f32 transcendentals alone and mixed with FMAs, LDS
+// atomics of each width, and global 32-bit float atomics; and the rate of the passes' own arithmetic per
+// (event, pixel) pair with nothing beside it (k_pixels), which is the peak of their roofline: the classes
+// run at rates of their own (additions 1.8 times as fast as FMAs with a scalar operand), so no number of
+// issue slots per pair and slots per second bounds a mix of them.
 //
 // Build: hipcc -O3 --offload-arch=gfx950 -Xclang -target-feature -Xclang -packed-fp32-ops
 //        -o microbench microbench.hip       (paper_1502_07478_amd/build.py does this)
@@ -75,6 +77,68 @@ __global__ void k_mix(float* out, float a, float b) {
   out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
+// eight independent chains of additions (ADD) or multiplications, operands in vector registers
+template <bool ADD>
+__global__ void k_one(float* out, float a) {
+  float x[8];
+  for (int j = 0; j < 8; ++j) x[j] = threadIdx.x * 1e-3f + j;
+  float v = a + threadIdx.x * 1e-9f;
+  for (int i = 0; i < kIt; ++i) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = ADD ? x[j] + v : x[j] * v;
+  }
+  float s = 0;
+  for (int j = 0; j < 8; ++j) s += x[j];
+  out[blockIdx.x * blockDim.x + threadIdx.x] = s;
+}
+
+// The arithmetic of the pass on ring blocks along a row of 2 H pixels, with nothing beside it (no image or
+// accumulators in LDS, no row set-up, masks, reductions or idle lanes).  PASS 0: the event pass (exponent of
+// x^5, v_exp_f32, P rho, its sum, the back-projection's multiplication); 1: the forward sums alone; 2: the
+// log-likelihood (the moments up to x^5, the back-projection in doubles).
+constexpr int kRows = 512;
+__device__ __forceinline__ float unknown(float v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+template <int PASS, int H, int WAVES>
+__global__ void __launch_bounds__(256, WAVES) k_pixels(float* out, float c0) {
+  float c1 = c0 + threadIdx.x * 1e-6f, c2 = -c0, c3 = c0 * 0.1f, c4 = c0 * 0.01f, c5 = c0 * 0.001f;
+  float rho = 1.0f + threadIdx.x * 1e-3f, sc = c0, sum[6] = {};
+  for (int i = 0; i < kRows; ++i) {
+    c1 = unknown(c1), c2 = unknown(c2), c3 = unknown(c3), c4 = unknown(c4), c5 = unknown(c5), rho = unknown(rho);
+    float m[2 * H];
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      const float x = q + 0.5f, X = x * x;
+      float ev = fmaf(c4, X, c2);
+      ev *= X;
+      const float od = fmaf(fmaf(c5, X, c3), X, c1);
+      const float lo = __builtin_amdgcn_exp2f(fmaf(od, -x, ev)), hi = __builtin_amdgcn_exp2f(fmaf(od, x, ev));
+      if (PASS == 2) {
+        m[2 * q] = lo, m[2 * q + 1] = hi;
+        const float a = lo * rho, b = hi * rho, s = b + a, d = b - a;
+        sum[0] += s;
+        sum[1] = fmaf(d, x, sum[1]);
+        sum[2] = fmaf(s, X, sum[2]);
+        sum[3] = fmaf(d, x * X, sum[3]);
+        sum[4] = fmaf(s, X * X, sum[4]);
+        sum[5] = fmaf(d, x * X * X, sum[5]);
+      } else {
+        sum[0] += m[2 * q] = lo * rho;
+        sum[1] += m[2 * q + 1] = hi * rho;
+      }
+    }
+    sc = unknown(sc);
+#pragma unroll
+    for (int q = 0; q < 2 * H; ++q) {
+      if (PASS == 0) asm volatile("" ::"v"(m[q] * sc));
+      if (PASS == 2) asm volatile("" ::"v"((double)(m[q] * sc)));
+    }
+  }
+  out[blockIdx.x * blockDim.x + threadIdx.x] = sum[0] + sum[1] + sum[2] + sum[3] + sum[4] + sum[5];
+}
+
 // LDS: every wavefront owns a 512-word window (16 wavefronts per workgroup), lanes walk it with
 // unit stride, so accesses are conflict-free.  MODE 1 ds_add_f32, 2 ds_add_u32, 3 ds_add_u64,
 // 4 ds_add_f64.
@@ -132,6 +196,22 @@ float time_ms(F f, int reps = 5) {
   return ms / reps;
 }
 
+// The fastest of several row lengths and wavefronts per SIMD.
+template <int PASS, int H, int WAVES>
+double pixels(float* out, int blocks, int threads) {
+  const float ms = time_ms([&] { hipLaunchKernelGGL((k_pixels<PASS, H, WAVES>), dim3(blocks), dim3(threads), 0, 0, out, 0.001f); });
+  return double(blocks) * threads * kRows * 2 * H / ms / 1e9;
+}
+template <int PASS>
+void best_pixels(const char* name, float* out, int blocks, int threads) {
+  double best = 0.0;
+  for (double r : {pixels<PASS, 5, 8>(out, blocks, threads), pixels<PASS, 7, 8>(out, blocks, threads),
+                   pixels<PASS, 11, 8>(out, blocks, threads), pixels<PASS, 11, 6>(out, blocks, threads),
+                   pixels<PASS, 11, 4>(out, blocks, threads), pixels<PASS, 16, 4>(out, blocks, threads)})
+    best = r > best ? r : best;
+  printf("%-16s %20.3f T pairs/s\n", name, best);
+}
+
 }  // namespace
 
 int main() {
@@ -144,6 +224,10 @@ int main() {
   const double lanes = double(blocks) * threads;
   float ms = time_ms([&] { hipLaunchKernelGGL(k_fma, dim3(blocks), dim3(threads), 0, 0, out, 0.999f, 0.001f); });
   printf("v_fma_f32        %8.3f ms  %7.2f T lane-ops/s\n", ms, lanes * kIt * 8 / ms / 1e9);
+  ms = time_ms([&] { hipLaunchKernelGGL(k_one<false>, dim3(blocks), dim3(threads), 0, 0, out, 0.999f); });
+  printf("v_mul_f32        %8.3f ms  %7.2f T lane-ops/s\n", ms, lanes * kIt * 8 / ms / 1e9);
+  ms = time_ms([&] { hipLaunchKernelGGL(k_one<true>, dim3(blocks), dim3(threads), 0, 0, out, 0.999f); });
+  printf("v_add_f32        %8.3f ms  %7.2f T lane-ops/s\n", ms, lanes * kIt * 8 / ms / 1e9);
   ms = time_ms([&] { hipLaunchKernelGGL(k_trans<false>, dim3(blocks), dim3(threads), 0, 0, out); });
   printf("v_exp_f32        %8.3f ms  %7.2f T lane-ops/s\n", ms, lanes * kIt * 8 / ms / 1e9);
   ms = time_ms([&] { hipLaunchKernelGGL(k_trans<true>, dim3(blocks), dim3(threads), 0, 0, out); });
@@ -156,6 +240,9 @@ int main() {
   printf("4 exp + 16 fma   %8.3f ms\n", ms);
   ms = time_ms([&] { hipLaunchKernelGGL(k_mix<4>, dim3(blocks), dim3(threads), 0, 0, out, 0.999f, 0.001f); });
   printf("4 exp + 32 fma   %8.3f ms\n", ms);
+  best_pixels<0>("event pass", out, blocks, threads);
+  best_pixels<1>("forward sums", out, blocks, threads);
+  best_pixels<2>("log-likelihood", out, blocks, threads);
   CHECK(hipFree(out));
 
   const int lblocks = 4096, lthreads = 1024;
