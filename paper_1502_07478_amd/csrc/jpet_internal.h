@@ -69,7 +69,8 @@ static_assert(sizeof(EvConst) == 64, "EvConst is copied to LDS in 16-byte units"
 //   S q    = s2u b1^2 + Q(r),       Q = Q0 + Q1 r + Q2 r^2
 // so that along the row, at its j-th pixel, kappa = kappa_0 + j KB pix, sqrt(S) gamma^ =
 // gs_0 + j GB pix and S q = qa j^2 + QB b1 j + S q_0 (qa = s2u pix^2, QB = 2 s2u pix).  The
-// coefficients are formed in double precision at prepare time and rounded once.
+// coefficients are formed in double precision at prepare time and rounded once.  Ring blocks measure b1 in pixels:
+// B0 and BT are divided by the pixel, KB and GB multiplied by it, s2u by its square.
 struct EvRow {
   float B0, BT;
   float K0, K1, K2, KB0, KB1;
@@ -190,9 +191,9 @@ constexpr int shape_rings(int shape) { return shape % 1000 / 100; }
 constexpr int shape_len(int shape) { return shape % 100; }
 // Wavefronts per SIMD a shape is compiled for, which leave 64, 80, 128, 168 or 256 registers for the cache and what
 // the passes need beside it: 45 to 60 registers, in the log-likelihood 70 to 80.  Where that is a few more than are
-// left the compiler spills: the event pass of 218, 326 and 1420 (2 registers), of 1344 (10; the 5 mm detector at
-// 0.5 mm pixels); batched also of 116, 1216 (2, 4) and 218 (22); the log-likelihood of 116, 1318, 1332, 1364 (1 to 4),
-// of 318 (12; sigma = (10, 63) at 2.5 mm pixels) and of 1454 (103).
+// left the compiler spills: the event pass of 218 (2) and 1344 (4; the 5 mm detector at 0.5 mm pixels); batched of
+// 326, 1420 (2), 1216 (4), 1344 (10) and 218 (14); the log-likelihood of 318 (2; sigma = (10, 63) at 2.5 mm pixels)
+// and of 1454 (47 to 58).
 constexpr int shape_waves_per_simd(int shape, bool loglik = false) {
   int cache = 0;
   for (int k = 0; k < shape_rings(shape); ++k) cache += 2 * ring_half_of(shape_rings(shape), shape_len(shape), k);

@@ -354,8 +354,9 @@ __global__ void __launch_bounds__(256) k_place(const uint32_t* __restrict__ key,
 // The per-event constants of the binned MLEM pass (EvRow) for a bin whose region starts at pixel
 // row rbase and (sheared) column kbase, in double precision.  With r the region row, the row's
 // y is Y = Yb + pix r and dy = Y - y~ = pix r - yr, both linear in r; each row constant of the
-// kernel (Eq. 7-12; see EvRow) is then a polynomial of degree <= 2 in r, expanded here.
-__device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int index, int rbase, int kbase) {
+// kernel (Eq. 7-12; see EvRow) is then a polynomial of degree <= 2 in r, expanded here.  unit: the length b1 is
+// measured in (1 mm, or the pixel for ring blocks).
+__device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int index, int rbase, int kbase, double unit) {
   const double pix = g.pixel, t = e.t, c = e.c, c2 = c * c, f = g.fa;
   const double u = g.u * e.su, w = g.w;  // u: this event's sigma_z^-2
   const double Yb = g.y0 + (double)rbase * pix;
@@ -371,26 +372,26 @@ __device__ EvRow event_row_constants(const Geo& g, const EventRec& e, int index,
   const double G1 = 2.0 * f * w * c2 * t, GG = -4.0 * g.gamma * g.R * c2 * c, GB = -2.0 * u * c2;
   const double Q3 = S * 4.0 * w * c2;                  // S q = S 2u b1^2 + Q3 dy^2
   EvRow k;
-  k.B0 = (float)(t * yr - zr);
-  k.BT = (float)(-t * pix);
+  k.B0 = (float)((t * yr - zr) / unit);
+  k.BT = (float)(-t * pix / unit);
   // Y^2 = Yb^2 + 2 Yb pix r + pix^2 r^2,  Y dy = -Yb yr + (Yb - yr) pix r + pix^2 r^2
   k.K0 = (float)(A1 * g.R * g.R + (A1 + A2) * Yb * Yb - A3 * Yb * yr + GK * (f * Yb - 2.0 * yr));
   k.K1 = (float)(((A1 + A2) * 2.0 * Yb + A3 * (Yb - yr) + GK * (f + 2.0)) * pix);
   k.K2 = (float)((A1 + A2 + A3) * pix * pix);
-  k.KB0 = (float)(KB * Yb);
-  k.KB1 = (float)(KB * pix);
+  k.KB0 = (float)(KB * Yb * unit);
+  k.KB1 = (float)(KB * pix * unit);
   k.S0 = (float)(rs * (-G1 * Yb * yr - GG * yr));
   k.S1 = (float)(rs * (G1 * (Yb - yr) + GG) * pix);
   k.S2 = (float)(rs * G1 * pix * pix);
-  k.GB0 = (float)(rs * GB * Yb);
-  k.GB1 = (float)(rs * GB * pix);
+  k.GB0 = (float)(rs * GB * Yb * unit);
+  k.GB1 = (float)(rs * GB * pix * unit);
   k.Q0 = (float)(Q3 * yr * yr);
   k.Q1 = (float)(-2.0 * Q3 * yr * pix);
   k.Q2 = (float)(Q3 * pix * pix);
   const double s2u = S * 2.0 * u;
   k.qa = (float)(s2u * pix * pix);
   k.QB = (float)(2.0 * s2u * pix);
-  k.s2u = (float)s2u;
+  k.s2u = (float)(s2u * unit * unit);
   k.index = index;
   k.mid = 0;
   return k;
@@ -522,7 +523,7 @@ __global__ void __launch_bounds__(1024) k_build_batches(Geo g, Plan p, const Eve
         k.pad[0] = k.pad[1] = 0;
         reinterpret_cast<EvConst*>(blk)[tid] = k;
       } else {
-        reinterpret_cast<EvRow*>(blk)[tid] = event_row_constants(g, e, j, rbase, kbase);
+        reinterpret_cast<EvRow*>(blk)[tid] = event_row_constants(g, e, j, rbase, kbase, 1.0);
       }
     }
     __syncthreads();
@@ -705,23 +706,23 @@ __device__ __forceinline__ bool row_interval_fast(const RowsOf& e, int x, int n_
 // row_mode for all rows of an event (half height X rows, at most 2 H pixels long) at once: over each of
 // eight bands of rows with the largest value that each of its terms has there.  kRowExact: not decided
 // by these bounds.
-__device__ inline int all_rows_mode(const EvRow& c, float X, int H, float pixf, float pix2) {
+__device__ inline int all_rows_mode(const EvRow& c, float X, int H) {
   int mode = (int)kRowPoly5;
   const float h = 0.125f * X;
   for (int s = 0; s < 8; ++s) {
     const float x = ((float)s - 3.5f) * 0.25f * X, out = (fabsf(x) - h) / X;  // band centre, its inner edge
     const int M = min(H, (int)(sqrtf(1.0f - out * out) * (float)H) + 1);
     const float kb = fabsf(fmaf(c.KB1, x, c.KB0)) + fabsf(c.KB1) * h, gb = fabsf(fmaf(c.GB1, x, c.GB0)) + fabsf(c.GB1) * h;
-    const float b1 = (float)(M + 1) * pixf;  // of a row's centre, rows cut by the grid's edge included
+    const float b1 = (float)(M + 1);  // of a row's centre, rows cut by the grid's edge included
     RowF k;
     k.kap0 = fmaf(fmaf(c.K2, x, c.K1), x, c.K0) - fmaf(fabsf(c.K2), h, fabsf(fmaf(2.0f * c.K2, x, c.K1))) * h - kb * b1;
-    k.dkap = kb * pixf;
+    k.dkap = kb;
     // (signs that add up in w and in the slope)
     k.gs0 = -(fabsf(fmaf(fmaf(c.S2, x, c.S1), x, c.S0)) + fmaf(fabsf(c.S2), h, fabsf(fmaf(2.0f * c.S2, x, c.S1))) * h +
               gb * b1);
-    k.dgs = gb * pixf;
-    k.qa = c.s2u * pix2;
-    k.qb = 2.0f * c.s2u * pixf * b1;
+    k.dgs = gb;
+    k.qa = c.s2u;
+    k.qb = 2.0f * c.s2u * b1;
     k.qc = 0.0f;
     mode = max(mode, row_mode(k, M, M, H));
   }
@@ -758,7 +759,7 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
     // polynomials in the rows from the event's central row on: the rounding of their coefficients
     // then stays below that of the rows' own values
     const int mid = centre_row(g, er);
-    EvRow k = event_row_constants(g, er, e < it.count ? j : -1, mid, kbase);  // (-1: no event)
+    EvRow k = event_row_constants(g, er, e < it.count ? j : -1, mid, kbase, g.pixel);  // (-1: no event)
     k.mid = mid - rbase;
     reinterpret_cast<EvRow*>(blk0 + (size_t)(e / epb) * (size_t)p.batch_bytes)[e % epb] = k;
     if (p.loglik) {
@@ -776,11 +777,10 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
     }
     RowsOf o = rows_of(g, er, mid, e >= it.count);
     o.mid = (int16_t)k.mid;
-    o.mode = (int16_t)all_rows_mode(k, (float)p.HY, p.ring_half[0], (float)g.pixel, (float)g.pixel * (float)g.pixel);
+    o.mode = (int16_t)all_rows_mode(k, (float)p.HY, p.ring_half[0]);
     rows_s[e] = o;
   }
   __syncthreads();
-  const float pixf = (float)g.pixel, pix2 = pixf * pixf;
   int outside = 0;
   unsigned long long pairs = 0;
   for (int q = tid >> 6; q < nblk; q += blockDim.x >> 6) {
@@ -813,7 +813,7 @@ __global__ void __launch_bounds__(256, 6) k_build_rings(Geo g, Plan p, const Eve
         m = er.mode;
         if (m == (int)kRowExact) {
           const EvRow& c = reinterpret_cast<const EvRow*>(blk)[lane / lpe];
-          m = row_mode(ring_constants(c, (float)x, kc + off_s[i - rbase] - kbase, pixf, pix2), nl, nr, p.ring_half[k]);
+          m = row_mode(ring_constants(c, (float)x, kc + off_s[i - rbase] - kbase), nl, nr, p.ring_half[k]);
         }
         // the chunks of two pairs the pass runs for this ring, from the row's centre, stay in the region and
         // its slack

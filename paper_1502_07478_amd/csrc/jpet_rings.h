@@ -212,7 +212,6 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
   const int kmin = -max(shear_offset(g, tc, 0), shear_offset(g, tc, g.n_y - 1));
   const int rbase = ty * p.TY - p.HY;
   const int kbase = kmin + tz * p.TZ - p.HZ;
-  const float pixf = uniform_f((float)g.pixel), pix2 = uniform_f(pixf * pixf);
 
   // a block's constants (16 bytes per lane to LDS), words and ring tails
   uint32_t word[kWords];
@@ -304,7 +303,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
         const uint32_t tw = tail(k);
         const int wlh = (int)((tw & 127u) + 1) >> 1, wminh = (int)((tw >> 7) & 127u) >> 1;
         const RingRow r = row(k, H);
-        const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
+        const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl]);
         at[k] = (r.kc - H) * pitch + r.rl;
         const float* const rr = rho_s + at[k];
         RowP rp;
@@ -351,7 +350,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const float up = bits ? 18446744073709551616.0f : 1.0f;
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
-      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
+      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl]);
       for (int j = -r.nl; j < r.nr; ++j)
         D = fmaf(exact_at(rk, (float)j + 0.5f, &nbad), rho_s[(r.kc + j) * pitch + r.rl] * up, D);
     }
@@ -364,7 +363,7 @@ __device__ __forceinline__ void ring_item(const Geo& g, const Plan& p, const uns
     const float sc = (float)(__builtin_ldexp(1.0, p.acc_shift) / (De * lift));
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
-      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], pixf, pix2);
+      const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl]);
       for (int j = -r.nl; j < r.nr; ++j) {
         const int px = (r.kc + j) * pitch + r.rl;
         const float m = exact_at(rk, (float)j + 0.5f, &again) * rho_s[px] * lift;

@@ -9,8 +9,8 @@
 // with S0 among them, against 8 for the sums pixel by pixel.
 //
 // Bound by VALU issue, as the event pass is.  1M events, 977M pairs on 200^2 of 2.5 mm (shape 318): 1.81 ms
-// with the sums pixel by pixel on the former batches, 0.97 ms here (1.0e12 pairs/s).  The value alone, 400k
-// events on the same grid: 0.36 ms and 0.25 ms.
+// with the sums pixel by pixel on the former batches, 0.97 ms here (1.0e12 pairs/s).  A call for the
+// value alone, 400k prepared events on the same grid: 467 us and 214.
 #pragma once
 
 #include <type_traits>
@@ -41,25 +41,27 @@ struct Moments {
 
 // Geometry constants of the derivatives, in scalar registers.
 struct LogGeo {
-  float pix, pix2, fa, iu, iw, cu, cw, iS2u;
+  float pix, fa, qlo;  // qlo: see row_poly
 };
 
-// A row's sums of v dlogP/du and v dlogP/dw from S0, X, G, H (see RowD); x: the row from its event's
-// central row on.
+// A row's parts of the derivatives of log D with respect to u and w, from S0, X, G, H (see RowD); x: the row from its
+// event's central row on.  With A and B their sums over an event's rows,
+//   D_u / D = cu - 1 / (2 u) + A / (2 S u D),  D_w / D = cw - B / (2 S w D),
+// whose constants are applied in double precision, event by event: what they multiply cancels to a few percent over the
+// events, and a constant rounded to 2^-25 would leave its share in every one of them.  The constants inside A and B
+// multiply terms of some percent of the others.
 __device__ __forceinline__ void row_derivatives(const EvRow& c, const EvLog& q, float x, const LogGeo& g,
-                                                float S0, float X, float G, float H, float& du, float& dw) {
+                                                float S0, float X, float G, float H, float& A, float& B) {
   const float irs = 1.1774100225154747f;  // 1 / sqrt(log2(e) / 2)
-  const float iS = 1.3862943611198906f;   // 1 / (log2(e) / 2)
+  const float S2 = 1.4426950408889634f;   // log2(e)
   const float Y = fmaf(x, g.pix, q.Y0), dy = fmaf(x, g.pix, -q.yr);
   const float wKl = Y * fmaf(q.A2, Y, q.A3 * dy);
   const float cr = fmaf(q.GK, fmaf(g.fa, Y, 2.0f * dy), wKl);
   const float er = irs * fmaf(fmaf(c.S2, x, c.S1), x, c.S0);
   const float wGl = fmaf(-q.GG, dy, er);
   const float SwBl = fmaf(fmaf(c.Q2, x, c.Q1), x, c.Q0);
-  const float a0 = fmaf(SwBl, g.iS2u, g.cu - 0.5f * g.iu);
-  const float b0 = fmaf(-0.5f * iS * g.iw, SwBl, g.cw);
-  du = fmaf(a0, S0, fmaf(g.iS2u, X, fmaf(-g.iu * irs * er, G, 0.5f * g.iu * cr * H)));
-  dw = fmaf(b0, S0, fmaf(irs * g.iw * wGl, G, -0.5f * g.iw * wKl * H));
+  A = fmaf(SwBl, S0, fmaf(S2, fmaf(-irs * er, G, 0.5f * cr * H), X));
+  B = fmaf(SwBl, S0, -S2 * fmaf(irs * wGl, G, -0.5f * wKl * H));
 }
 
 // X, G and H of a row from its moments.
@@ -221,13 +223,9 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
   const int kbase = kmin + tz * p.TZ - p.HZ;
   LogGeo lg;
   lg.pix = uniform_f((float)g.pixel);
-  lg.pix2 = uniform_f(lg.pix * lg.pix);
   lg.fa = uniform_f((float)g.fa);
-  lg.iu = uniform_f((float)(1.0 / g.u));
-  lg.iw = uniform_f((float)(1.0 / g.w));
-  lg.cu = uniform_f((float)g.cu);
-  lg.cw = uniform_f((float)g.cw);
-  lg.iS2u = uniform_f((float)(1.0 / (kHalfLog2e * 2.0 * g.u)));
+  const double s2u = kHalfLog2e * 2.0 * g.u * g.pixel * g.pixel;  // (u in pixels, as the blocks have it rounded)
+  lg.qlo = uniform_f((float)(s2u - (double)(float)s2u));
 
   uint32_t word[kWords];
   uint2 tails;
@@ -309,15 +307,15 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
           const int wlh = (int)((tw & 127u) + 1) >> 1;
           const RingRow r = row(k, wlh);
           const float x = (float)(lrow + k * lstep);
-          const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl], lg.pix, lg.pix2);
+          const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl]);
           const float* const rr = rho_s + r.kc * pitch + r.rl;
           RowP rp;
           float F, S;
           if ((tw >> 14) == kRowPoly5) {
-            F = row_poly<5>(rk, (float)r.nr - 0.5f, rp);
+            F = row_poly<5>(rk, (float)r.nr - 0.5f, rp, lg.qlo);
             S = ring_value<5>(rp, rr, pitch, r.nl, r.nr, wlh);
           } else {
-            F = row_poly<6>(rk, (float)r.nr - 0.5f, rp);
+            F = row_poly<6>(rk, (float)r.nr - 0.5f, rp, lg.qlo);
             S = ring_value<6>(rp, rr, pitch, r.nl, r.nr, wlh);
           }
           if (r.nr > 0) D = fmaf(F, S, D);
@@ -336,19 +334,19 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
           const int wlh = (int)((tw & 127u) + 1) >> 1, wminh = (int)((tw >> 7) & 127u) >> 1;
           const RingRow r = row(k, H);
           const float x = (float)(lrow + k * lstep);
-          const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl], lg.pix, lg.pix2);
+          const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl]);
           const float* const rr = rho_s + (r.kc - H) * pitch + r.rl;
           RowP rp;
           float S0, X, G, Hs;
           if ((tw >> 14) == kRowPoly5) {
             Moments<5> M;
-            F[k] = row_poly<5>(rk, (float)r.nr - 0.5f, rp);
+            F[k] = row_poly<5>(rk, (float)r.nr - 0.5f, rp, lg.qlo);
             ring_moments<H, 5>(rp, rr, pitch, r.nl, r.nr, wminh, wlh, cache.template ring<k>(), M);
             row_sums<5>(rk, M, X, G, Hs);
             S0 = M.m[0];
           } else {
             Moments<6> M;
-            F[k] = row_poly<6>(rk, (float)r.nr - 0.5f, rp);
+            F[k] = row_poly<6>(rk, (float)r.nr - 0.5f, rp, lg.qlo);
             ring_moments<H, 6>(rp, rr, pitch, r.nl, r.nr, wminh, wlh, cache.template ring<k>(), M);
             row_sums<6>(rk, M, X, G, Hs);
             S0 = M.m[0];
@@ -390,7 +388,7 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
     for (int k = first; k < RINGS; ++k) {
       const RingRow r = row(k, 0);
       const float x = (float)(lrow + k * lstep), iS = 1.3862943611198906f;
-      const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl], lg.pix, lg.pix2);
+      const RowF rk = ring_constants(c, x, r.kc + off_s[r.rl]);
       float S0 = 0.0f, X = 0.0f, G = 0.0f, H = 0.0f;
       for (int j = -r.nl; j < r.nr; ++j) {
         const float xj = (float)j + 0.5f;
@@ -425,7 +423,7 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
       const float invD = De > 0.0 ? (float)(1.0 / De) : 0.0f;
       for (int k = first; k < RINGS; ++k) {
         const RingRow r = row(k, 0);
-        const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl], lg.pix, lg.pix2);
+        const RowF rk = ring_constants(c, (float)(lrow + k * lstep), r.kc + off_s[r.rl]);
         for (int j = -r.nl; j < r.nr && invD > 0.0f; ++j)
           unsafeAtomicAdd(&acc_s[(r.kc + j) * pitch + r.rl], (double)(exact_at(rk, (float)j + 0.5f, &again) * invD));
       }
@@ -433,16 +431,17 @@ __device__ __forceinline__ void loglik_item(const Geo& g, const Plan& p, const u
   }
   __syncthreads();
 
-  // the events' logarithms and ratios
+  // the events' logarithms and ratios (see row_derivatives; b1^2 enters A by the blocks' rounded s2u)
   double a[3] = {0.0, 0.0, 0.0};
+  const double cu = g.cu - 0.5 / g.u, iu = g.pixel * g.pixel / (double)(float)s2u, iw = 0.5 / (kHalfLog2e * g.w);
   unsigned zero = 0;
   for (int e = tid; e < it.count; e += (int)blockDim.x) {
     const double D = D_s[e];
     if (D > 0.0) {
       a[0] += log(D);
       if constexpr (!VALUE) {
-        a[1] += (double)Du_s[e] / D;
-        a[2] += (double)Dw_s[e] / D;
+        a[1] += cu + iu * ((double)Du_s[e] / D);
+        a[2] += g.cw - iw * ((double)Dw_s[e] / D);
       }
     } else {
       ++zero;

@@ -20,18 +20,19 @@ struct RowF {
 };
 
 // The constants at the centre of a row of a ring block: x the row from its event's central row on, col
-// the first pixel right of the centre (region-local column plus the row's shift).
-__device__ __forceinline__ RowF ring_constants(const EvRow& c, float x, int col, float pixf, float pix2) {
-  const float b1 = fmaf(pixf, (float)col - 0.5f, fmaf(c.BT, x, c.B0));
+// the first pixel right of the centre (region-local column plus the row's shift).  b1 is in pixels, so that one
+// rounded constant, s2u, stands for u in every term of S q.
+__device__ __forceinline__ RowF ring_constants(const EvRow& c, float x, int col) {
+  const float b1 = ((float)col - 0.5f) + fmaf(c.BT, x, c.B0);
   const float kb = fmaf(c.KB1, x, c.KB0), gb = fmaf(c.GB1, x, c.GB0);
   const float sb = c.s2u * b1;
   RowF k;
   k.kap0 = fmaf(kb, b1, fmaf(fmaf(c.K2, x, c.K1), x, c.K0));
-  k.dkap = kb * pixf;
+  k.dkap = kb;
   k.gs0 = fmaf(gb, b1, fmaf(fmaf(c.S2, x, c.S1), x, c.S0));
-  k.dgs = gb * pixf;
-  k.qa = c.s2u * pix2;
-  k.qb = (sb + sb) * pixf;
+  k.dgs = gb;
+  k.qa = c.s2u;
+  k.qb = sb + sb;
   k.qc = fmaf(sb, b1, fmaf(fmaf(c.Q2, x, c.Q1), x, c.Q0));
   return k;
 }
@@ -58,15 +59,17 @@ constexpr float kHalfLog2eF = 0.72134752044448170368f;
 // previous batch's value would keep the whole cache live through pass 1).
 __device__ __forceinline__ float unread() { return __builtin_nondeterministic_value(0.0f); }
 
-// The polynomial form of a row; half: the largest |x| of its pixels.  Returns F.
+// The polynomial form of a row; half: the largest |x| of its pixels; qlo: what qa has lost by its rounding, the same
+// for all rows (the log-likelihood's derivatives sum over many events what is left of terms that cancel).
+// Returns F.
 template <int DEG>
-__device__ __forceinline__ float row_poly(const RowF& k, float half, RowP& p) {
+__device__ __forceinline__ float row_poly(const RowF& k, float half, RowP& p, float qlo = 0.0f) {
   const float rq = __builtin_amdgcn_rsqf(k.kap0);
   const float dl = k.dkap * (rq * rq);
   const float h0 = k.gs0 * rq, h1 = k.dgs * rq;
   const float d = fmaf(-dl, h0, h1), w = d * d, dl2 = dl * dl;
   p.c1 = fmaf(h0, h1 + d, -fmaf(kHalfLog2eF, dl, k.qb));
-  p.c2 = fmaf(0.5f * kHalfLog2eF, dl2, w - k.qa);
+  p.c2 = fmaf(0.5f * kHalfLog2eF, dl2, (w - qlo) - k.qa);
   p.c3 = -dl * fmaf(kHalfLog2eF / 3.0f, dl2, w);
   if constexpr (DEG == 5) {  // the logarithm's x^4 and x^5 terms only nearly, within row_mode's bound
     p.c4 = -dl * p.c3;
